@@ -1,0 +1,70 @@
+"""The 3-D residual kernel (marching along z, tiles with and without a halo)
+against the sum-factorised form in float64 torch on the CPU.
+
+The 1-D spatial and temporal matrices are the oracle's.  The tolerance is the
+a-priori bound of both evaluations: at most d = 5 (2p + 1) + 2 N_t + 4 roundings on
+the way to each entry (z, time, x and y sums), each relative to the sum of the
+absolute values of its terms, which the same sums give with absolute factors;
+1-D matrix entries of the two sides agree to 1e-14 of their largest.
+"""
+import numpy as np
+import pytest
+
+from oracle.spacetime import Problem, time_matrices, space_matrices_1d
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _apply(mats, v):
+    """mats[a] along the last three axes (z, y, x) of v (slab, time, z, y, x)."""
+    for a, m in enumerate(mats):
+        v = torch.tensordot(v, m, dims=([a + 2], [1])).movedim(-1, a + 2)
+    return v
+
+
+def _mix(m, v):
+    return torch.tensordot(v, m, dims=([1], [1])).movedim(-1, 1)
+
+
+def _operator(Kt, Mt, M, K, u):
+    mass = _apply([M, M, M], u)
+    stiff = _apply([K, M, M], u) + _apply([M, K, M], u) + _apply([M, M, K], u)
+    y = _mix(Kt, mass) + _mix(Mt, stiff)
+    return y, mass[:, -1]
+
+
+# whole-plane tiles (n <= 22), rows of several tiles, tiles in both axes with
+# remainders, a plane smaller than the band, one slab, chunked z, p = 4 with
+# N_t = 8 (the per-tile kernel) and every degree
+@pytest.mark.parametrize("n_elem,degree,n_slabs,n_elem_t", [
+    (2, 1, 3, 1), (2, 2, 1, 2), (3, 3, 5, 1), (2, 4, 2, 1), (19, 4, 2, 1), (21, 3, 3, 1), (20, 2, 40, 1),
+    (23, 1, 4, 7), (33, 2, 3, 2), (30, 3, 2, 2), (26, 4, 2, 2), (47, 2, 2, 1), (70, 1, 2, 1), (12, 4, 2, 4),
+    (16, 3, 2, 5), (17, 2, 3, 6),
+])
+def test_residual_3d(n_elem, degree, n_slabs, n_elem_t):
+    import paper_1802_09277_amd as sth
+    prob = Problem(3, n_elem, degree, n_slabs, n_elem_t)
+    Kt, Mt = (torch.from_numpy(np.asarray(m)) for m in time_matrices(0.0, prob.tau, n_elem_t, degree, prob.sigma))
+    M, K = (torch.from_numpy(np.ascontiguousarray(m)) for m in space_matrices_1d(n_elem, degree))
+    n, nt = prob.n, prob.N_t
+    g = torch.Generator().manual_seed(7)
+    shape = (n_slabs, nt, n, n, n)
+    f, u = (torch.randn(shape, generator=g, dtype=torch.float64) for _ in range(2))
+    y, last = _operator(Kt, Mt, M, K, u)
+    y[1:, 0] -= last[:-1]
+    bound, blast = _operator(Kt.abs(), Mt.abs(), M.abs(), K.abs(), u.abs())
+    bound[1:, 0] += blast[:-1]
+    bound = bound + f.abs()
+    s = sth.Solver(3, n_elem, degree, n_slabs, n_elem_t)
+    r, a = s.new_vector(), s.new_vector()
+    uc = u.reshape(-1).cuda()
+    s.residual(f.reshape(-1).cuda(), uc, r)
+    s.apply(uc, a)
+    eps = np.finfo(np.float64).eps
+    tol = 2 * (5 * (2 * degree + 1) + 2 * nt + 4) * eps + 8e-14
+    for got, want in ((r, f - y), (a, y)):
+        err = ((got.cpu().reshape(shape) - want).abs() / bound).max().item()
+        print(f"  n={n} p={degree} S={n_slabs} N_t={nt}: {err:.2e} of the bound {tol:.2e}")
+        assert err <= tol
+    s.close()
