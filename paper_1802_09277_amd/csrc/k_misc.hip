@@ -354,26 +354,49 @@ hipError_t launch_rhs(int dim, int Nt, int n, int n_modes, const double* Tpart, 
 // Krylov support (FGMRES outer loop): k <= kMaxKrylov vectors stored one
 // after the other with stride ld.
 // ---------------------------------------------------------------------------
-// partial[b * kMaxKrylov + i] = block b's share of <V_i, w>, i < k; the
-// elements of a block and the lanes of the reduction are visited in a fixed
-// order, so the result does not depend on timing
-__global__ __launch_bounds__(256) void k_multidot(const double* __restrict__ V, long ld, int k,
-                                                  const double* __restrict__ w, long len,
-                                                  double* __restrict__ partial) {
-    double acc[kMaxKrylov];
-#pragma unroll
-    for (int i = 0; i < kMaxKrylov; ++i) acc[i] = 0.0;
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < len; e += (long)gridDim.x * 256) {
-        const double we = w[e];
-#pragma unroll
-        for (int i = 0; i < kMaxKrylov; ++i)
-            if (i < k) acc[i] += V[i * ld + e] * we;
+// Gram-Schmidt passes of FGMRES over k Krylov vectors V_i (KM: the bound on k
+// its registers are sized for), each bound by one read of the k + 1 vectors:
+//   AXPY: w[e] -= sum_i c[i] V_i[e] first (c on the device, so no host round
+//         trip between a projection and the next),
+//   DOTS: partial sums of <V_i, w> with the updated w, from the same read of
+//         V_i (a second read of the basis saved), else of <w, w>.
+// Sums go to partial[i gridDim + block], in a fixed order.
+template <int KM, bool AXPY, bool DOTS>
+__global__ __launch_bounds__(256) void k_krylov(const double* __restrict__ V, long ld, int k,
+                                                const double* __restrict__ c, double* __restrict__ w, long len,
+                                                double* __restrict__ partial) {
+    constexpr int NA = DOTS ? KM : 1;
+    __shared__ double cs[KM];
+    if (AXPY) {
+        if ((int)threadIdx.x < k) cs[threadIdx.x] = c[threadIdx.x];
+        __syncthreads();
     }
-    __shared__ double red[4][kMaxKrylov];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double acc[NA];
 #pragma unroll
-    for (int i = 0; i < kMaxKrylov; ++i) {
-        if (i < k) {
+    for (int i = 0; i < NA; ++i) acc[i] = 0.0;
+    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < len; e += (long)gridDim.x * 256) {
+        double we = w[e], v[KM];
+#pragma unroll
+        for (int i = 0; i < KM; ++i) v[i] = i < k ? V[i * ld + e] : 0.0;
+        if (AXPY) {
+#pragma unroll
+            for (int i = 0; i < KM; ++i)
+                if (i < k) we -= cs[i] * v[i];
+            w[e] = we;
+        }
+        if (DOTS) {
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                if (i < k) acc[i] += v[i] * we;
+        } else {
+            acc[0] += we * we;
+        }
+    }
+    __shared__ double red[4][NA];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ns = DOTS ? k : 1;
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        if (i < ns) {
             double v = acc[i];
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -381,48 +404,97 @@ __global__ __launch_bounds__(256) void k_multidot(const double* __restrict__ V, 
         }
     }
     __syncthreads();
-    if ((int)threadIdx.x < k)
-        partial[(long)blockIdx.x * kMaxKrylov + threadIdx.x] =
+    if ((int)threadIdx.x < ns)
+        partial[(long)threadIdx.x * gridDim.x + blockIdx.x] =
             (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
 }
 
-__global__ __launch_bounds__(64) void k_multidot_final(const double* __restrict__ partial, int blocks, int k,
-                                                       double* __restrict__ out) {
-    const int i = threadIdx.x;
-    if (i >= k) return;
+// out[i] = sum of the `blocks` partials of sum i, one block per sum (one
+// thread walking the 1024 partials of a sum by itself took 265 us)
+__global__ __launch_bounds__(256) void k_krylov_final(const double* __restrict__ partial, int blocks,
+                                                      double* __restrict__ out) {
+    __shared__ double sh[256];
     double s = 0.0;
-    for (int b = 0; b < blocks; ++b) s += partial[(long)b * kMaxKrylov + i];
-    out[i] = s;
+    for (int b = threadIdx.x; b < blocks; b += 256) s += partial[(long)blockIdx.x * blocks + b];
+    const double tot = block_sum_256(s, sh);
+    if (threadIdx.x == 0) out[blockIdx.x] = tot;
+}
+
+// w *= 1 / sqrt(*n2) where *n2 > 0
+__global__ __launch_bounds__(256) void k_normalize(double* __restrict__ w, long len, const double* __restrict__ n2) {
+    const double s = *n2;
+    if (!(s > 0.0)) return;
+    const double a = 1.0 / sqrt(s);
+    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < len; e += (long)gridDim.x * 256) w[e] *= a;
 }
 
 // w[e] = alpha w[e] + sum_{i<k} c[i] V_i[e]  (c on the device)
+template <int KM>
 __global__ __launch_bounds__(256) void k_multiaxpy(const double* __restrict__ V, long ld, int k,
                                                    const double* __restrict__ c, double alpha,
                                                    double* __restrict__ w, long len) {
-    __shared__ double cs[kMaxKrylov];
+    __shared__ double cs[KM];
     if ((int)threadIdx.x < k) cs[threadIdx.x] = c[threadIdx.x];
     __syncthreads();
     for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < len; e += (long)gridDim.x * 256) {
-        double v = alpha * w[e];
-        for (int i = 0; i < k; ++i) v += cs[i] * V[i * ld + e];
-        w[e] = v;
+        double we = alpha * w[e], v[KM];
+#pragma unroll
+        for (int i = 0; i < KM; ++i) v[i] = i < k ? V[i * ld + e] : 0.0;
+#pragma unroll
+        for (int i = 0; i < KM; ++i)
+            if (i < k) we += cs[i] * v[i];
+        w[e] = we;
     }
 }
 
 static const int kKrylovBlocks = 1024;
 
-hipError_t launch_multidot(const double* V, long ld, int k, const double* w, long len, double* partial, double* out,
-                           hipStream_t st) {
+template <bool AXPY, bool DOTS>
+static hipError_t krylov_pass(const double* V, long ld, int k, const double* c, double* w, long len, double* partial,
+                              double* out, hipStream_t st) {
     if (k < 1 || k > kMaxKrylov || len <= 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_multidot, dim3(kKrylovBlocks), dim3(256), 0, st, V, ld, k, w, len, partial);
-    hipLaunchKernelGGL(k_multidot_final, dim3(1), dim3(64), 0, st, partial, kKrylovBlocks, k, out);
+    const dim3 g(kKrylovBlocks), b(256);
+    if (k <= 4)
+        hipLaunchKernelGGL((k_krylov<4, AXPY, DOTS>), g, b, 0, st, V, ld, k, c, w, len, partial);
+    else if (k <= 12)
+        hipLaunchKernelGGL((k_krylov<12, AXPY, DOTS>), g, b, 0, st, V, ld, k, c, w, len, partial);
+    else
+        hipLaunchKernelGGL((k_krylov<kMaxKrylov, AXPY, DOTS>), g, b, 0, st, V, ld, k, c, w, len, partial);
+    hipLaunchKernelGGL(k_krylov_final, dim3(DOTS ? k : 1), b, 0, st, partial, kKrylovBlocks, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_multidot(const double* V, long ld, int k, double* w, long len, double* partial, double* out,
+                           hipStream_t st) {
+    return krylov_pass<false, true>(V, ld, k, nullptr, w, len, partial, out, st);
+}
+
+hipError_t launch_project_dot(const double* V, long ld, int k, const double* c, double* w, long len, double* partial,
+                              double* out, hipStream_t st) {
+    return krylov_pass<true, true>(V, ld, k, c, w, len, partial, out, st);
+}
+
+hipError_t launch_project_norm(const double* V, long ld, int k, const double* c, double* w, long len, double* partial,
+                               double* out, hipStream_t st) {
+    return krylov_pass<true, false>(V, ld, k, c, w, len, partial, out, st);
+}
+
+hipError_t launch_normalize(double* w, long len, const double* n2, hipStream_t st) {
+    if (len <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_normalize, dim3(kKrylovBlocks), dim3(256), 0, st, w, len, n2);
     return hipGetLastError();
 }
 
 hipError_t launch_multiaxpy(const double* V, long ld, int k, const double* c, double alpha, double* w, long len,
                             hipStream_t st) {
     if (k < 0 || k > kMaxKrylov || len <= 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_multiaxpy, dim3(kKrylovBlocks), dim3(256), 0, st, V, ld, k, c, alpha, w, len);
+    const dim3 g(kKrylovBlocks), b(256);
+    if (k <= 4)
+        hipLaunchKernelGGL(k_multiaxpy<4>, g, b, 0, st, V, ld, k, c, alpha, w, len);
+    else if (k <= 12)
+        hipLaunchKernelGGL(k_multiaxpy<12>, g, b, 0, st, V, ld, k, c, alpha, w, len);
+    else
+        hipLaunchKernelGGL(k_multiaxpy<kMaxKrylov>, g, b, 0, st, V, ld, k, c, alpha, w, len);
     return hipGetLastError();
 }
 

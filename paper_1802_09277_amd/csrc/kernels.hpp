@@ -285,12 +285,21 @@ hipError_t launch_fill(double* v, long len, double val, hipStream_t st, const in
 // *flag = 1 if some entry of v[0..len) is not zero (NaN included), else 0
 hipError_t launch_any_nonzero(const double* v, long len, int* flag, hipStream_t st);
 
-// Krylov vectors V_i = V + i*ld (i < k <= kMaxKrylov), for the FGMRES loop:
-//  out[i] = <V_i, w> (deterministic; partial needs 1024 * kMaxKrylov entries)
-//  w = alpha w + sum_i c[i] V_i (c: k device values)
+// Krylov vectors V_i = V + i*ld (1 <= k <= kMaxKrylov of them), for the
+// FGMRES loop; sums are deterministic, partial needs 1024 * kMaxKrylov
+// entries, c and out are device values:
+//  out[i] = <V_i, w>
 constexpr int kMaxKrylov = 32;
-hipError_t launch_multidot(const double* V, long ld, int k, const double* w, long len, double* partial, double* out,
+hipError_t launch_multidot(const double* V, long ld, int k, double* w, long len, double* partial, double* out,
                            hipStream_t st);
+//  w -= sum_i c[i] V_i, then out[i] = <V_i, w> (project_dot) or out[0] = <w, w> (project_norm)
+hipError_t launch_project_dot(const double* V, long ld, int k, const double* c, double* w, long len, double* partial,
+                              double* out, hipStream_t st);
+hipError_t launch_project_norm(const double* V, long ld, int k, const double* c, double* w, long len, double* partial,
+                               double* out, hipStream_t st);
+//  w /= sqrt(*n2) where *n2 > 0
+hipError_t launch_normalize(double* w, long len, const double* n2, hipStream_t st);
+//  w = alpha w + sum_i c[i] V_i (k may be 0)
 hipError_t launch_multiaxpy(const double* V, long ld, int k, const double* c, double alpha, double* w, long len,
                             hipStream_t st);
 

@@ -123,7 +123,7 @@ struct sth_handle {
     int k_alloc = 0;                    // restart length the workspace holds
     double* kv = nullptr;               // (restart+1) Krylov vectors
     double* kz = nullptr;               // restart preconditioned vectors
-    double* kc = nullptr;               // kMaxKrylov coefficients / dot products
+    double* kc = nullptr;               // projection coefficients and squared norm (kKrylovScalars)
     double* kpart = nullptr;            // 1024 x kMaxKrylov partial sums
     double* khost = nullptr;            // pinned copy of kc
     double nb_lo = 0.0;                 // ||(I (x) C) r^||^2 >= nb_lo ||r^||^2
@@ -2588,6 +2588,9 @@ static int precondition(sth_handle* h, const double* v, double* z, hipStream_t s
                          h->f32 ? 1 : 0);
 }
 
+// coefficients of the two projections (kMaxKrylov each) and the squared norm
+constexpr int kKrylovScalars = 2 * kMaxKrylov + 1;
+
 static int krylov_workspace(sth_handle* h, int m) {
     if (h->k_alloc >= m) return STH_OK;
     for (double** q : {&h->kv, &h->kz, &h->kc, &h->kpart})
@@ -2597,9 +2600,9 @@ static int krylov_workspace(sth_handle* h, int m) {
     const size_t len = (size_t)h->lev_S[0] * slab_len(h);
     if (hipMalloc((void**)&h->kv, sizeof(double) * len * (m + 1)) != hipSuccess ||
         hipMalloc((void**)&h->kz, sizeof(double) * len * m) != hipSuccess ||
-        hipMalloc((void**)&h->kc, sizeof(double) * kMaxKrylov) != hipSuccess ||
+        hipMalloc((void**)&h->kc, sizeof(double) * kKrylovScalars) != hipSuccess ||
         hipMalloc((void**)&h->kpart, sizeof(double) * 1024 * kMaxKrylov) != hipSuccess ||
-        hipHostMalloc((void**)&h->khost, sizeof(double) * kMaxKrylov, 0) != hipSuccess)
+        hipHostMalloc((void**)&h->khost, sizeof(double) * kKrylovScalars, 0) != hipSuccess)
         return fail(STH_ENOMEM, "FGMRES workspace allocation failed");
     h->k_alloc = m;
     return STH_OK;
@@ -2631,8 +2634,6 @@ int sth_solve_fgmres(sth_handle* h, const double* f, double* u, double rtol, int
         rn = beta;
         if (!std::isfinite(beta)) break;
         if (beta <= rtol * fn || it >= maxit) break;
-        h->khost[0] = 1.0 / beta;
-        HIPCHK(hipMemcpyAsync(h->kc, h->khost, sizeof(double), hipMemcpyHostToDevice, st));
         HIPCHK(launch_multiaxpy(V, len, 0, h->kc, 1.0 / beta, V, len, st));       // V_0 = r / beta
         std::fill(g.begin(), g.end(), 0.0);
         g[0] = beta;
@@ -2643,22 +2644,20 @@ int sth_solve_fgmres(sth_handle* h, const double* f, double* u, double rtol, int
             double* w = V + (size_t)(j + 1) * len;
             if ((rc = precondition(h, Vj, Zj, st))) return rc;
             if ((rc = residual(h, 0, nullptr, Zj, w, 0, h->lev_S[0], -1.0, st))) return rc;   // w = L z_j
-            for (int i = 0; i <= j; ++i) Hij(i, j) = 0.0;
-            for (int pass = 0; pass < 2; ++pass) {
-                HIPCHK(launch_multidot(V, len, j + 1, w, len, h->kpart, h->kc, st));
-                HIPCHK(hipMemcpyAsync(h->khost, h->kc, sizeof(double) * (j + 1), hipMemcpyDeviceToHost, st));
-                HIPCHK(hipStreamSynchronize(st));
-                for (int i = 0; i <= j; ++i) {
-                    Hij(i, j) += h->khost[i];
-                    h->khost[i] = -h->khost[i];
-                }
-                HIPCHK(hipMemcpyAsync(h->kc, h->khost, sizeof(double) * (j + 1), hipMemcpyHostToDevice, st));
-                HIPCHK(launch_multiaxpy(V, len, j + 1, h->kc, 1.0, w, len, st));
-            }
-            double hn = 0.0;
-            if ((rc = read_norm(h, w, len, st, &hn))) return rc;
+            // Gram-Schmidt twice and the normalisation, without a host round
+            // trip in between: the coefficients stay on the device and come
+            // to the host together
+            double* c2 = h->kc + kMaxKrylov;
+            double* n2 = h->kc + 2 * kMaxKrylov;
+            HIPCHK(launch_multidot(V, len, j + 1, w, len, h->kpart, h->kc, st));
+            HIPCHK(launch_project_dot(V, len, j + 1, h->kc, w, len, h->kpart, c2, st));
+            HIPCHK(launch_project_norm(V, len, j + 1, c2, w, len, h->kpart, n2, st));
+            HIPCHK(launch_normalize(w, len, n2, st));
+            HIPCHK(hipMemcpyAsync(h->khost, h->kc, sizeof(double) * kKrylovScalars, hipMemcpyDeviceToHost, st));
+            HIPCHK(hipStreamSynchronize(st));
+            for (int i = 0; i <= j; ++i) Hij(i, j) = h->khost[i] + h->khost[kMaxKrylov + i];
+            const double hn = std::sqrt(h->khost[2 * kMaxKrylov]);
             Hij(j + 1, j) = hn;
-            if (hn > 0.0) HIPCHK(launch_multiaxpy(V, len, 0, h->kc, 1.0 / hn, w, len, st));
             // apply the previous rotations to column j, then a new one
             for (int i = 0; i < j; ++i) {
                 const double a = Hij(i, j), b = Hij(i + 1, j);

@@ -75,3 +75,24 @@ def test_fgmres_short_restart_and_nonconvergence():
     with pytest.raises(sth.StatusError):
         s.solve_fgmres(dev(f), u, restart=40)
     s.close()
+
+
+@pytest.mark.parametrize("restart", [4, 12, 31])
+def test_fgmres_long_bases(restart):
+    """A weakly damped cycle (omega 0.05) needs more than 12 Krylov vectors, so
+    every size of the projection kernels runs (bases up to 4, 12 and 31); the
+    result must be the direct solution to the accuracy a 1e-11 residual gives
+    (the bounds of the short-restart test above)."""
+    import paper_1802_09277_amd as sth
+    print(f"[gpu-krylov] restart {restart}, omega 0.05", flush=True)
+    prob, mg = oracle_for("2d_16slabs")
+    f = assemble_rhs(prob, W.random_modes(11, prob.dim))
+    ud = mg.levels[0].forward_substitution(f)
+    s = sth.Solver(**SHAPES["2d_16slabs"], omega=0.05)
+    u = s.new_vector()
+    it, rr, _ = s.solve_fgmres(dev(f), u, rtol=1e-11, maxit=400, restart=restart)
+    torch.cuda.synchronize()
+    err = np.linalg.norm(u.cpu().numpy() - ud) / np.linalg.norm(ud)
+    print(f"  {it} iterations, relres {rr:.2e}, error vs direct {err:.2e}")
+    assert it > 12 and rr <= 1e-11 and err <= 1e-9
+    s.close()
