@@ -1,8 +1,9 @@
 // gfx950 kernels of the space-time slab solver: the spatial eigenbasis
 // transforms one axis at a time (3-D, and 2-D images too large for the
 // LDS-resident kernels) as MFMA GEMMs in FP64, FP32 and BF16x3.  The
-// launchers take the panel kernels (transform matrix in LDS) for np <= 256;
-// the kernels here serve larger n.
+// launchers take the panel kernels (transform matrix in LDS) in the reduced
+// precisions for np <= 256 a multiple of 32, and the runtime the even/odd
+// kernels in FP64 up to n = kEoMaxN; the kernels here serve the rest.
 #include "kernels_common.hpp"
 
 namespace sth {
@@ -295,7 +296,7 @@ hipError_t launch_xform_x(int prec, int epi, const double* in, double* out, cons
                           long lines, double alpha, hipStream_t st, const int* guard, int sym, int io) {
     if (lines <= 0) return hipSuccess;
     if (epi < 0 || epi > 2 || prec < 0 || prec > 2) return hipErrorInvalidValue;
-    if (xform_panel_supported(np))
+    if (prec != 0 && xform_panel_supported(np))
         return launch_xform_panel_x_io(prec, epi, in, out, T, n, np, lines, alpha, st, guard, sym, io);
     if (sym || io) return hipErrorInvalidValue;
     dim3 grid((unsigned)((lines + 63) / 64), (unsigned)((np + 127) / 128));
@@ -314,7 +315,7 @@ hipError_t launch_xform_s(int prec, const double* in, double* out, const double*
                           long nbatch, long inner, hipStream_t st, const int* guard, int io_f32, int sym) {
     if (nbatch <= 0) return hipSuccess;
     if (prec < 0 || prec > 2) return hipErrorInvalidValue;
-    if (xform_panel_supported(np))
+    if (prec != 0 && xform_panel_supported(np))
         return launch_xform_panel_s(prec, in, out, T, n, np, nbatch, inner, st, guard, io_f32, sym);
     if (sym) return hipErrorInvalidValue;
     if (io_f32) return hipErrorInvalidValue;      // FP32 storage: the panel kernels only

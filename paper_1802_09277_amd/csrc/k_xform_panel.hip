@@ -1,8 +1,8 @@
 // gfx950 kernels of the space-time slab solver: the spatial eigenbasis
 // transforms one axis at a time (eq. equ:ST:generalDecompA with fast
-// diagonalisation of K_x + lambda M_x) for np <= 256 (a multiple of 32), as
-// MFMA GEMMs with the
-// transform matrix held in LDS and the data streamed through registers.
+// diagonalisation of K_x + lambda M_x) in FP32 and BF16x3 for np <= 256 (a
+// multiple of 32), as MFMA GEMMs with the transform matrix held in LDS and
+// the data streamed through registers.
 //
 // A block stages one panel of PW output columns of the (padded) transform
 // matrix T, all of its rows, in LDS once; then each wave works on its own
@@ -36,19 +36,12 @@ constexpr int kPanelThreads = 512;              // eight waves
 constexpr int kPanelWaves = kPanelThreads / 64;
 
 // compute types of the panel kernels
-struct PanelF64 {};
 struct PanelF32 {};
 struct PanelBf16x3 {};
 
-template <typename C> struct PanelTraits;
-template <> struct PanelTraits<PanelF64> { static constexpr int PW = 64; };
-template <> struct PanelTraits<PanelF32> { static constexpr int PW = 128; };
-template <> struct PanelTraits<PanelBf16x3> { static constexpr int PW = 128; };
-
 // LDS bytes of a panel of pw columns and kp rows
 template <typename C> static size_t panel_lds(int kp, int pw) {
-    if constexpr (std::is_same<C, PanelF64>::value) return sizeof(double) * (size_t)kp * pw;
-    else if constexpr (std::is_same<C, PanelF32>::value) return sizeof(float) * (size_t)kp * pw;
+    if constexpr (std::is_same<C, PanelF32>::value) return sizeof(float) * (size_t)kp * pw;
     else return 2 * sizeof(unsigned short) * (size_t)pw * (kp + 4);
 }
 
@@ -60,7 +53,6 @@ __global__ __launch_bounds__(kPanelThreads) void k_xform_panel(const TI* __restr
     if (guard_off(guard)) return;
     constexpr int pw = PW;                       // panel width (output columns)
     constexpr int NJT = PW / 16;                 // column tiles per wave
-    constexpr bool F64 = std::is_same<C, PanelF64>::value;
     constexpr bool BF = std::is_same<C, PanelBf16x3>::value;
     const int hn = n / 2;
     // panel rows (k), zero from np on; with the even/odd split (np = n,
@@ -86,7 +78,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_xform_panel(const TI* __restr
             split_bf16(k < np ? T[(long)k * np + j0 + jj] : 0.0, &th[jj * (KP + 4) + k], &tl[jj * (KP + 4) + k]);
         }
     } else {
-        using CT = typename std::conditional<F64, double, float>::type;
+        using CT = float;
         CT* tp = reinterpret_cast<CT*>(sm_raw);
         for (int i = tid; i < KP * pw; i += kPanelThreads) {
             const int k = i / pw, jj = i % pw;
@@ -130,7 +122,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_xform_panel(const TI* __restr
     // are in flight while group gi is in the MFMAs; only then are they
     // converted (and folded) into cur, held in the compute precision
     // (FP32 for the FP32 and BF16x3 kernels).
-    using DT = typename std::conditional<F64, double, float>::type;
+    using DT = float;
     TI ra[4][4], rb[SYM == 1 ? 4 : 1][4];
     // addresses: a wave-uniform base (scalar registers) plus a 32-bit lane
     // offset, the same for all sixteen loads of a group
@@ -283,7 +275,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_xform_panel(const TI* __restr
                          SYM == 2 ? (double)acc2[SYM == 2 ? jt : 0][r] : 0.0, old[EPI == 1 ? jt : 0][r]);
             (void)acc2;
         } else {
-            using CT = typename std::conditional<F64, double, float>::type;
+            using CT = float;
             using M = Mfma16<CT>;
             typedef typename M::acc_t acc_t;
             const CT* tp = reinterpret_cast<const CT*>(sm_raw);
@@ -382,11 +374,11 @@ static hipError_t panel_go(const TI* in, TO* out, const double* T, int n, int np
     return hipGetLastError();
 }
 
-// panel width: the widest of 128 (64 in FP64), 64, 32 that divides np (the
+// panel width: the widest of 128, 64, 32 that divides np (the
 // split transforms: n / 2)
-template <typename C> static int panel_width(int np) {
+static int panel_width(int np) {
     for (int pw : {128, 64, 32})
-        if (pw <= PanelTraits<C>::PW && np % pw == 0) return pw;
+        if (np % pw == 0) return pw;
     return 0;
 }
 
@@ -397,7 +389,6 @@ static hipError_t panel_pw(int sym, const TI* in, TO* out, const double* T, int 
         // the folding loads take a second set of registers: width 128 on the
         // x axis only (n / 2 is 64 or 128)
         if (EPI != 0) return hipErrorInvalidValue;
-        // (in FP64 too: half as many panels re-read each line)
         if constexpr (XAXIS)
             if (n == 256) return panel_go<C, 128, XAXIS, EPI, TI, TO, 1>(in, out, T, n, np, nrows, inner, ntiles, alpha, st, guard);
         return panel_go<C, 64, XAXIS, EPI, TI, TO, 1>(in, out, T, n, np, nrows, inner, ntiles, alpha, st, guard);
@@ -407,7 +398,7 @@ static hipError_t panel_pw(int sym, const TI* in, TO* out, const double* T, int 
         // whose addressing takes more registers, at half the width
         if constexpr (XAXIS) {
             // (the update epilogue holds the old outputs too: width 64)
-            if constexpr (PanelTraits<C>::PW >= 128 && EPI != 1)
+            if constexpr (EPI != 1)
                 if (n == 256) return panel_go<C, 128, XAXIS, EPI, TI, TO, 2>(in, out, T, n, np, nrows, inner, ntiles, alpha, st, guard);
             return panel_go<C, 64, XAXIS, EPI, TI, TO, 2>(in, out, T, n, np, nrows, inner, ntiles, alpha, st, guard);
         } else {
@@ -416,13 +407,11 @@ static hipError_t panel_pw(int sym, const TI* in, TO* out, const double* T, int 
             return panel_go<C, 32, XAXIS, EPI, TI, TO, 2>(in, out, T, n, np, nrows, inner, ntiles, alpha, st, guard);
         }
     }
-    switch (panel_width<C>(np)) {
+    switch (panel_width(np)) {
         case 32: return panel_go<C, 32, XAXIS, EPI, TI, TO, 0>(in, out, T, n, np, nrows, inner, ntiles, alpha, st, guard);
         case 64: return panel_go<C, 64, XAXIS, EPI, TI, TO, 0>(in, out, T, n, np, nrows, inner, ntiles, alpha, st, guard);
         case 128:
-            if constexpr (PanelTraits<C>::PW >= 128)
-                return panel_go<C, 128, XAXIS, EPI, TI, TO, 0>(in, out, T, n, np, nrows, inner, ntiles, alpha, st, guard);
-            return hipErrorInvalidValue;
+            return panel_go<C, 128, XAXIS, EPI, TI, TO, 0>(in, out, T, n, np, nrows, inner, ntiles, alpha, st, guard);
         default: return hipErrorInvalidValue;
     }
 }
@@ -440,19 +429,17 @@ static hipError_t panel_x_epi(int sym, int epi, int io, const double* in, double
         if (epi == 1) return panel_pw<C, true, 1>(sym, in, out, T, n, np, lines, 0, ntiles, alpha, st, guard);
         return panel_pw<C, true, 2>(sym, in, out, T, n, np, lines, 0, ntiles, alpha, st, guard);
     }
-    if constexpr (!std::is_same<C, PanelF64>::value) {
-        if (io == 2) {
-            if (epi != 0 || sym == 2) return hipErrorInvalidValue;
-            return panel_pw<C, true, 0, double, float>(sym, in, (float*)out, T, n, np, lines, 0, ntiles, alpha, st,
-                                                       guard);
-        }
-        if (io == 1) {
-            if (sym == 1) return hipErrorInvalidValue;
-            const float* fin = (const float*)in;
-            if (epi == 0) return panel_pw<C, true, 0, float, double>(sym, fin, out, T, n, np, lines, 0, ntiles, alpha, st, guard);
-            if (epi == 1) return panel_pw<C, true, 1, float, double>(sym, fin, out, T, n, np, lines, 0, ntiles, alpha, st, guard);
-            return panel_pw<C, true, 2, float, double>(sym, fin, out, T, n, np, lines, 0, ntiles, alpha, st, guard);
-        }
+    if (io == 2) {
+        if (epi != 0 || sym == 2) return hipErrorInvalidValue;
+        return panel_pw<C, true, 0, double, float>(sym, in, (float*)out, T, n, np, lines, 0, ntiles, alpha, st,
+                                                   guard);
+    }
+    if (io == 1) {
+        if (sym == 1) return hipErrorInvalidValue;
+        const float* fin = (const float*)in;
+        if (epi == 0) return panel_pw<C, true, 0, float, double>(sym, fin, out, T, n, np, lines, 0, ntiles, alpha, st, guard);
+        if (epi == 1) return panel_pw<C, true, 1, float, double>(sym, fin, out, T, n, np, lines, 0, ntiles, alpha, st, guard);
+        return panel_pw<C, true, 2, float, double>(sym, fin, out, T, n, np, lines, 0, ntiles, alpha, st, guard);
     }
     return hipErrorInvalidValue;
 }
@@ -463,18 +450,12 @@ bool xform_panel_split_supported(int n) { return n == 128 || n == 256; }
 
 bool xform_panel_f32_io(int np) { return xform_panel_supported(np); }
 
-hipError_t launch_xform_panel_x(int prec, int epi, const double* in, double* out, const double* T, int n, int np,
-                                long lines, double alpha, hipStream_t st, const int* guard, int sym) {
-    return launch_xform_panel_x_io(prec, epi, in, out, T, n, np, lines, alpha, st, guard, sym, 0);
-}
-
 hipError_t launch_xform_panel_x_io(int prec, int epi, const double* in, double* out, const double* T, int n, int np,
                                    long lines, double alpha, hipStream_t st, const int* guard, int sym, int io) {
     if (lines <= 0) return hipSuccess;
     if (!xform_panel_supported(np) || epi < 0 || epi > 2 || sym < 0 || sym > 2 || io < 0 || io > 2)
         return hipErrorInvalidValue;
     if (sym != 0 && !(xform_panel_split_supported(n) && np == n)) return hipErrorInvalidValue;
-    if (prec == 0) return panel_x_epi<PanelF64>(sym, epi, io, in, out, T, n, np, lines, alpha, st, guard);
     if (prec == 1) return panel_x_epi<PanelF32>(sym, epi, io, in, out, T, n, np, lines, alpha, st, guard);
     if (prec == 2) return panel_x_epi<PanelBf16x3>(sym, epi, io, in, out, T, n, np, lines, alpha, st, guard);
     return hipErrorInvalidValue;
@@ -495,10 +476,8 @@ static hipError_t panel_s_io(int sym, const double* in, double* out, const doubl
     }
     if (io_f32 == 3) {
         // float on both sides (the intermediate of a reduced-precision transform)
-        if constexpr (!std::is_same<C, PanelF64>::value)
-            return panel_pw<C, false, 0, float, float>(sym, (const float*)in, (float*)out, T, n, np, 0, inner, ntiles,
-                                                       1.0, st, guard);
-        return hipErrorInvalidValue;
+        return panel_pw<C, false, 0, float, float>(sym, (const float*)in, (float*)out, T, n, np, 0, inner, ntiles,
+                                                   1.0, st, guard);
     }
     return panel_pw<C, false, 0>(sym, in, out, T, n, np, 0, inner, ntiles, 1.0, st, guard);
 }
@@ -509,7 +488,6 @@ hipError_t launch_xform_panel_s(int prec, const double* in, double* out, const d
     if (!xform_panel_supported(np) || io_f32 < 0 || io_f32 > 3 || sym < 0 || sym > 2) return hipErrorInvalidValue;
     if (sym != 0 && !(xform_panel_split_supported(n) && np == n)) return hipErrorInvalidValue;
     const long ntiles = nbatch * ((inner + 15) / 16);
-    if (prec == 0) return panel_s_io<PanelF64>(sym, in, out, T, n, np, inner, ntiles, st, guard, io_f32);
     if (prec == 1) return panel_s_io<PanelF32>(sym, in, out, T, n, np, inner, ntiles, st, guard, io_f32);
     if (prec == 2) return panel_s_io<PanelBf16x3>(sym, in, out, T, n, np, inner, ntiles, st, guard, io_f32);
     return hipErrorInvalidValue;

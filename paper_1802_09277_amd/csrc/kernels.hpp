@@ -93,7 +93,23 @@ hipError_t launch_xform_s(int prec, const double* in, double* out, const double*
 // and odd ones [n/2, n) under the reflection i -> n-1-i, which halves the
 // multiply-adds; only for n = np with xform_split_supported(n)
 bool xform_split_supported(int n);
-// (both per-axis launchers: every block returns at once when guard is given
+
+// FP64 per-axis transforms with the even/odd split, any n <= kEoMaxN (modes
+// [0, ceil(n/2)) even, the rest odd, under i -> n-1-i).  T: the packed panels
+// of A (U or C = M_1 U, host n x n, row stride lda) forward, out = A^T in, or
+// inverse, out (epi 0 =, 1 += alpha, 2 = alpha) A in; xform_eo_pack_len(n) doubles.
+// x: `lines` contiguous lines; s: in[b][k][i] with k stride inner.  in and
+// out must differ.
+constexpr int kEoMaxN = 1024;
+bool xform_eo_supported(int n);
+bool xform_eo_s_supported(int n, long inner);   // also the lane offsets fit 32 bits
+size_t xform_eo_pack_len(int n);
+void xform_eo_pack(bool inv, const double* A, int n, int lda, double* out);
+hipError_t launch_xform_eo_x(bool inv, int epi, const double* in, double* out, const double* T, int n, long lines,
+                             double alpha, hipStream_t st, const int* guard = nullptr);
+hipError_t launch_xform_eo_s(bool inv, const double* in, double* out, const double* T, int n, long nbatch,
+                             long inner, hipStream_t st, const int* guard = nullptr);
+// (all per-axis launchers: every block returns at once when guard is given
 // and *guard == 0, as in the guards of speculative cycles; launch_xform_s
 // with io_f32 2 writes float output, 1 reads float input, 3 both (reduced
 // precisions), for np <= 256 a multiple of 32: xform_panel_f32_io(np))

@@ -57,8 +57,7 @@ struct sth_handle {
     int dim = 2, n = 0, np = 0, Nt = 0, p = 0, L = 0;
     long Nx = 0;
     long Nxe = 0;                       // modes per time row of an eigenbasis vector (eig_modes)
-    // the spatial modes are ordered [even | odd] under the reflection
-    // i -> n-1-i and the per-axis transforms use the split kernels
+    // the reduced-precision per-axis transforms use the even/odd split panels
     bool split = false;
     double omega = 0.5;
     int nu_pre = 1, nu_post = 1;
@@ -70,6 +69,7 @@ struct sth_handle {
     // device data
     double* Tf = nullptr;               // np x np, U padded  (forward: r^ = U^T r)
     double* Ti = nullptr;               // np x np, U^T padded (inverse: z = U z^)
+    double* eo[4] = {};                 // packed FP64 panels of U forward, inverse, C forward, inverse
     double* mu1 = nullptr;
     double* M1b = nullptr;
     double* K1b = nullptr;
@@ -332,35 +332,48 @@ static int residual(sth_handle* h, int lvl, const double* f, const double* u, do
     return STH_OK;
 }
 
-// Split form of a per-axis transform with matrix T: 1 for the forward
-// matrices (U, C = M_1 U: out = T^T in), 2 for the inverse ones (their
-// transposes), 0 without the even/odd mode order
-static int split_of(const sth_handle* h, const double* T) {
-    if (!h->split) return 0;
-    if (T == h->Tf || (h->Cf && T == h->Cf)) return 1;
-    if (T == h->Ti || (h->Ci && T == h->Ci)) return 2;
-    return 0;
+// whether T is one of the inverse matrices (out = U in or C in; T = U^T, C^T)
+static bool inverse_of(const sth_handle* h, const double* T) { return T == h->Ti || (h->Ci && T == h->Ci); }
+
+// the packed FP64 panels of the matrix T
+static const double* eo_panels(const sth_handle* h, const double* T) {
+    return T == h->Tf ? h->eo[0] : (T == h->Ti ? h->eo[1] : (T == h->Cf ? h->eo[2] : h->eo[3]));
 }
 
+// Split form of a reduced-precision per-axis transform with matrix T: 1 for
+// the forward matrices (U, C = M_1 U: out = T^T in), 2 for the inverse ones
+// (their transposes), 0 where the panels have no split
+static int split_of(const sth_handle* h, const double* T) { return !h->split ? 0 : (inverse_of(h, T) ? 2 : 1); }
+
 // per-axis transforms in the precision `prec` (sth_prec); the split forms
-// take n / 2 multiply-adds per output instead of n
+// (FP64 up to kEoMaxN, reduced precisions where split_of) take n / 2
+// multiply-adds per output instead of n
 // io (reduced precisions): 2 float output, 1 float input
 static int xform_x(sth_handle* h, int prec, int epi, const double* in, double* out, const double* T, long lines,
                    double alpha, hipStream_t st, const int* guard = nullptr, int io = 0) {
     const double dof = (double)lines * h->n;
+    const bool eo = prec == STH_FP64 && xform_eo_supported(h->n);
     const int sym = split_of(h, T);
-    Timed tm(h, STH_K_XFORM_X, (sym ? 1.0 : 2.0) * h->n * dof, dof * ((epi == 1 ? 24.0 : 16.0) - (io ? 4.0 : 0.0)),
-             st);
-    HIPCHK(launch_xform_x(prec, epi, in, out, T, h->n, h->np, lines, alpha, st, guard, sym, io));
+    Timed tm(h, STH_K_XFORM_X, (eo || sym ? 1.0 : 2.0) * h->n * dof,
+             dof * ((epi == 1 ? 24.0 : 16.0) - (io ? 4.0 : 0.0)), st);
+    if (eo)
+        HIPCHK(launch_xform_eo_x(inverse_of(h, T), epi, in, out, eo_panels(h, T), h->n, lines, alpha, st, guard));
+    else
+        HIPCHK(launch_xform_x(prec, epi, in, out, T, h->n, h->np, lines, alpha, st, guard, sym, io));
     return STH_OK;
 }
 
 static int xform_s(sth_handle* h, int prec, const double* in, double* out, const double* T, long nbatch,
                    long inner, hipStream_t st, const int* guard = nullptr, int io_f32 = 0) {
     const double dof = (double)nbatch * h->n * inner;
+    const bool eo = prec == STH_FP64 && xform_eo_s_supported(h->n, inner);
     const int sym = split_of(h, T);
-    Timed tm(h, STH_K_XFORM_S, (sym ? 1.0 : 2.0) * h->n * dof, (io_f32 == 3 ? 8.0 : (io_f32 ? 12.0 : 16.0)) * dof, st);
-    HIPCHK(launch_xform_s(prec, in, out, T, h->n, h->np, nbatch, inner, st, guard, io_f32, sym));
+    Timed tm(h, STH_K_XFORM_S, (eo || sym ? 1.0 : 2.0) * h->n * dof,
+             (io_f32 == 3 ? 8.0 : (io_f32 ? 12.0 : 16.0)) * dof, st);
+    if (eo)
+        HIPCHK(launch_xform_eo_s(inverse_of(h, T), in, out, eo_panels(h, T), h->n, nbatch, inner, st, guard));
+    else
+        HIPCHK(launch_xform_s(prec, in, out, T, h->n, h->np, nbatch, inner, st, guard, io_f32, sym));
     return STH_OK;
 }
 
@@ -750,7 +763,7 @@ static int spatial_apply(sth_handle* h, SpatialKind kind, const double* in, doub
         // float eigenbasis data with reduced-precision transforms: the
         // intermediate between the two axes is float as well
         const bool fmid = io_f32 != 0 && prec != STH_FP64;
-        if (fwd || (epi == 0 && io_f32 == 0)) {
+        if (fwd) {
             if ((rc = xform_x(h, prec, 0, in, tmp, T, rows * n, 1.0, st, g, fmid ? 2 : 0))) return rc;
             if ((rc = xform_s(h, prec, tmp, out, T, rows, n, st, g, fmid ? 3 : io_f32))) return rc;
         } else {
@@ -1178,6 +1191,7 @@ static size_t workspace_of(Problem q) {
     long slab = (long)q.Nt() * Nx;
     size_t total = 0;
     total += 2 * sizeof(double) * np * np;                   // transforms
+    total += (q.basis == 1 ? 4 : 2) * sizeof(double) * xform_eo_pack_len((int)n);
     total += sizeof(double) * n * (1 + 2 * (2 * q.degree + 1));
     const bool f32 = f32_storage(q, level_count(q));
     const size_t evecs0 = q.basis == 1 ? 3 + (fused_cycle_close(q, level_count(q)) ? 1 : 0) : 0;   // f^, u^ (x2 or 3)
@@ -1329,7 +1343,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     h->dim = q.dim;
     h->n = h->S.n;
     h->np = (h->n + 15) / 16 * 16;
-    h->split = h->S.half > 0 && h->np == h->n && xform_split_supported(h->n);
+    h->split = h->np == h->n && xform_split_supported(h->n);
     h->Nt = h->S.Nt;
     h->p = q.degree;
     h->Nx = (long)h->n * h->n * (q.dim == 3 ? h->n : 1);
@@ -1521,6 +1535,16 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
                 hipMemcpyAsync(h->Gf, Gf.data(), Gf.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess)
                 return cleanup(STH_EHIP, "upload of the setup failed");
         }
+    }
+    // packed panels of the FP64 per-axis transforms
+    const size_t eo_len = xform_eo_pack_len(n);
+    std::vector<double> eo_host[4];
+    for (int i = 0; i < (h->basis == 1 ? 4 : 2) && eo_len > 0; ++i) {
+        eo_host[i].assign(eo_len, 0.0);
+        xform_eo_pack(i % 2 == 1, i < 2 ? Tf.data() : Cf.data(), n, np, eo_host[i].data());
+        if (!dalloc(&h->eo[i], eo_len)) return cleanup(STH_ENOMEM, "device allocation failed");
+        if (hipMemcpyAsync(h->eo[i], eo_host[i].data(), eo_len * 8, hipMemcpyHostToDevice, s) != hipSuccess)
+            return cleanup(STH_EHIP, "upload of the setup failed");
     }
     const unsigned mapped = hipHostMallocMapped | hipHostMallocCoherent;
     if (hipHostMalloc((void**)&h->hnorm, kNormSlots * sizeof(double), mapped) != hipSuccess ||
@@ -2738,6 +2762,8 @@ int sth_destroy(sth_handle* h) {
                     (void*)h->mrst})
         if (q) (void)hipFree(q);
     for (double* q : h->mr)
+        if (q) (void)hipFree(q);
+    for (double* q : h->eo)
         if (q) (void)hipFree(q);
     double* ptrs[] = {h->Tf, h->Ti, h->mu1, h->M1b, h->K1b, h->buf0, h->buf1, h->partial, h->dnorm, h->dktmt,
                       h->Cf, h->Ci, h->Gf, h->e0, h->e1, h->e2, h->e3, h->cpartial, h->kv, h->kz, h->kc,

@@ -984,7 +984,7 @@ static bool pencil_eigen(const Mat& K, const Mat& M, std::vector<double>& mu, Ma
     return true;
 }
 
-// A(i, j) = A(n-1-i, n-1-j) to rounding
+// A(i, j) = A(n-1-i, n-1-j) to the rounding of the knots
 static bool reflection_symmetric(const Mat& A) {
     const int n = A.r;
     double amax = 0.0, d = 0.0;
@@ -993,7 +993,7 @@ static bool reflection_symmetric(const Mat& A) {
             amax = std::max(amax, std::fabs(A(i, j)));
             d = std::max(d, std::fabs(A(i, j) - A(n - 1 - i, n - 1 - j)));
         }
-    return d <= 1e-12 * amax;
+    return d <= 1e-9 * amax;
 }
 
 int build_setup(const Problem& p, Setup& s, std::string& err) {
@@ -1004,66 +1004,69 @@ int build_setup(const Problem& p, Setup& s, std::string& err) {
     s.Nt = p.Nt();
     space_matrices(p.n_elem, p.degree, s.M1, s.K1);
     const int n = s.n;
-    const int h = n / 2;
-    if (n % 2 == 0 && reflection_symmetric(s.M1) && reflection_symmetric(s.K1)) {
-        // The reflection J (i -> n - 1 - i) commutes with M1 and K1, so the
-        // eigenvectors split into even ones, v = [w; J w], and odd ones,
-        // v = [w; -J w], where w solves the half pencil (K11 +- K12 J,
-        // M11 +- M12 J) of order n / 2.  With w^T (M11 +- M12 J) w = 1,
-        // v / sqrt 2 is M1-orthonormal.
-        Mat U(n, n);
-        s.mu.assign(n, 0.0);
-        for (int sg = 0; sg < 2; ++sg) {
-            const double sign = sg == 0 ? 1.0 : -1.0;
-            Mat Kh(h, h), Mh(h, h);
-            for (int i = 0; i < h; ++i)
-                for (int j = 0; j < h; ++j) {
-                    Kh(i, j) = s.K1(i, j) + sign * s.K1(i, n - 1 - j);
-                    Mh(i, j) = s.M1(i, j) + sign * s.M1(i, n - 1 - j);
+    if (!reflection_symmetric(s.M1) || !reflection_symmetric(s.K1)) {
+        err = "1-D matrices of the uniform mesh are not symmetric under reflection";
+        return -5;
+    }
+    // The reflection J (i -> n - 1 - i) commutes with M1 and K1, so the
+    // eigenvectors split into even ones, v = [w; (m;) J w], and odd ones,
+    // v = [w; (0;) -J w] (the middle entry for an odd n).  In the orthonormal
+    // basis (e_i +- e_{n-1-i}) / sqrt 2, and e_mid for the even ones, they
+    // solve half pencils of order ceil(n / 2) and n / 2, ordered [even | odd].
+    Mat U(n, n);
+    s.mu.assign(n, 0.0);
+    s.half = (n + 1) / 2;
+    const int h0 = n / 2;
+    const double r2 = std::sqrt(0.5);
+    for (int sg = 0; sg < 2; ++sg) {
+        const int m = sg == 0 ? s.half : h0;
+        if (m == 0) continue;
+        const double sign = sg == 0 ? 1.0 : -1.0;
+        auto fold = [&](const Mat& A) {
+            Mat B(m, m);
+            for (int i = 0; i < m; ++i)
+                for (int j = 0; j < m; ++j) {
+                    // (an entry of the middle row or column counts sqrt 2, the middle one once)
+                    const bool mi = i >= h0, mj = j >= h0;
+                    if (mi && mj) B(i, j) = A(i, j);
+                    else if (mi || mj) B(i, j) = std::sqrt(2.0) * A(i, j);
+                    else B(i, j) = A(i, j) + sign * A(i, n - 1 - j);
                 }
-            std::vector<double> mh;
-            Mat Uh;
-            if (!pencil_eigen(Kh, Mh, mh, Uh)) {
-                err = "half mass matrix not positive definite";
-                return -5;
-            }
-            if (p.basis == 1) {
-                // the eigenvalues of M1 are those of its two half matrices
-                std::vector<double> ev;
-                Mat Qm;
-                sym_eigen(Mh, ev, Qm);
-                const double lo = *std::min_element(ev.begin(), ev.end());
-                const double hi = *std::max_element(ev.begin(), ev.end());
-                s.m1_min = sg == 0 ? lo : std::min(s.m1_min, lo);
-                s.m1_max = sg == 0 ? hi : std::max(s.m1_max, hi);
-            }
-            const double r2 = std::sqrt(0.5);
-            for (int j = 0; j < h; ++j) {
-                s.mu[sg * h + j] = mh[j];
-                for (int i = 0; i < h; ++i) {
-                    U(i, sg * h + j) = r2 * Uh(i, j);
-                    U(n - 1 - i, sg * h + j) = sign * r2 * Uh(i, j);
-                }
-            }
-        }
-        s.U = U;
-        s.half = h;
-    } else {
-        if (!pencil_eigen(s.K1, s.M1, s.mu, s.U)) {
-            err = "M1 not positive definite";
+            return B;
+        };
+        const Mat Kh = fold(s.K1), Mh = fold(s.M1);
+        std::vector<double> mh;
+        Mat Uh;
+        if (!pencil_eigen(Kh, Mh, mh, Uh)) {
+            err = "half mass matrix not positive definite";
             return -5;
         }
-        s.half = 0;
+        if (p.basis == 1) {
+            // C = M1 U satisfies C C^T = M1 (U U^T = M1^{-1}): its squared
+            // singular values are the eigenvalues of M1, those of the two
+            // half matrices
+            std::vector<double> ev;
+            Mat Qm;
+            sym_eigen(Mh, ev, Qm);
+            const double lo = *std::min_element(ev.begin(), ev.end());
+            const double hi = *std::max_element(ev.begin(), ev.end());
+            s.m1_min = sg == 0 ? lo : std::min(s.m1_min, lo);
+            s.m1_max = sg == 0 ? hi : std::max(s.m1_max, hi);
+        }
+        for (int j = 0; j < m; ++j) {
+            const int c = sg * s.half + j;
+            s.mu[c] = mh[j];
+            for (int i = 0; i < m; ++i) {
+                if (i >= h0) {
+                    U(i, c) = Uh(i, j);
+                } else {
+                    U(i, c) = r2 * Uh(i, j);
+                    U(n - 1 - i, c) = sign * r2 * Uh(i, j);
+                }
+            }
+        }
     }
-    if (p.basis == 1 && s.half == 0) {
-        // C = M1 U satisfies C C^T = M1 (U U^T = M1^{-1}), so the squared
-        // singular values of C are the eigenvalues of M1
-        std::vector<double> ev;
-        Mat Qm;
-        sym_eigen(s.M1, ev, Qm);
-        s.m1_min = *std::min_element(ev.begin(), ev.end());
-        s.m1_max = *std::max_element(ev.begin(), ev.end());
-    }
+    s.U = U;
     // temporal levels
     s.levels.clear();
     int S = p.n_slabs;
