@@ -319,6 +319,68 @@ hipError_t launch_norm2(const double* v, long len, double* partial, double* out,
     return hipGetLastError();
 }
 
+// ||f||^2 and whether u has a nonzero entry, in one pass (partial sums, then
+// kNormBlocks flags); streaming loads, four of each vector in flight
+__global__ __launch_bounds__(256) void k_prologue(const double* __restrict__ f, const double* __restrict__ u, long len,
+                                                  long chunk, double* __restrict__ partial) {
+    __shared__ double sh[256];
+    const long beg = (long)blockIdx.x * chunk, end = beg + chunk < len ? beg + chunk : len;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    int nz = 0;
+    long i = beg + threadIdx.x;
+    for (; i + 768 < end; i += 1024) {
+        double a[4], b[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            a[q] = __builtin_nontemporal_load(f + i + 256 * q);
+            b[q] = __builtin_nontemporal_load(u + i + 256 * q);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            s[q] += a[q] * a[q];
+            nz |= !(b[q] == 0.0);
+        }
+    }
+    for (; i < end; i += 256) {
+        s[0] += f[i] * f[i];
+        nz |= !(u[i] == 0.0);
+    }
+    nz = __syncthreads_or(nz);
+    const double tot = block_sum_256((s[0] + s[1]) + (s[2] + s[3]), sh);
+    if (threadIdx.x == 0) {
+        partial[blockIdx.x] = tot;
+        partial[kNormBlocks + blockIdx.x] = nz ? 1.0 : 0.0;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_prologue_final(const double* __restrict__ partial, double* out,
+                                                        double* out_host, int* flags, int* flag_host) {
+    __shared__ double sh[256];
+    double s = 0.0;
+    int nz = 0;
+    for (int i = threadIdx.x; i < kNormBlocks; i += 256) {
+        s += partial[i];
+        nz |= partial[kNormBlocks + i] != 0.0;
+    }
+    nz = __syncthreads_or(nz);
+    const double tot = block_sum_256(s, sh);
+    if (threadIdx.x == 0) {
+        out[0] = tot;
+        *out_host = tot;
+        flags[0] = nz ? 1 : 0;
+        flags[1] = nz ? 0 : 1;
+        *flag_host = nz ? 1 : 0;
+    }
+}
+
+hipError_t launch_solve_prologue(const double* f, const double* u, long len, double* partial, double* out,
+                                 double* out_host, int* flags, int* flag_host, hipStream_t st) {
+    const long chunk = std::max<long>(1, (len + kNormBlocks - 1) / kNormBlocks);
+    hipLaunchKernelGGL(k_prologue, dim3(kNormBlocks), dim3(256), 0, st, f, u, len, chunk, partial);
+    hipLaunchKernelGGL(k_prologue_final, dim3(1), dim3(256), 0, st, partial, out, out_host, flags, flag_host);
+    return hipGetLastError();
+}
+
 __global__ __launch_bounds__(256) void k_rhs(int dim, int Nt, int n, int n_modes,
                                              const double* __restrict__ Tpart,
                                              const double* __restrict__ Xpart, double* __restrict__ f,

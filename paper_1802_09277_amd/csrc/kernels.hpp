@@ -60,7 +60,7 @@ struct CycleFlag {
 // ktmt: device copy of op (K_t then M_t, kNt x kNt each).
 hipError_t launch_residual(int dim, int Nt, int p, int n, const double* M1b, const double* K1b,
                            const TimeOp& op, const double* ktmt, const double* f, const double* u, double* r,
-                           long s0, long ns, double sign, hipStream_t st);
+                           long s0, long ns, double sign, hipStream_t st, const int* guard = nullptr);
 
 // The residual with its squared norm (2-D images of 128 or more columns and
 // small degrees: residual_norm_fused): r = f - L u over all ns slabs, and
@@ -233,6 +233,26 @@ hipError_t launch_eig_coarse_tail3(int dim, int Nt, const TimeMix* tma_dev, cons
                                    const TimeMix* tmc_dev, bool schur, const double* mu1, int n, const double* fa,
                                    double* ua, const Transfer& tr, double omega, long SA, hipStream_t st,
                                    const int* guard = nullptr, int vt = 0);
+//  m <= kMaxBatch whole V(1,1) cycles (L <= 4 levels) on the residual alone:
+//  rin -> rout (may be null); uout (may be null) = L^{-1}(fh - r) of the
+//  residual r after the cycles, the iterate that belongs to it.  With L = 1 a
+//  cycle (m <= 1) is the exact solve e = L^{-1} rin, stored to uout, and rout
+//  = rin - L e; m = 0 forms uout as above.  tab: the table of
+//  launch_cycles_table (per-level slab inverses tm and K_t, M_t on the device;
+//  vw may be null when no sums are taken).  partial (may be null; max_partial
+//  entries, cycles_partials() suffice): sums 3 c .. 3 c + 2 of out_host
+//  (mapped pinned host memory) are ||r||^2 and its lower and upper
+//  mode-weighted forms after c = 0 .. m cycles; seq (may be null): after sum
+//  j, seq[j] = seq_val.  Vectors differ, except fh == rin.
+constexpr int kMaxBatch = 8;
+bool cycles_supported(int Nt, int L, long S);
+long cycles_partials(long Nx);
+size_t cycles_table_len(int Nt, int L, long Nx);
+hipError_t launch_cycles_table(int dim, int Nt, int L, const TimeMix* tm, const double* ktmt, const double* mu1, int n,
+                               long Nx, const Transfer& tr, const double* vw, double* tab, hipStream_t st);
+hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega, long S, int m,
+                         const double* rin, const double* fh, double* rout, double* uout, double* partial,
+                         long max_partial, double* out_host, int* seq, int seq_val, hipStream_t st, int vt = 0);
 //  rh = fh - L uh
 hipError_t launch_eig_residual(int dim, int Nt, const double* ktmt, const double* mu1, int n, const double* fh,
                                const double* uh, double* rh, long S, hipStream_t st);
@@ -318,6 +338,13 @@ hipError_t launch_normalize(double* w, long len, const double* n2, hipStream_t s
 //  w = alpha w + sum_i c[i] V_i (k may be 0)
 hipError_t launch_multiaxpy(const double* V, long ld, int k, const double* c, double alpha, double* w, long len,
                             hipStream_t st);
+
+// Start of a solve in one read of f and u: out[0] = ||f||^2 (also to out_host),
+// flags[0] = 1 if some entry of u is not zero (NaN included), flags[1] = 1 -
+// flags[0] (flags[0] also to flag_host); the host pointers are mapped pinned
+// memory; partial needs 2 kNormBlocks entries.
+hipError_t launch_solve_prologue(const double* f, const double* u, long len, double* partial, double* out,
+                                 double* out_host, int* flags, int* flag_host, hipStream_t st);
 
 // Two-stage deterministic sum of squares: partial sums over a fixed number
 // of blocks, then one block; result in out[0].

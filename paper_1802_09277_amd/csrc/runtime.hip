@@ -39,6 +39,7 @@ static thread_local std::string g_err;
 constexpr int kNormSlots = 14;
 constexpr int slot_base(int slot) { return 2 + 3 * slot; }
 constexpr int kMixR = 11, kMixF = 12;
+constexpr int kCycSums = 3 * (kMaxBatch + 1);      // sums of a batch of cycles
 
 static int fail(int code, const std::string& msg) {
     g_err = msg;
@@ -88,6 +89,15 @@ struct sth_handle {
     bool fuse_tail = false;             // the two coarsest levels in one pass (k_eig_coarse_tail)
     bool fuse_tail3 = false;            // the three coarsest levels in one pass (k_eig_coarse_tail3)
     TimeMix* dmix = nullptr;            // per level slab inverse in device memory
+    // whole cycles on chip (launch_cycles): the eigenbasis solve runs batches
+    // of cycles on the residual
+    bool cyc = false;
+    double* cyc_tab = nullptr;          // per mode: its matrices on every level (launch_cycles_table)
+    double* hcyc = nullptr;             // mapped, coherent: the sums of a batch
+    double* hcyc_dev = nullptr;
+    int* hcseq = nullptr;               // and their completion marks
+    int* hcseq_dev = nullptr;
+    int wait_cyc = 0, wait_cyc_seq = 0; // marks the blocking solve waits for (0: none)
     bool defer_close = false;           // set by a solve iteration: level 0 leaves its post-smoothing
     const double* pending_ec = nullptr; // coarse correction waiting for the fused cycle close
     // The solve loop's fused cycle closes do not store the cycle's result
@@ -225,6 +235,15 @@ struct sth_handle {
         // inner solve of a mixed-precision solve: zero initial guess, ||f||
         // known, transforms in precision tprec, no exact B-spline norm (the
         // lower bound decides), the result added into u
+        // batches of whole cycles (phase 10: batch enqueued, 11: exact norm of
+        // a batch's residual): level-0 buffers of the batch's first and last
+        // residual and of the iterate formed with it (-1: f^, i.e. the initial
+        // residual; -2: none), its cycles, and whether it starts the solve
+        bool cyc = false;
+        int start = -1, end = 0, uout = -2, m = 0;
+        int known = 0;                  // cycles of the batch whose sums have been tested already
+        bool first = true;
+        bool nonzero = false;           // the initial guess has a nonzero entry
         bool inner = false;
         bool inner_store = false;       // the inner result is stored into u (u was zero), not added
         int tprec = STH_FP64;
@@ -247,7 +266,8 @@ struct sth_handle {
     int* dgo = nullptr;                 // per norm slot: continuation flag of the cycle (device);
                                         // [2]: the final exact norm ends the solve; [3]: the
                                         // initial pass of a speculative solve; [4]: the initial
-                                        // guess of the solve has a nonzero entry; [5]: always 0
+                                        // guess of the solve has a nonzero entry; [5]: always 0;
+                                        // [6], [7]: [4] of a solve by batches, and its negation
     int* hflag = nullptr;               // its mapped host copy
     int* hflag_dev = nullptr;
     double* dthr = nullptr;             // (rtol ||f||)^2 and rtol ||f|| of the solve in progress (device)
@@ -320,7 +340,7 @@ struct Timed {
 // building blocks
 // ---------------------------------------------------------------------------
 static int residual(sth_handle* h, int lvl, const double* f, const double* u, double* r, long s0, long ns,
-                    double sign, hipStream_t st) {
+                    double sign, hipStream_t st, const int* guard = nullptr) {
     h->tlev = lvl;
     double dof = (double)ns * slab_len(h);
     int B = 2 * h->p + 1;
@@ -328,7 +348,7 @@ static int residual(sth_handle* h, int lvl, const double* f, const double* u, do
     double bytes = dof * (f ? 24.0 : 16.0);
     Timed tm(h, STH_K_RESIDUAL, flops, bytes, st);
     HIPCHK(launch_residual(h->dim, h->Nt, h->p, h->n, h->M1b, h->K1b, h->ops[lvl],
-                           h->dktmt + (size_t)lvl * 2 * kNt * kNt, f, u, r, s0, ns, sign, st));
+                           h->dktmt + (size_t)lvl * 2 * kNt * kNt, f, u, r, s0, ns, sign, st, guard));
     return STH_OK;
 }
 
@@ -1035,6 +1055,29 @@ static int form_result(sth_handle* h, hipStream_t st) {
     return STH_OK;
 }
 
+// ||(I (x) C_x) r||^2 of the FP64 eigenbasis vector r (which may be buf0) to
+// hnorm[0] (not synchronised); buf0 and buf1 are the work vectors
+static int eig_norm_of(sth_handle* h, const double* r, hipStream_t st, const CycleFlag& fin = CycleFlag{}) {
+    h->tlev = 0;
+    const long S = h->lev_S[0], rows = S * h->Nt;
+    const double dof = (double)S * slab_len(h);
+    if (h->dim == 2 && xform2d_supported(h->np)) {
+        // ||C r^ C^T||^2 per image as <r^ G, G r^> (G = C^T C), r not formed
+        Timed tm(h, STH_K_RESNORM, dof * 4.0 * h->n, dof * 8.0, st);
+        HIPCHK(launch_gram_norm2d(r, h->Gf, h->n, h->np, rows, h->partial, kNormBlocks, h->dnorm,
+                                  h->hnorm_dev, st, fin, h->Nxe));
+        return STH_OK;                  // stored hnorm[0] itself
+    }
+    // per-axis transforms (2-D: s then x, r -> buf1 -> buf0; 3-D: r -> buf1 ->
+    // buf0 -> buf1; the rows of these paths are not padded)
+    double* out = h->dim == 2 ? h->buf0 : h->buf1;
+    int rc = spatial_apply(h, INV_C, r, out, rows, h->dim == 2 ? h->buf1 : h->buf0, st);
+    if (rc) return rc;
+    if ((rc = norm2_dev(h, out, S * eslab_len(h), st))) return rc;
+    HIPCHK(hipMemcpyAsync(h->hnorm, h->dnorm, sizeof(double), hipMemcpyDeviceToHost, st));
+    return STH_OK;
+}
+
 // The B-spline residual norm ||(I (x) C_x) r^||^2 (C = M_1 U = U^{-T}) of
 // the current eigenbasis iterate to hnorm[0] (not synchronised); r^ is
 // formed again in buf0.
@@ -1043,32 +1086,13 @@ static int eig_exact_norm(sth_handle* h, hipStream_t st, const CycleFlag& fin = 
     if (rc) return rc;
     h->tlev = 0;
     const long S = h->lev_S[0];
-    const long len = S * eslab_len(h);             // eigenbasis layout (padded rows)
     const double dof = (double)S * slab_len(h);
-    const long rows = S * h->Nt;
     {
         Timed tm(h, STH_K_EIG_RESID, dof * 4.0 * h->Nt, dof * 24.0, st);
         HIPCHK(launch_eig_residual(h->dim, h->Nt, level_ktmt(h, 0), h->mu1, h->n, h->e0, eig_u(h, 0, h->ecur[0]),
                                    h->buf0, S, st));
     }
-    if (h->dim == 2 && xform2d_supported(h->np)) {
-        // ||C r^ C^T||^2 per image as <r^ G, G r^> (G = C^T C), r not formed
-        Timed tm(h, STH_K_RESNORM, dof * 4.0 * h->n, dof * 8.0, st);
-        HIPCHK(launch_gram_norm2d(h->buf0, h->Gf, h->n, h->np, rows, h->partial, kNormBlocks, h->dnorm,
-                                  h->hnorm_dev, st, fin, h->Nxe));
-        return STH_OK;                  // stored hnorm[0] itself
-    }
-    if (h->dim == 2) {
-        // per-axis transforms buf0 -> buf1 -> buf0
-        if ((rc = spatial_apply(h, INV_C, h->buf0, h->buf0, rows, h->buf1, st))) return rc;
-        if ((rc = norm2_dev(h, h->buf0, len, st))) return rc;
-    } else {
-        // x: buf0 -> buf1, y: buf1 -> buf0, z: buf0 -> buf1
-        if ((rc = spatial_apply(h, INV_C, h->buf0, h->buf1, rows, h->buf0, st))) return rc;
-        if ((rc = norm2_dev(h, h->buf1, len, st))) return rc;
-    }
-    HIPCHK(hipMemcpyAsync(h->hnorm, h->dnorm, sizeof(double), hipMemcpyDeviceToHost, st));
-    return STH_OK;
+    return eig_norm_of(h, h->buf0, st, fin);
 }
 
 // ---------------------------------------------------------------------------
@@ -1167,6 +1191,24 @@ static bool f32_storage(const Problem& q, size_t levels) {
            ((q.dim == 2 && xform2d_supported(np)) || xform_panel_f32_io(np));
 }
 
+// Whole cycles on chip: eigenbasis iteration with V(1,1) cycles, levels and
+// time line within what a block holds
+static bool cycles_on_chip(const Problem& q, size_t levels) {
+    return q.basis == 1 && q.nu_pre == 1 && q.nu_post == 1 && cycles_supported(q.Nt(), (int)levels, q.n_slabs);
+}
+
+// third iterate buffer: the fused cycle close, or batches of several levels
+static bool third_buffer(const Problem& q, size_t levels) {
+    return fused_cycle_close(q, levels) || (levels > 1 && cycles_on_chip(q, levels));
+}
+
+// per-block partial sums of the eigenbasis passes
+static size_t cycle_partials(const Problem& q, size_t levels, long modes) {
+    const size_t pass = 3 * (((size_t)(q.n_slabs / 2) * (size_t)modes + 255) / 256);
+    return std::max(pass, cycles_on_chip(q, levels)
+                              ? (size_t)cycles_partials(modes) : 0);
+}
+
 static size_t workspace_of(Problem q);
 
 int sth_workspace_bytes(const sth_problem* p, size_t* bytes) {
@@ -1194,7 +1236,7 @@ static size_t workspace_of(Problem q) {
     total += (q.basis == 1 ? 4 : 2) * sizeof(double) * xform_eo_pack_len((int)n);
     total += sizeof(double) * n * (1 + 2 * (2 * q.degree + 1));
     const bool f32 = f32_storage(q, level_count(q));
-    const size_t evecs0 = q.basis == 1 ? 3 + (fused_cycle_close(q, level_count(q)) ? 1 : 0) : 0;   // f^, u^ (x2 or 3)
+    const size_t evecs0 = q.basis == 1 ? 3 + (third_buffer(q, level_count(q)) ? 1 : 0) : 0;   // f^, u^ (x2 or 3)
     total += 2 * sizeof(double) * (size_t)q.n_slabs * slab;                            // buf0, buf1
     total += evecs0 * (f32 ? sizeof(float) : sizeof(double)) * (size_t)q.n_slabs * slab;
     // per coarse level: u, f (nodal), and the eigenbasis u^, its partner and
@@ -1202,7 +1244,10 @@ static size_t workspace_of(Problem q) {
     const size_t vecsl_bytes = 2 * sizeof(double) + (q.basis == 1 ? (f32 ? 3 * sizeof(float) : sizeof(double)) : 0);
     if (q.basis == 1) {
         total += 3 * sizeof(double) * np * np;                // C, C^T, G
-        total += sizeof(double) * (2 * (((size_t)(q.n_slabs / 2) * (size_t)(Nx) + 255) / 256) + 1);   // cycle-end partials
+        total += sizeof(double) * (cycle_partials(q, level_count(q), Nx) + 1);
+        if (cycles_on_chip(q, level_count(q)))
+            total += sizeof(double) * cycles_table_len(q.Nt(), (int)level_count(q), Nx);
+
         total += sizeof(double) * 2 * n;                                 // mode weights
     }
     long S = q.n_slabs;
@@ -1211,7 +1256,7 @@ static size_t workspace_of(Problem q) {
         S /= 2;
         total += vecsl_bytes * (size_t)S * slab;
     }
-    total += sizeof(double) * (kNormBlocks + kNormSlots + L * 2 * kNt * kNt) + sizeof(TimeMix) * L;
+    total += sizeof(double) * (2 * kNormBlocks + kNormSlots + L * 2 * kNt * kNt) + sizeof(TimeMix) * L;
     if (q.minres_iters > 0)   // eight MinRes vectors of the finest level and the per-system scalars
         total += sizeof(double) * (size_t)q.n_slabs * slab * 8 + sizeof(double) * q.n_slabs * (kNt / 2) * kMrState;
     if (own > 0) {
@@ -1362,6 +1407,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     h->nb_hi = std::pow(h->S.m1_max, h->dim);
     h->fuse_close = fused_cycle_close(q, (size_t)h->L);
     h->f32 = f32_storage(q, (size_t)h->L);
+    h->cyc = cycles_on_chip(q, (size_t)h->L);
     {
         int G = 0, LA = 0;
         h->fuse_tail = h->basis == 1 && h->nu_pre == 1 && h->nu_post == 1 && h->L >= 3 &&
@@ -1449,7 +1495,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     if (!dalloc(&h->Tf, (size_t)np * np) || !dalloc(&h->Ti, (size_t)np * np) || !dalloc(&h->mu1, n) ||
         !dalloc(&h->M1b, (size_t)n * B) || !dalloc(&h->K1b, (size_t)n * B) ||
         !dalloc(&h->buf0, (size_t)q.n_slabs * slab) || !dalloc(&h->buf1, (size_t)q.n_slabs * slab) ||
-        !dalloc(&h->partial, kNormBlocks) || !dalloc(&h->dnorm, kNormSlots) ||
+        !dalloc(&h->partial, 2 * kNormBlocks) || !dalloc(&h->dnorm, kNormSlots) ||
         !dalloc(&h->dktmt, (size_t)h->L * 2 * kNt * kNt))
         return cleanup(STH_ENOMEM, "device allocation failed");
     std::vector<double> ktmt((size_t)h->L * 2 * kNt * kNt);
@@ -1495,12 +1541,12 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
                 Cf[(size_t)i * np + j] = c;
                 Ci[(size_t)j * np + i] = c;
             }
-        h->n_cpartial = 3 * (((q.n_slabs / 2) * h->Nxe + 255) / 256);   // three sums per block
+        h->n_cpartial = (long)cycle_partials(q, (size_t)h->L, h->Nxe);
         if (!dalloc(&h->cpartial, (size_t)h->n_cpartial) ||
             !dalloc(&h->Cf, (size_t)np * np) || !dalloc(&h->Ci, (size_t)np * np) ||
             !dalloc(&h->e0, ecount((size_t)q.n_slabs * eslab)) || !dalloc(&h->e1, ecount((size_t)q.n_slabs * eslab)) ||
             !dalloc(&h->e2, ecount((size_t)q.n_slabs * eslab)) ||
-            (h->fuse_close && !dalloc(&h->e3, ecount((size_t)q.n_slabs * eslab))))
+            (third_buffer(q, (size_t)h->L) && !dalloc(&h->e3, ecount((size_t)q.n_slabs * eslab))))
             return cleanup(STH_ENOMEM, "device allocation failed");
         // the padded modes of the eigenbasis vectors start (and stay) zero
         for (double* v : {h->e0, h->e1, h->e2, h->e3})
@@ -1546,21 +1592,30 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
         if (hipMemcpyAsync(h->eo[i], eo_host[i].data(), eo_len * 8, hipMemcpyHostToDevice, s) != hipSuccess)
             return cleanup(STH_EHIP, "upload of the setup failed");
     }
+    if (h->cyc) {
+        if (!dalloc(&h->cyc_tab, cycles_table_len(h->Nt, h->L, h->Nxe)))
+            return cleanup(STH_ENOMEM, "device allocation failed");
+    }
     const unsigned mapped = hipHostMallocMapped | hipHostMallocCoherent;
     if (hipHostMalloc((void**)&h->hnorm, kNormSlots * sizeof(double), mapped) != hipSuccess ||
         hipHostMalloc((void**)&h->hflag, 5 * sizeof(int), mapped) != hipSuccess ||
-        hipHostMalloc((void**)&h->hseq, 2 * sizeof(int), mapped) != hipSuccess)
+        hipHostMalloc((void**)&h->hseq, 2 * sizeof(int), mapped) != hipSuccess ||
+        hipHostMalloc((void**)&h->hcyc, kCycSums * sizeof(double), mapped) != hipSuccess ||
+        hipHostMalloc((void**)&h->hcseq, kCycSums * sizeof(int), mapped) != hipSuccess)
         return cleanup(STH_ENOMEM, "pinned host allocation failed");
+    for (int i = 0; i < kCycSums; ++i) h->hcseq[i] = 0;
     h->hseq[0] = h->hseq[1] = 0;
     if (hipHostGetDevicePointer((void**)&h->hnorm_dev, h->hnorm, 0) != hipSuccess ||
+        hipHostGetDevicePointer((void**)&h->hcyc_dev, h->hcyc, 0) != hipSuccess ||
+        hipHostGetDevicePointer((void**)&h->hcseq_dev, h->hcseq, 0) != hipSuccess ||
         hipHostGetDevicePointer((void**)&h->hflag_dev, h->hflag, 0) != hipSuccess ||
         hipHostGetDevicePointer((void**)&h->hseq_dev, h->hseq, 0) != hipSuccess)
         return cleanup(STH_EHIP, "pinned host memory is not mapped");
-    if (hipMalloc((void**)&h->dgo, 6 * sizeof(int)) != hipSuccess ||
+    if (hipMalloc((void**)&h->dgo, 8 * sizeof(int)) != hipSuccess ||
         hipMalloc((void**)&h->dthr, 2 * sizeof(double)) != hipSuccess)
         return cleanup(STH_ENOMEM, "device allocation failed");
     // dgo[5] stays 0: the flag of an inner solve's zero guess
-    if (hipMemsetAsync(h->dgo, 0, 6 * sizeof(int), s) != hipSuccess)
+    if (hipMemsetAsync(h->dgo, 0, 8 * sizeof(int), s) != hipSuccess)
         return cleanup(STH_EHIP, "clearing the device flags failed");
     for (auto& e : h->evring)
         if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
@@ -1571,6 +1626,8 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
         hipMemcpyAsync(h->M1b, M1b.data(), M1b.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(h->K1b, K1b.data(), K1b.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(h->dktmt, ktmt.data(), ktmt.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
+        (h->cyc && launch_cycles_table(h->dim, h->Nt, h->L, h->dmix, h->dktmt, h->mu1, h->n, h->Nxe, h->tr, h->vw,
+                                       h->cyc_tab, s) != hipSuccess) ||
         hipStreamSynchronize(s) != hipSuccess)
         return cleanup(STH_EHIP, "upload of the setup failed");
     if (q.minres_iters > 0) {
@@ -1902,6 +1959,23 @@ namespace sth {
 // the pinned host scalars.
 static sth_handle::Snap take_snap(const sth_handle* h);
 static int spec_enqueue(sth_handle* h);
+static int cyc_begin(sth_handle* h, const double* inner_fn);
+static int cyc_continue(sth_handle* h, bool* more);
+
+// Smallest relative tolerance of a solve by batches of cycles.  Its residual
+// is carried from cycle to cycle instead of being formed from the iterate, so
+// the two differ by the rounding of the iterate's own residual: up to 2e-13
+// ||f|| (64 x 64 elements, p = 3, 256 slabs; 5e-14 with p = 4 and 256 x 256, 2e-15
+// to 2e-14 elsewhere), at 1e-12 still a fraction of the tolerance.
+constexpr double kCycMinRtol = 1e-12;
+// Cycles of a solve's first batch, before its contraction is known: about
+// three quarters of what a residual reduction of 0.17 per cycle takes to
+// rtol (V(1,1) cycles need 10 to 14 to 1e-8; the last batch then starts from a
+// settled rate, and cycles past the stopping one are rarely taken).
+static int first_batch(double rtol) {
+    const double n = rtol > 0.0 && rtol < 1.0 ? std::log(rtol) / std::log(0.17) : 1.0;
+    return std::max(1, std::min(kMaxBatch, (int)(0.75 * n)));
+}
 
 // inner (not null): an inner solve of a mixed-precision solve, with ||f|| =
 // *inner_fn known on the host and transforms in precision tprec
@@ -1917,6 +1991,8 @@ static int solve_begin_impl(sth_handle* h, const double* f, double* u, double rt
     v.maxit = maxit;
     v.inner = inner_fn != nullptr;
     v.tprec = tprec;
+    h->wait_cyc = 0;
+    if (h->cyc && rtol >= kCycMinRtol) return cyc_begin(h, inner_fn);
     // cycles enqueued ahead of their predecessor's norm (eigenbasis with the
     // fused cycle close; not while kernels are timed one by one)
     v.spec = h->basis == 1 && h->fuse_close && h->speculate && !h->timing;
@@ -2091,11 +2167,14 @@ static int solve_finish(sth_handle* h, bool* more) {
 // Lower bound of the B-spline residual norm of the cycle whose sums are in
 // norm slot `slot` (the larger of the two bounds of solve_continue); slot 2
 // holds the initial pass of a speculative solve
-static double eig_lower_bound(const sth_handle* h, int slot) {
-    const double ssq = h->hnorm[slot_base(slot)], wsq = h->hnorm[slot_base(slot) + 1];
+static double lower_bound_of(const sth_handle* h, double ssq, double wsq) {
     double lo2 = h->nb_lo * ssq;
-    if (h->wsum_valid && std::isfinite(wsq)) lo2 = std::max(lo2, (1.0 - 1e-8) * wsq);
+    if (std::isfinite(wsq)) lo2 = std::max(lo2, (1.0 - 1e-8) * wsq);
     return std::sqrt(lo2);
+}
+static double eig_lower_bound(const sth_handle* h, int slot) {
+    const double* q = h->hnorm + slot_base(slot);
+    return lower_bound_of(h, q[0], h->wsum_valid ? q[1] : 0.0);
 }
 
 // Upper bound of the B-spline residual norm of the same cycle: the smaller
@@ -2106,11 +2185,14 @@ static double eig_lower_bound(const sth_handle* h, int slot) {
 // tolerance the cycle has converged without the exact norm; with the lower
 // bound above the tolerance it provably has not, so the cycle count is that
 // of the plain stopping test either way.
-static double eig_upper_bound(const sth_handle* h, int slot) {
-    const double ssq = h->hnorm[slot_base(slot)], usq = h->hnorm[slot_base(slot) + 2];
+static double upper_bound_of(const sth_handle* h, double ssq, double usq) {
     double up2 = h->nb_hi * ssq;
-    if (h->wsum_valid && std::isfinite(usq)) up2 = std::min(up2, (1.0 + 1e-8) * usq);
+    if (std::isfinite(usq)) up2 = std::min(up2, (1.0 + 1e-8) * usq);
     return std::sqrt(up2);
+}
+static double eig_upper_bound(const sth_handle* h, int slot) {
+    const double* q = h->hnorm + slot_base(slot);
+    return upper_bound_of(h, q[0], h->wsum_valid ? q[2] : INFINITY);
 }
 
 // Exact norm of the current iterate in the speculative loop; on the fused
@@ -2275,6 +2357,205 @@ static int solve_continue_spec(sth_handle* h, bool* more) {
     return spec_exact_norm(h);
 }
 
+// ---------------------------------------------------------------------------
+// Solve by batches of whole cycles (launch_cycles).  The state of the
+// iteration is the residual r^ in the eigenbasis; a batch reads it once, takes
+// up to kMaxBatch cycles on chip and returns the residual norms of each, which
+// go through the stopping test one after the other exactly as in the plain
+// loop.  The iterate that belongs to the residual the loop stops at is
+// L^{-1}(r^_0 - r^) on top of the initial guess.  A batch that ends past the
+// stopping cycle is taken again up to that cycle, from the same residual.
+// ---------------------------------------------------------------------------
+// level-0 eigenbasis vector of a batch: -1 the initial residual, else the
+// iterate buffers
+static double* cyc_buf(sth_handle* h, int i) { return i < 0 ? h->e0 : eig_u(h, 0, i); }
+
+// a buffer that is none of a, b (-2 where there is none)
+static int cyc_free(const sth_handle* h, int a, int b) {
+    for (int i = 0; i < (h->e3 ? 3 : 2); ++i)
+        if (i != a && i != b) return i;
+    return -2;
+}
+
+// m cycles from buffer `from`; end / uout < -1: not stored; sums: the norms of
+// every cycle to the host
+static int cyc_launch(sth_handle* h, int from, int end, int uout, int m, bool sums) {
+    auto& v = h->sv;
+    h->tlev = 0;
+    const double dof = (double)h->lev_S[0] * slab_len(h), eb = h->f32 ? 4.0 : 8.0;
+    if (sums && h->want_poll) ++h->seq_counter;
+    Timed tm(h, STH_K_EIG_CYCLE_CLOSE, dof * (m * (9.4 * h->Nt + 19.0) + (uout >= 0 ? 4.0 * h->Nt : 0.0)),
+             dof * eb * (1.0 + (end >= 0 ? 1.0 : 0.0) + (uout >= 0 ? (from < 0 ? 1.0 : 2.0) : 0.0)), v.st);
+    HIPCHK(launch_cycles(h->Nt, h->L, h->cyc_tab, h->Nxe, h->omega, h->lev_S[0], m, cyc_buf(h, from), h->e0,
+                         end >= 0 ? cyc_buf(h, end) : nullptr, uout >= 0 ? cyc_buf(h, uout) : nullptr,
+                         sums ? h->cpartial : nullptr, h->n_cpartial, h->hcyc_dev, sums && h->want_poll ? h->hcseq_dev : nullptr, h->seq_counter, v.st, h->f32));
+    h->wait_ev = nullptr;
+    h->wait_slot = -1;
+    h->wait_cyc = sums && h->want_poll ? 3 * (m + 1) : 0;
+    h->wait_cyc_seq = h->seq_counter;
+    return STH_OK;
+}
+
+// Next batch from buffer `from`: `want` cycles, the first `known` of which the
+// stopping test has seen (a batch taken again because its residual was not
+// stored).  last: the stopping cycle is expected in it, so the iterate is
+// formed with it, and with at most two cycles to go its residual is not stored.
+static int cyc_batch(sth_handle* h, int from, int want, int known, bool last) {
+    auto& v = h->sv;
+    v.m = std::max(0, std::min({want, h->L == 1 ? 1 : kMaxBatch, v.maxit - v.it + known}));
+    if (!h->speculate) v.m = std::min(v.m, known + 1);
+    v.start = from;
+    v.known = known;
+    v.end = cyc_free(h, from, -2);
+    // (one level: the cycle's own result is the iterate after the first cycle only)
+    v.uout = (last && v.m > 0 && (h->L > 1 || from < 0)) ? cyc_free(h, from, v.end) : -2;
+    if (v.uout >= 0 && h->L > 1 && v.m - known <= 2 && v.m <= kMaxBatch - 2) v.end = -2;
+    v.phase = 10;
+    return cyc_launch(h, v.start, v.end, v.uout, v.m, true);
+}
+
+// the result after j cycles of the current batch
+static int cyc_finish(sth_handle* h, int j, bool* more) {
+    auto& v = h->sv;
+    *more = false;
+    v.phase = 2;
+    h->wait_cyc = 0;
+    if (j == 0 && v.start < 0 && !v.inner) return STH_OK;      // no cycle: u stays as it is
+    int u = v.uout;
+    if (u < 0 || j != v.m) {
+        const int from = j == v.m && j > 0 && v.end >= 0 ? v.end : v.start;
+        u = cyc_free(h, from, -2);
+        int rc;
+        if ((rc = cyc_launch(h, from, -2, u, from == v.start ? j : 0, false))) return rc;
+    }
+    h->wait_cyc = 0;                    // (a launch above sets it)
+    const bool add = v.inner ? !v.inner_store : v.nonzero;
+    return spatial_apply(h, INV_U, cyc_buf(h, u), v.u, h->lev_S[0] * h->Nt, h->buf0, v.st, nullptr, v.tprec,
+                         add ? 1 : 0, h->buf1, h->f32 ? 1 : 0);
+}
+
+// exact B-spline norm of the residual after j cycles of the current batch,
+// which becomes the (empty) current batch
+static int cyc_exact(sth_handle* h, int j) {
+    auto& v = h->sv;
+    int at = v.start, rc;
+    if (j > 0) {
+        const bool stored = j == v.m && v.end >= 0;
+        if (!(v.uout >= 0 && j == v.m)) v.uout = -2;
+        at = v.end >= 0 ? v.end : cyc_free(h, v.start, v.uout);
+        if (!stored && (rc = cyc_launch(h, v.start, at, -2, j, false))) return rc;
+    } else {
+        v.uout = -2;
+    }
+    v.start = v.end = at;
+    v.m = 0;
+    v.phase = 11;
+    h->wait_cyc = 0;
+    return eig_norm_of(h, cyc_buf(h, at), v.st);
+}
+
+static int cyc_begin(sth_handle* h, const double* inner_fn) {
+    auto& v = h->sv;
+    v.cyc = true;
+    h->wait_ev = nullptr;
+    h->wait_slot = -1;
+    h->graph_launched = false;
+    h->presmoothed = false;
+    h->unformed = sth_handle::Unformed{};
+    h->ecur[0] = 0;
+    h->tlev = 0;
+    const long rows = h->lev_S[0] * h->Nt, len = h->lev_S[0] * slab_len(h);
+    int rc;
+    // the initial residual in the eigenbasis: f^ from a zero guess (the usual
+    // start, found on the device: the transforms of the other case return at
+    // once), else that of f - L u
+    if (v.inner) {
+        h->hnorm[1] = (*inner_fn) * (*inner_fn);     // read by the host only
+        if ((rc = spatial_apply(h, FWD_U, v.f, h->e0, rows, h->buf0, v.st, nullptr, v.tprec, 0,
+                                h->f32 ? h->buf1 : nullptr, h->f32 ? 2 : 0)))
+            return rc;
+    } else {
+        int* nz = h->dgo + 6;                        // and its negation behind it
+        {
+            Timed tm(h, STH_K_NORM, 2.0 * len, 16.0 * len, v.st);
+            HIPCHK(launch_solve_prologue(v.f, v.u, len, h->partial, h->dnorm + 1, h->hnorm_dev + 1, nz,
+                                         h->hflag_dev + 4, v.st));
+        }
+        if ((rc = spatial_apply(h, FWD_U, v.f, h->e0, rows, h->buf0, v.st, nz + 1))) return rc;
+        if ((rc = residual(h, 0, v.f, v.u, h->buf1, 0, h->lev_S[0], 1.0, v.st, nz))) return rc;
+        if ((rc = spatial_apply(h, FWD_U, h->buf1, h->e0, rows, h->buf0, v.st, nz))) return rc;
+    }
+    v.first = true;
+    return cyc_batch(h, -1, first_batch(v.rtol), 0, h->L == 1);
+}
+
+static int cyc_continue(sth_handle* h, bool* more) {
+    auto& v = h->sv;
+    const auto target = [&] { return v.rtol * v.fn; };
+    *more = true;
+    h->wait_cyc = 0;
+    if (v.phase == 11) {
+        v.rn = std::sqrt(h->hnorm[0]);
+        if (!(v.rn > target()) || !std::isfinite(v.rn) || v.it >= v.maxit || v.growth >= 3) {
+            return cyc_finish(h, 0, more);            // (the current batch is empty)
+        }
+        return cyc_batch(h, v.start, 1, 0, true);
+    }
+    const double* q = h->hcyc;
+    int j = 0;
+    if (v.first) {
+        v.first = false;
+        v.fn = std::sqrt(h->hnorm[1]);
+        if (v.fn == 0.0) v.fn = 1.0;
+        v.nonzero = !v.inner && h->hflag[4] != 0;
+        v.prev = std::sqrt(q[0]);
+    } else {
+        j = v.known + 1;                             // (sum `known` is the last one tested)
+    }
+    double rate = 0.0;
+    for (; j <= v.m; ++j) {
+        const double ssq = q[3 * j], wsq = q[3 * j + 1], usq = q[3 * j + 2], r = std::sqrt(ssq);
+        if (j > 0) {
+            ++v.it;
+            if (std::isfinite(r)) {
+                v.growth = (r > v.prev) ? v.growth + 1 : 0;
+                rate = v.prev > 0.0 ? r / v.prev : 0.0;
+                v.prev = r;
+            }
+        }
+        v.rn = lower_bound_of(h, ssq, wsq);
+        if (!std::isfinite(r)) {
+            v.rn = r;
+            return cyc_finish(h, j, more);
+        }
+        const bool stop = v.growth >= 3 || v.it >= v.maxit;
+        if (v.rn > target() && !stop) continue;
+        // the bound does not exclude convergence, or this is the last cycle
+        // (whose bound is what a loop with cycles enqueued ahead reports)
+        if (v.rn > target() && h->fuse_close && h->speculate && !h->timing) return cyc_finish(h, j, more);
+        if (v.inner) return cyc_finish(h, j, more);
+        const double up = upper_bound_of(h, ssq, usq);
+        if (up <= target()) {
+            v.rn = up;
+            return cyc_finish(h, j, more);
+        }
+        return cyc_exact(h, j);
+    }
+    // Not converged: as many cycles as the last contraction asks for.  On
+    // large vectors (a batch's transfers, 16 B per unknown, cost more than a
+    // launch and a host round trip) all but two of them first: the contraction
+    // settles on the way, and a batch that ends past the stopping cycle would
+    // be taken again.
+    int want = 1;
+    if (rate > 0.0 && rate < 1.0 && target() > 0.0)
+        want = (int)std::min(64.0, std::max(1.0, std::ceil(std::log(target() / v.rn) / std::log(rate) - 0.05)));
+    const bool large = (double)h->lev_S[0] * slab_len(h) > 4e6;
+    const bool last = want <= (large ? 2 : kMaxBatch);
+    if (!last && large) want = std::max(1, want - 2);
+    if (v.end >= 0) return cyc_batch(h, v.end, want, 0, last);
+    return cyc_batch(h, v.start, v.m + want, v.m, last);
+}
+
 // Once the work enqueued by the previous call has completed: read the
 // residual norm, then enqueue either the next iteration (*more = true) or
 // the final mapping of the result into u (*more = false).
@@ -2300,6 +2581,7 @@ static int solve_continue_impl(sth_handle* h, bool* more) {
         if (rc) return rc;
         h->graph_launched = false;
     }
+    if (v.cyc) return cyc_continue(h, more);
     if (v.spec) return solve_continue_spec(h, more);
     const bool eig = h->basis == 1;
     if (v.phase == 3) {
@@ -2566,6 +2848,31 @@ static int wait_mark(sth_handle* h, hipStream_t st) {
     return STH_OK;
 }
 
+// The same for the marks of a batch's sums.
+static int wait_cycle_marks(sth_handle* h, hipStream_t st) {
+    volatile int* p = h->hcseq;
+    const int want = h->wait_cyc_seq;
+    auto last = std::chrono::steady_clock::now();
+    int i = 0;                                       // marks seen so far
+    for (long spin = 1; i < h->wait_cyc; ++spin) {
+        while (i < h->wait_cyc && p[i] == want) ++i;
+        if ((spin & 1023) != 0 || i == h->wait_cyc) continue;
+        const auto now = std::chrono::steady_clock::now();
+        if (now - last >= std::chrono::milliseconds(1)) {
+            last = now;
+            const hipError_t q = hipStreamQuery(st);
+            if (q == hipSuccess) {
+                while (i < h->wait_cyc && p[i] == want) ++i;
+                if (i == h->wait_cyc) break;
+                return fail(STH_EHIP, "completion marks of a batch of cycles not set");
+            }
+            if (q != hipErrorNotReady) return fail(STH_EHIP, std::string("stream work failed: ") + hipGetErrorString(q));
+        }
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+    return STH_OK;
+}
+
 int sth_solve(sth_handle* h, const double* f, double* u, double rtol, int maxit, int* iters, double* relres,
               void* stream) {
     if (!h || !f || !u || !(rtol >= 0) || maxit < 0) return fail(STH_EINVAL, "bad argument");
@@ -2576,7 +2883,8 @@ int sth_solve(sth_handle* h, const double* f, double* u, double rtol, int maxit,
     int rc = solve_begin(h, f, u, rtol, maxit, st);
     bool more = true;
     while (rc == STH_OK && more) {
-        if (h->wait_slot >= 0) rc = wait_mark(h, st);
+        if (h->wait_cyc > 0) rc = wait_cycle_marks(h, st);
+        else if (h->wait_slot >= 0) rc = wait_mark(h, st);
         else if (h->wait_ev) HIPCHK(hipEventSynchronize(h->wait_ev));
         else HIPCHK(hipStreamSynchronize(st));
         if (rc == STH_OK) rc = solve_continue(h, &more);
@@ -2607,7 +2915,16 @@ static int precondition(sth_handle* h, const double* v, double* z, hipStream_t s
     h->ecur[0] = 0;
     h->presmoothed = false;
     h->unformed = sth_handle::Unformed{};
-    if ((rc = eig_vcycle(h, 0, true, st))) return rc;
+    if (h->cyc && h->L > 1) {
+        // one cycle from zero on chip, the iterate formed with it
+        const double dof = (double)h->lev_S[0] * slab_len(h);
+        h->tlev = 0;
+        Timed tm(h, STH_K_EIG_CYCLE_CLOSE, dof * (13.4 * h->Nt + 19.0), dof * 2.0 * (h->f32 ? 4.0 : 8.0), st);
+        HIPCHK(launch_cycles(h->Nt, h->L, h->cyc_tab, h->Nxe, h->omega, h->lev_S[0], 1, h->e0, h->e0, nullptr,
+                             eig_u(h, 0, 0), nullptr, 0, nullptr, nullptr, 0, st, h->f32));
+    } else if ((rc = eig_vcycle(h, 0, true, st))) {
+        return rc;
+    }
     return spatial_apply(h, INV_U, eig_u(h, 0, h->ecur[0]), z, rows, h->buf0, st, nullptr, h->prec, 0, h->buf1,
                          h->f32 ? 1 : 0);
 }
@@ -2765,6 +3082,7 @@ int sth_destroy(sth_handle* h) {
         if (q) (void)hipFree(q);
     for (double* q : h->eo)
         if (q) (void)hipFree(q);
+    if (h->cyc_tab) (void)hipFree(h->cyc_tab);
     double* ptrs[] = {h->Tf, h->Ti, h->mu1, h->M1b, h->K1b, h->buf0, h->buf1, h->partial, h->dnorm, h->dktmt,
                       h->Cf, h->Ci, h->Gf, h->e0, h->e1, h->e2, h->e3, h->cpartial, h->kv, h->kz, h->kc,
                       h->kpart, h->vw};
@@ -2776,6 +3094,8 @@ int sth_destroy(sth_handle* h) {
     if (h->hnorm) (void)hipHostFree(h->hnorm);
     if (h->hflag) (void)hipHostFree(h->hflag);
     if (h->hseq) (void)hipHostFree(h->hseq);
+    if (h->hcyc) (void)hipHostFree(h->hcyc);
+    if (h->hcseq) (void)hipHostFree(h->hcseq);
     if (h->dthr) (void)hipFree(h->dthr);
     if (h->dmix) (void)hipFree(h->dmix);
     if (h->dgo) (void)hipFree(h->dgo);
