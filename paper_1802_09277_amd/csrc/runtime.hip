@@ -92,6 +92,7 @@ struct sth_handle {
     // whole cycles on chip (launch_cycles): the eigenbasis solve runs batches
     // of cycles on the residual
     bool cyc = false;
+    bool batches = false;               // ... and so do solves of the coefficient iteration
     double* cyc_tab = nullptr;          // per mode: its matrices on every level (launch_cycles_table)
     double* hcyc = nullptr;             // mapped, coherent: the sums of a batch
     double* hcyc_dev = nullptr;
@@ -670,11 +671,14 @@ static int vcycle_lvl(sth_handle* h, int lvl, const double* f, double* u, bool z
 // the coarse-grid correction below the last level of h: V-cycle of the
 // child from a zero guess (its exact solve when it has one level)
 static int child_cycle(sth_handle* c, const double* f, double* u, hipStream_t st) {
-    if (c->L == 1 && !c->child) return coarse_solve(c, 0, f, u, st);
+    if (c->L == 1 && !c->child && !c->cyc) return coarse_solve(c, 0, f, u, st);
     return vcycle_lvl(c, 0, f, u, true, st);
 }
 
+static int mode_cycle(sth_handle* h, const double* f, double* u, bool zero_guess, bool have_r, hipStream_t st);
+
 static int vcycle_lvl(sth_handle* h, int lvl, const double* f, double* u, bool zero_guess, hipStream_t st) {
+    if (lvl == 0 && h->basis == 0 && h->cyc) return mode_cycle(h, f, u, zero_guess, false, st);
     h->tlev = lvl;
     int rc;
     if (lvl == h->L - 1 && !h->child) {
@@ -806,6 +810,29 @@ static int spatial_apply(sth_handle* h, SpatialKind kind, const double* in, doub
         if ((rc = xform_x(h, prec, epi, tmp2, out, T, rows * n * n, 1.0, st, g))) return rc;   // x
     }
     return STH_OK;
+}
+
+// A V-cycle of the coefficient iteration as u += (I (x) U) V((I (x) U^T) r):
+// one residual, the transforms, and the cycle on chip from zero, instead of
+// two transforms and a residual for each smoothing step of each level (at 101
+// x 101 x 300 x 3 unknowns 1236 us, now 384).  From a zero guess r = f;
+// have_r: buf1 holds f - L u already.  buf0 and buf1 are the work vectors.
+static int mode_cycle(sth_handle* h, const double* f, double* u, bool zero_guess, bool have_r, hipStream_t st) {
+    const long S = h->lev_S[0], rows = S * h->Nt;
+    int rc;
+    if (!zero_guess && !have_r && (rc = residual(h, 0, f, u, h->buf1, 0, S, 1.0, st))) return rc;
+    // (spatial_apply reads its input before it writes buf1)
+    const bool axes2 = h->dim == 2 && !xform2d_supported(h->np);
+    double* a = axes2 ? h->buf1 : h->buf0;
+    double* b = axes2 ? h->buf0 : h->buf1;
+    if ((rc = spatial_apply(h, FWD_U, zero_guess ? f : h->buf1, a, rows, b, st))) return rc;
+    {
+        const double dof = (double)S * slab_len(h);
+        Timed tm(h, STH_K_EIG_CYCLE_CLOSE, dof * (13.4 * h->Nt + 19.0), dof * 24.0, st);
+        HIPCHK(launch_cycles(h->Nt, h->L, h->cyc_tab, h->Nxe, h->omega, S, 1, a, a, nullptr, b, nullptr, 0, nullptr,
+                             nullptr, 0, st, false));
+    }
+    return spatial_apply(h, INV_U, b, u, rows, a, st, nullptr, STH_FP64, zero_guess ? 0 : 1, b);
 }
 
 static double* eig_u(sth_handle* h, int lvl, int which) {
@@ -1055,9 +1082,11 @@ static int form_result(sth_handle* h, hipStream_t st) {
     return STH_OK;
 }
 
-// ||(I (x) C_x) r||^2 of the FP64 eigenbasis vector r (which may be buf0) to
-// hnorm[0] (not synchronised); buf0 and buf1 are the work vectors
-static int eig_norm_of(sth_handle* h, const double* r, hipStream_t st, const CycleFlag& fin = CycleFlag{}) {
+// ||(I (x) C_x) r||^2 of the FP64 eigenbasis vector r (which may be w0) to
+// hnorm[0] (not synchronised); w0 and w1 are the work vectors of the per-axis
+// transforms
+static int eig_norm_of(sth_handle* h, const double* r, double* w0, double* w1, hipStream_t st,
+                       const CycleFlag& fin = CycleFlag{}) {
     h->tlev = 0;
     const long S = h->lev_S[0], rows = S * h->Nt;
     const double dof = (double)S * slab_len(h);
@@ -1068,10 +1097,10 @@ static int eig_norm_of(sth_handle* h, const double* r, hipStream_t st, const Cyc
                                   h->hnorm_dev, st, fin, h->Nxe));
         return STH_OK;                  // stored hnorm[0] itself
     }
-    // per-axis transforms (2-D: s then x, r -> buf1 -> buf0; 3-D: r -> buf1 ->
-    // buf0 -> buf1; the rows of these paths are not padded)
-    double* out = h->dim == 2 ? h->buf0 : h->buf1;
-    int rc = spatial_apply(h, INV_C, r, out, rows, h->dim == 2 ? h->buf1 : h->buf0, st);
+    // per-axis transforms (2-D: s then x, r -> w1 -> w0; 3-D: r -> w1 -> w0 ->
+    // w1; the rows of these paths are not padded)
+    double* out = h->dim == 2 ? w0 : w1;
+    int rc = spatial_apply(h, INV_C, r, out, rows, h->dim == 2 ? w1 : w0, st);
     if (rc) return rc;
     if ((rc = norm2_dev(h, out, S * eslab_len(h), st))) return rc;
     HIPCHK(hipMemcpyAsync(h->hnorm, h->dnorm, sizeof(double), hipMemcpyDeviceToHost, st));
@@ -1092,7 +1121,7 @@ static int eig_exact_norm(sth_handle* h, hipStream_t st, const CycleFlag& fin = 
         HIPCHK(launch_eig_residual(h->dim, h->Nt, level_ktmt(h, 0), h->mu1, h->n, h->e0, eig_u(h, 0, h->ecur[0]),
                                    h->buf0, S, st));
     }
-    return eig_norm_of(h, h->buf0, st, fin);
+    return eig_norm_of(h, h->buf0, h->buf0, h->buf1, st, fin);
 }
 
 // ---------------------------------------------------------------------------
@@ -1191,20 +1220,32 @@ static bool f32_storage(const Problem& q, size_t levels) {
            ((q.dim == 2 && xform2d_supported(np)) || xform_panel_f32_io(np));
 }
 
-// Whole cycles on chip: eigenbasis iteration with V(1,1) cycles, levels and
-// time line within what a block holds
+// Whole cycles on chip: V(1,1) cycles, levels and time line within what a
+// block holds; in the B-spline coefficient iteration, whose cycle is the same
+// map between the spatial transforms, with exact FP64 slab inverses and
+// coarsening in time only
 static bool cycles_on_chip(const Problem& q, size_t levels) {
-    return q.basis == 1 && q.nu_pre == 1 && q.nu_post == 1 && cycles_supported(q.Nt(), (int)levels, q.n_slabs);
+    return (q.basis == 1 || (q.prec == STH_FP64 && q.minres_iters == 0 && space_transition(q) == 0)) &&
+           q.nu_pre == 1 && q.nu_post == 1 && cycles_supported(q.Nt(), (int)levels, q.n_slabs);
+}
+
+// ... and whole solves of the coefficient iteration in batches of them: with
+// several levels, whose vectors (one to 1.75 of the finest level) they replace
+// by one.  62 x 62 x 192 x 5 unknowns, 11 cycles: 6811 -> 341 us (single
+// cycles between transforms and residuals about 2 ms); with one level a solve
+// is one or two cycles and needs no further vector.
+static bool coefficient_batches(const Problem& q, size_t levels) {
+    return q.basis == 0 && levels > 1 && cycles_on_chip(q, levels);
 }
 
 // third iterate buffer: the fused cycle close, or batches of several levels
 static bool third_buffer(const Problem& q, size_t levels) {
-    return fused_cycle_close(q, levels) || (levels > 1 && cycles_on_chip(q, levels));
+    return fused_cycle_close(q, levels) || (q.basis == 1 && levels > 1 && cycles_on_chip(q, levels));
 }
 
 // per-block partial sums of the eigenbasis passes
 static size_t cycle_partials(const Problem& q, size_t levels, long modes) {
-    const size_t pass = 3 * (((size_t)(q.n_slabs / 2) * (size_t)modes + 255) / 256);
+    const size_t pass = q.basis == 1 ? 3 * (((size_t)(q.n_slabs / 2) * (size_t)modes + 255) / 256) : 0;
     return std::max(pass, cycles_on_chip(q, levels)
                               ? (size_t)cycles_partials(modes) : 0);
 }
@@ -1233,21 +1274,22 @@ static size_t workspace_of(Problem q) {
     long slab = (long)q.Nt() * Nx;
     size_t total = 0;
     total += 2 * sizeof(double) * np * np;                   // transforms
-    total += (q.basis == 1 ? 4 : 2) * sizeof(double) * xform_eo_pack_len((int)n);
+    const bool onchip = cycles_on_chip(q, level_count(q)), batches = coefficient_batches(q, level_count(q));
+    total += (q.basis == 1 || batches ? 4 : 2) * sizeof(double) * xform_eo_pack_len((int)n);
     total += sizeof(double) * n * (1 + 2 * (2 * q.degree + 1));
     const bool f32 = f32_storage(q, level_count(q));
-    const size_t evecs0 = q.basis == 1 ? 3 + (third_buffer(q, level_count(q)) ? 1 : 0) : 0;   // f^, u^ (x2 or 3)
+    // f^, u^ (x2 or 3)
+    const size_t evecs0 = q.basis == 1 ? 3 + (third_buffer(q, level_count(q)) ? 1 : 0) : (batches ? 1 : 0);
     total += 2 * sizeof(double) * (size_t)q.n_slabs * slab;                            // buf0, buf1
     total += evecs0 * (f32 ? sizeof(float) : sizeof(double)) * (size_t)q.n_slabs * slab;
     // per coarse level: u, f (nodal), and the eigenbasis u^, its partner and
     // f^ (the u, f pair shared unless the eigenbasis vectors are float)
-    const size_t vecsl_bytes = 2 * sizeof(double) + (q.basis == 1 ? (f32 ? 3 * sizeof(float) : sizeof(double)) : 0);
-    if (q.basis == 1) {
+    const size_t vecsl_bytes = q.basis == 1 ? 2 * sizeof(double) + (f32 ? 3 * sizeof(float) : sizeof(double))
+                                            : (onchip ? 0 : 2 * sizeof(double));
+    if (onchip) total += sizeof(double) * cycles_table_len(q.Nt(), (int)level_count(q), Nx);
+    if (q.basis == 1 || batches) {
         total += 3 * sizeof(double) * np * np;                // C, C^T, G
         total += sizeof(double) * (cycle_partials(q, level_count(q), Nx) + 1);
-        if (cycles_on_chip(q, level_count(q)))
-            total += sizeof(double) * cycles_table_len(q.Nt(), (int)level_count(q), Nx);
-
         total += sizeof(double) * 2 * n;                                 // mode weights
     }
     long S = q.n_slabs;
@@ -1392,7 +1434,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     h->Nt = h->S.Nt;
     h->p = q.degree;
     h->Nx = (long)h->n * h->n * (q.dim == 3 ? h->n : 1);
-    h->Nxe = eig_modes(q.dim, h->n);
+    h->Nxe = q.basis == 1 ? eig_modes(q.dim, h->n) : h->Nx;
     h->omega = q.omega;
     h->nu_pre = q.nu_pre;
     h->nu_post = q.nu_post;
@@ -1408,6 +1450,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     h->fuse_close = fused_cycle_close(q, (size_t)h->L);
     h->f32 = f32_storage(q, (size_t)h->L);
     h->cyc = cycles_on_chip(q, (size_t)h->L);
+    h->batches = coefficient_batches(q, (size_t)h->L);
     {
         int G = 0, LA = 0;
         h->fuse_tail = h->basis == 1 && h->nu_pre == 1 && h->nu_post == 1 && h->L >= 3 &&
@@ -1513,7 +1556,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     h->eu.assign(h->L, nullptr);
     h->ef.assign(h->L, nullptr);
     h->eu2.assign(h->L, nullptr);
-    for (int l = 1; l < h->L; ++l) {
+    for (int l = 1; l < h->L && !(h->cyc && h->basis == 0); ++l) {
         if (!dalloc(&h->lu[l], (size_t)h->lev_S[l] * slab) || !dalloc(&h->lf[l], (size_t)h->lev_S[l] * slab))
             return cleanup(STH_ENOMEM, "device allocation failed");
         if (h->basis == 1 && !h->f32 && !dalloc(&h->lu2[l], (size_t)h->lev_S[l] * slab))
@@ -1530,7 +1573,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
         hipSuccess)
         return cleanup(STH_EHIP, "upload of the setup failed");
     std::vector<double> Cf, Ci, Gf;
-    if (h->basis == 1) {
+    if (h->basis == 1 || h->batches) {
         // C = M_1 U = U^{-T} (from U^T M_1 U = I)
         Cf.assign((size_t)np * np, 0.0);
         Ci.assign((size_t)np * np, 0.0);
@@ -1544,8 +1587,9 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
         h->n_cpartial = (long)cycle_partials(q, (size_t)h->L, h->Nxe);
         if (!dalloc(&h->cpartial, (size_t)h->n_cpartial) ||
             !dalloc(&h->Cf, (size_t)np * np) || !dalloc(&h->Ci, (size_t)np * np) ||
-            !dalloc(&h->e0, ecount((size_t)q.n_slabs * eslab)) || !dalloc(&h->e1, ecount((size_t)q.n_slabs * eslab)) ||
-            !dalloc(&h->e2, ecount((size_t)q.n_slabs * eslab)) ||
+            !dalloc(&h->e0, ecount((size_t)q.n_slabs * eslab)) ||
+            (h->basis == 1 && !dalloc(&h->e1, ecount((size_t)q.n_slabs * eslab))) ||
+            (h->basis == 1 && !dalloc(&h->e2, ecount((size_t)q.n_slabs * eslab))) ||
             (third_buffer(q, (size_t)h->L) && !dalloc(&h->e3, ecount((size_t)q.n_slabs * eslab))))
             return cleanup(STH_ENOMEM, "device allocation failed");
         // the padded modes of the eigenbasis vectors start (and stay) zero
@@ -1585,7 +1629,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     // packed panels of the FP64 per-axis transforms
     const size_t eo_len = xform_eo_pack_len(n);
     std::vector<double> eo_host[4];
-    for (int i = 0; i < (h->basis == 1 ? 4 : 2) && eo_len > 0; ++i) {
+    for (int i = 0; i < (h->basis == 1 || h->batches ? 4 : 2) && eo_len > 0; ++i) {
         eo_host[i].assign(eo_len, 0.0);
         xform_eo_pack(i % 2 == 1, i < 2 ? Tf.data() : Cf.data(), n, np, eo_host[i].data());
         if (!dalloc(&h->eo[i], eo_len)) return cleanup(STH_ENOMEM, "device allocation failed");
@@ -1862,7 +1906,8 @@ static int solve_iteration(sth_handle* h, const double* f, double* u, hipStream_
         h->guard = nullptr;
         return rc;
     }
-    if ((rc = vcycle_lvl(h, 0, f, u, false, st))) return rc;
+    // (buf1 holds the residual of u)
+    if ((rc = h->cyc ? mode_cycle(h, f, u, false, true, st) : vcycle_lvl(h, 0, f, u, false, st))) return rc;
     if ((rc = residual(h, 0, f, u, h->buf1, 0, h->lev_S[0], 1.0, st))) return rc;
     if ((rc = norm2_dev(h, h->buf1, len, st))) return rc;
     HIPCHK(hipMemcpyAsync(h->hnorm, h->dnorm, sizeof(double), hipMemcpyDeviceToHost, st));
@@ -1979,6 +2024,21 @@ static int first_batch(double rtol) {
 
 // inner (not null): an inner solve of a mixed-precision solve, with ||f|| =
 // *inner_fn known on the host and transforms in precision tprec
+// The initial residual of the coefficient iteration and its norm (||f||^2 is
+// on its way to the pinned host scalars): the loop over single cycles.
+static int coefficient_begin(sth_handle* h) {
+    auto& v = h->sv;
+    v.cyc = false;
+    v.phase = 0;
+    h->wait_ev = nullptr;
+    h->wait_slot = -1;
+    int rc;
+    if ((rc = residual(h, 0, v.f, v.u, h->buf1, 0, h->lev_S[0], 1.0, v.st))) return rc;
+    if ((rc = norm2_dev(h, h->buf1, h->lev_S[0] * slab_len(h), v.st))) return rc;
+    HIPCHK(hipMemcpyAsync(h->hnorm, h->dnorm, sizeof(double), hipMemcpyDeviceToHost, v.st));
+    return STH_OK;
+}
+
 static int solve_begin_impl(sth_handle* h, const double* f, double* u, double rtol, int maxit, hipStream_t st,
                             const double* inner_fn = nullptr, int tprec = STH_FP64) {
     if (!h || !f || !u || !(rtol >= 0) || maxit < 0) return fail(STH_EINVAL, "bad argument");
@@ -1992,7 +2052,7 @@ static int solve_begin_impl(sth_handle* h, const double* f, double* u, double rt
     v.inner = inner_fn != nullptr;
     v.tprec = tprec;
     h->wait_cyc = 0;
-    if (h->cyc && rtol >= kCycMinRtol) return cyc_begin(h, inner_fn);
+    if ((h->basis == 1 ? h->cyc : h->batches) && rtol >= kCycMinRtol) return cyc_begin(h, inner_fn);
     // cycles enqueued ahead of their predecessor's norm (eigenbasis with the
     // fused cycle close; not while kernels are timed one by one)
     v.spec = h->basis == 1 && h->fuse_close && h->speculate && !h->timing;
@@ -2076,10 +2136,7 @@ static int solve_begin_impl(sth_handle* h, const double* f, double* u, double rt
         v.phase = 4;                    // (enqueue_iteration sets phase 1)
         return STH_OK;
     }
-    if ((rc = residual(h, 0, f, u, h->buf1, 0, h->lev_S[0], 1.0, st))) return rc;
-    if ((rc = norm2_dev(h, h->buf1, len, st))) return rc;
-    HIPCHK(hipMemcpyAsync(h->hnorm, h->dnorm, sizeof(double), hipMemcpyDeviceToHost, st));
-    return STH_OK;
+    return coefficient_begin(h);
 }
 
 static bool solve_should_stop(const sth_handle::SolveState& v) {
@@ -2366,12 +2423,20 @@ static int solve_continue_spec(sth_handle* h, bool* more) {
 // L^{-1}(r^_0 - r^) on top of the initial guess.  A batch that ends past the
 // stopping cycle is taken again up to that cycle, from the same residual.
 // ---------------------------------------------------------------------------
-// level-0 eigenbasis vector of a batch: -1 the initial residual, else the
-// iterate buffers
-static double* cyc_buf(sth_handle* h, int i) { return i < 0 ? h->e0 : eig_u(h, 0, i); }
+// Eigenbasis vector of a batch: -1 the initial residual, else the iterate
+// buffers.  The coefficient iteration has buf0, buf1 and, from the second
+// batch on, the caller's u, which is known to be zero by then.
+static double* cyc_buf(sth_handle* h, int i) {
+    if (i < 0) return h->e0;
+    if (h->basis == 0) return i == 0 ? h->buf0 : (i == 1 ? h->buf1 : h->sv.u);
+    return eig_u(h, 0, i);
+}
 
-// a buffer that is none of a, b (-2 where there is none)
-static int cyc_free(const sth_handle* h, int a, int b) {
+// a buffer that is none of a, b (-2 where there is none); in the coefficient
+// iteration u holds residuals only (the result is mapped from another buffer
+// into it)
+static int cyc_free(const sth_handle* h, int a, int b, bool residual) {
+    if (h->basis == 0 && residual && !h->sv.first && a != 2 && b != 2) return 2;
     for (int i = 0; i < (h->e3 ? 3 : 2); ++i)
         if (i != a && i != b) return i;
     return -2;
@@ -2406,9 +2471,9 @@ static int cyc_batch(sth_handle* h, int from, int want, int known, bool last) {
     if (!h->speculate) v.m = std::min(v.m, known + 1);
     v.start = from;
     v.known = known;
-    v.end = cyc_free(h, from, -2);
+    v.end = cyc_free(h, from, -2, true);
     // (one level: the cycle's own result is the iterate after the first cycle only)
-    v.uout = (last && v.m > 0 && (h->L > 1 || from < 0)) ? cyc_free(h, from, v.end) : -2;
+    v.uout = (last && v.m > 0 && (h->L > 1 || from < 0)) ? cyc_free(h, from, v.end, false) : -2;
     if (v.uout >= 0 && h->L > 1 && v.m - known <= 2 && v.m <= kMaxBatch - 2) v.end = -2;
     v.phase = 10;
     return cyc_launch(h, v.start, v.end, v.uout, v.m, true);
@@ -2420,18 +2485,22 @@ static int cyc_finish(sth_handle* h, int j, bool* more) {
     *more = false;
     v.phase = 2;
     h->wait_cyc = 0;
-    if (j == 0 && v.start < 0 && !v.inner) return STH_OK;      // no cycle: u stays as it is
+    if (j == 0 && v.start < 0 && !v.inner) {
+        // no cycle: u stays as it is (zero again where it was a work vector)
+        if (h->basis == 0) HIPCHK(launch_fill(v.u, h->lev_S[0] * slab_len(h), 0.0, v.st));
+        return STH_OK;
+    }
     int u = v.uout;
     if (u < 0 || j != v.m) {
         const int from = j == v.m && j > 0 && v.end >= 0 ? v.end : v.start;
-        u = cyc_free(h, from, -2);
+        u = cyc_free(h, from, -2, false);
         int rc;
         if ((rc = cyc_launch(h, from, -2, u, from == v.start ? j : 0, false))) return rc;
     }
     h->wait_cyc = 0;                    // (a launch above sets it)
     const bool add = v.inner ? !v.inner_store : v.nonzero;
-    return spatial_apply(h, INV_U, cyc_buf(h, u), v.u, h->lev_S[0] * h->Nt, h->buf0, v.st, nullptr, v.tprec,
-                         add ? 1 : 0, h->buf1, h->f32 ? 1 : 0);
+    return spatial_apply(h, INV_U, cyc_buf(h, u), v.u, h->lev_S[0] * h->Nt, h->basis == 0 ? h->e0 : h->buf0, v.st,
+                         nullptr, v.tprec, add ? 1 : 0, h->buf1, h->f32 ? 1 : 0);
 }
 
 // exact B-spline norm of the residual after j cycles of the current batch,
@@ -2442,7 +2511,7 @@ static int cyc_exact(sth_handle* h, int j) {
     if (j > 0) {
         const bool stored = j == v.m && v.end >= 0;
         if (!(v.uout >= 0 && j == v.m)) v.uout = -2;
-        at = v.end >= 0 ? v.end : cyc_free(h, v.start, v.uout);
+        at = v.end >= 0 ? v.end : cyc_free(h, v.start, v.uout, true);
         if (!stored && (rc = cyc_launch(h, v.start, at, -2, j, false))) return rc;
     } else {
         v.uout = -2;
@@ -2451,7 +2520,14 @@ static int cyc_exact(sth_handle* h, int j) {
     v.m = 0;
     v.phase = 11;
     h->wait_cyc = 0;
-    return eig_norm_of(h, cyc_buf(h, at), v.st);
+    double *w0 = h->buf0, *w1 = h->buf1;
+    if (h->basis == 0) {
+        // the two other buffers (an iterate in one of them is formed again)
+        w0 = cyc_buf(h, at == 0 ? 1 : 0);
+        w1 = cyc_buf(h, at == 2 ? 1 : 2);
+        if (!(h->dim == 2 && xform2d_supported(h->np))) v.uout = -2;
+    }
+    return eig_norm_of(h, cyc_buf(h, at), w0, w1, v.st);
 }
 
 static int cyc_begin(sth_handle* h, const double* inner_fn) {
@@ -2492,6 +2568,7 @@ static int cyc_begin(sth_handle* h, const double* inner_fn) {
 static int cyc_continue(sth_handle* h, bool* more) {
     auto& v = h->sv;
     const auto target = [&] { return v.rtol * v.fn; };
+    const bool coef = h->basis == 0;                 // (it reports exact norms only)
     *more = true;
     h->wait_cyc = 0;
     if (v.phase == 11) {
@@ -2509,6 +2586,7 @@ static int cyc_continue(sth_handle* h, bool* more) {
         if (v.fn == 0.0) v.fn = 1.0;
         v.nonzero = !v.inner && h->hflag[4] != 0;
         v.prev = std::sqrt(q[0]);
+        if (coef && v.nonzero) return coefficient_begin(h);      // (u holds the guess: no third buffer)
     } else {
         j = v.known + 1;                             // (sum `known` is the last one tested)
     }
@@ -2532,10 +2610,10 @@ static int cyc_continue(sth_handle* h, bool* more) {
         if (v.rn > target() && !stop) continue;
         // the bound does not exclude convergence, or this is the last cycle
         // (whose bound is what a loop with cycles enqueued ahead reports)
-        if (v.rn > target() && h->fuse_close && h->speculate && !h->timing) return cyc_finish(h, j, more);
+        if (v.rn > target() && !coef && h->fuse_close && h->speculate && !h->timing) return cyc_finish(h, j, more);
         if (v.inner) return cyc_finish(h, j, more);
         const double up = upper_bound_of(h, ssq, usq);
-        if (up <= target()) {
+        if (up <= target() && !coef) {
             v.rn = up;
             return cyc_finish(h, j, more);
         }

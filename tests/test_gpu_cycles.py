@@ -22,10 +22,10 @@ SHAPES = [
 ]
 
 
-def _solver(shape, **kw):
+def _solver(shape, basis="eigen", **kw):
     import paper_1802_09277_amd as sth
     dim, n_elem, degree, n_slabs, n_elem_t, coarse = shape
-    return sth.Solver(dim, n_elem, degree, n_slabs, n_elem_t, basis="eigen", coarse_slabs=coarse, **kw)
+    return sth.Solver(dim, n_elem, degree, n_slabs, n_elem_t, basis=basis, coarse_slabs=coarse, **kw)
 
 
 def _vector(s, seed):
@@ -72,3 +72,45 @@ def test_reported_residual(shape, prec):
     it1, _, _ = s.solve(f, w, rtol=1e-8, maxit=80, check=False)
     if prec == "fp64":
         assert it1 == it and float((u - w).abs().max()) <= 1e-10 * float(u.abs().max())
+
+
+# per-axis transforms in two dimensions as well
+@pytest.mark.parametrize("shape", SHAPES + [(2, 97, 1, 6, 1, 3), (2, 99, 2, 40, 1, 5), (2, 98, 1, 70, 2, 35)])
+def test_coefficient_iteration(shape):
+    """The B-spline coefficient iteration: batches (zero guess) and single
+    cycles between transforms (smaller tolerances, other guesses, V-cycle
+    calls) against each other and against the eigenbasis iteration level by
+    level; residual norms are those of the result."""
+    print(f"[gpu-cycles] coefficients {shape}", flush=True)
+    s, e = _solver(shape, "nodal"), _solver(shape)
+    f, g = _vector(s, 4), _vector(s, 5)
+    for maxit, guess in ((0, False), (1, False), (1, True), (2, False), (3, True), (9, False)):
+        start = (lambda: g.clone()) if guess else s.new_vector
+        ua, ub, uc, ud = start(), start(), start(), start()
+        ia, ra, _ = s.solve(f, ua, rtol=1e-12, maxit=maxit, check=False)
+        ib, rb, _ = s.solve(f, ub, rtol=1e-13, maxit=maxit, check=False)
+        ic, _, _ = e.solve(f, uc, rtol=1e-13, maxit=maxit, check=False)
+        for _ in range(ia):
+            s.vcycle(f, ud)
+        one = s.num_levels == 1                     # the first cycle is exact
+        assert ia == ib == ic or (one and min(ia, ib, ic) >= 1)
+        for u in (ub, uc, ud):
+            assert float((ua - u).abs().max()) <= 1e-10 * float(u.abs().max())
+        if rb > 1e-9:
+            assert abs(ra - rb) <= 1e-8 * rb and abs(_relres(s, f, ua) - ra) <= 1e-8 * ra
+
+
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[3] > s[5]] + [(2, 99, 2, 40, 1, 5)])
+def test_coefficient_solve(shape):
+    print(f"[gpu-cycles] coefficient solve {shape}", flush=True)
+    s, e = _solver(shape, "nodal"), _solver(shape)
+    f, u, w = _vector(s, 6), s.new_vector(), s.new_vector()
+    it, rr, _ = s.solve(f, u, rtol=1e-8, maxit=80)
+    ie, _, _ = e.solve(f, w, rtol=1e-8, maxit=80)
+    assert it == ie and rr <= 1e-8
+    assert abs(_relres(s, f, u) - rr) <= 1e-4 * rr
+    assert float((u - w).abs().max()) <= 1e-10 * float(w.abs().max())
+    # the preconditioner: one such cycle from zero
+    w = s.new_vector()
+    s.solve_fgmres(f, w, rtol=1e-8, maxit=80)
+    assert _relres(s, f, w) <= 1e-8 * (1.0 + 1e-4)
