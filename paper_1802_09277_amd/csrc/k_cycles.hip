@@ -25,18 +25,20 @@
 // the time line (modes across the lanes kept them in vector registers or LDS:
 // 3.9 ms per batch against 2.2 ms on 65536 modes x 1024 slabs x 3).  Rows
 // between lanes and the recurrence x_s = a_s + gamma x_{s-1} of the exact
-// solve go through wave shuffles; no barrier inside a cycle.  A block
+// solve go by data-parallel primitives (through LDS shuffles 9 to 14 % slower);
+// no barrier inside a cycle.  A block
 // takes 8 or 16 modes, pieces of 64 or 128 bytes of each row, transposed
 // through LDS on the way in and out.
 //
 // A cycle takes about 5 N_t + 10 multiply-adds per unknown and no memory
 // traffic, against 40 B per unknown of passes over the vectors level by
 // level; a batch moves 16 B per unknown, 24 with the iterate.  On 65536 modes
-// x 1024 slabs x 3 (1.6 GB vectors) a cycle takes 0.13 ms and the transfers,
-// which bound a batch, 1.3 ms (2.5 TB/s: one block per compute unit at 254
-// registers, so little of them overlaps the cycles); the solve of 12 cycles
-// went from 23.6 to 10.4 ms, 4489 modes x 256 slabs x 5 from 1078 to 342 us,
-// 1024 modes x 16 slabs x 4 from 114 to 73 us.
+// x 1024 slabs x 3 (1.6 GB vectors) a cycle takes 0.13 ms; a batch of 8 takes
+// 1.32 ms, one of 2 1.15 ms and 2.07 ms with the iterate: there the transfers
+// bound it (2.3 to 2.8 TB/s by rows of modes, 3.6 by time lines; one block per
+// compute unit at 250 registers, so little of them overlaps the cycles).
+// Solves, from passes level by level: the 12 cycles there 23.6 -> 9.3 ms,
+// 4489 modes x 256 slabs x 5 1078 -> 320 us, 1024 x 16 x 4 114 -> 73 us.
 #include <algorithm>
 
 #include "kernels_common.hpp"
@@ -45,6 +47,7 @@ namespace sth {
 
 struct CycArgs {
     int L, m;
+    int rin_lines, rout_lines;  // residual by time lines: [mode][row of a lane][lane]
     long S, Nx;
     double omega;
     // per mode: A_l^{-1} (l < L), A P_0, A P_1 (one level: A), the two norm
@@ -120,11 +123,27 @@ __global__ __launch_bounds__(256) void k_mode_table(int dim, int n, int L, long 
 // wave-uniform tables: scalar loads
 typedef const __attribute__((address_space(4))) double* uptr;
 
+// A double from another lane of the wave by data-parallel primitives (no trip
+// through LDS): lanes without a source, or in rows outside the mask, get 0.
+constexpr int kDppRowShr = 0x110, kDppWaveShr1 = 0x138, kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp(double v) {
+    const long b = __builtin_bit_cast(long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, (long)(unsigned)lo | (long)hi << 32);
+}
+
 // ONE: a single level.  A cycle is the exact solve e = L^{-1} r, whose result
 // goes to uout, and r becomes its residual r - L e (m = 1).
 // MB: modes (waves) per block.
+// Waves per SIMD to leave registers for: two blocks of 8 per compute unit up
+// to 24 values per lane, so that one block's transfers overlap the other's
+// cycles (a first batch of 8 on 65536 modes x 512 slabs x 3: 722 against 1094
+// us; 10404 modes x 150 slabs x 6: 128 against 170 us a batch; a handful of
+// spilled registers costs less), else one block.
+template <int NT, int LA, int MB> constexpr int cycles_waves() { return MB == 16 || LA * NT <= 24 ? 4 : 2; }
 template <int NT, int LA, int MB, typename VT, bool ONE>
-__global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(MB / 4))) void k_cycles(CycArgs a, int len) {
+__global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_waves<NT, LA, MB>()))) void k_cycles(CycArgs a, int len) {
     constexpr int NM = NT * NT, E = LA * NT;
     constexpr int KB = E < 12 ? E : 12;         // rows per transposition
     constexpr int PITCH = 72;                   // 64 lanes, padded against bank conflicts of the eight modes
@@ -199,13 +218,22 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(MB / 4)
                 if (e0 + k < ce) p[(e0 + k) * a.Nx] = (VT)tile[k][cw][cg];
         }
     };
-    read(a.rin, [&](int e, double v) { r[e / NT][e % NT] = v; });
+    // a residual between two batches stays by time lines: whole lanes in
+    // order, no transposition (S is a multiple of LA there)
+    const int lanes = (int)(a.S / LA);
+    if (a.rin_lines) {
+        const VT* p = static_cast<const VT*>(a.rin) + mode * E * lanes + min(lane, lanes - 1);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const double v = (double)p[e * lanes];
+            r[e / NT][e % NT] = lane < lanes ? v : 0.0;
+        }
+    } else {
+        read(a.rin, [&](int e, double v) { r[e / NT][e % NT] = v; });
+    }
 
     // value of the previous lane (0 for the first)
-    auto prev = [&](double v) {
-        const double x = __shfl_up(v, 1);
-        return lane > 0 ? x : 0.0;
-    };
+    auto prev = [&](double v) { return dpp<kDppWaveShr1, 0xf>(v); };
     // exact solve of a level over NS slabs per lane, in place: u_s = a_s +
     // x_{s-1} A^{-1} e_1 with a_s = A^{-1} f_s, the scalars x over the lanes by
     // a prefix sum with the constant factor gamma^NS
@@ -228,12 +256,24 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(MB / 4)
             y = z[j][NT - 1] + gamma * y;
             G *= gamma;
         }
-#pragma unroll
-        for (int d = 1; d < 64; d *= 2) {
-            const double t = __shfl_up(y, d);
-            if (lane >= d) y += G * t;
-            G *= G;
-        }
+        // within rows of 16 lanes, then row 0 into 1 and 2 into 3, then the
+        // first half into the second, with the power of the factor between
+        double w = G;
+        y += G * dpp<kDppRowShr + 1, 0xf>(y);
+        w *= lane & 1 ? G : 1.0;
+        G *= G;
+        y += G * dpp<kDppRowShr + 2, 0xf>(y);
+        w *= lane & 2 ? G : 1.0;
+        G *= G;
+        y += G * dpp<kDppRowShr + 4, 0xf>(y);
+        w *= lane & 4 ? G : 1.0;
+        G *= G;
+        y += G * dpp<kDppRowShr + 8, 0xf>(y);
+        w *= lane & 8 ? G : 1.0;
+        G *= G;
+        y += w * dpp<kDppRowBcast15, 0xa>(y);
+        w *= lane & 16 ? G : 1.0;
+        y += w * dpp<kDppRowBcast31, 0xc>(y);
         double x = prev(y);
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
@@ -352,10 +392,14 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(MB / 4)
             for (int t = 0; t < NT; ++t) q += r[i][t] * r[i][t];
             s2 += i < nv ? q : 0.0;
         }
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) s2 += __shfl_xor(s2, d);
+        s2 += dpp<kDppRowShr + 1, 0xf>(s2);
+        s2 += dpp<kDppRowShr + 2, 0xf>(s2);
+        s2 += dpp<kDppRowShr + 4, 0xf>(s2);
+        s2 += dpp<kDppRowShr + 8, 0xf>(s2);
+        s2 += dpp<kDppRowBcast15, 0xa>(s2);
+        s2 += dpp<kDppRowBcast31, 0xc>(s2);          // the total in the last lane
         if (m0 + wave >= a.Nx) s2 = 0.0;
-        if (lane == 0) {
+        if (lane == 63) {
             red[wave][c][0] = s2;
             const uptr w = mat(a.L + (ONE ? 1 : 2));
             red[wave][c][1] = w[0] * s2;
@@ -449,7 +493,14 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(MB / 4)
             sums(cyc + 1);
         }
     }
-    if (a.rout) write(a.rout, [&](int k) { return r[k / NT][k % NT]; });
+    if (a.rout && a.rout_lines) {
+        VT* p = static_cast<VT*>(a.rout) + mode * E * lanes + lane;
+        if (lane < lanes && m0 + wave < a.Nx)
+#pragma unroll
+            for (int e = 0; e < E; ++e) p[e * lanes] = (VT)r[e / NT][e % NT];
+    } else if (a.rout) {
+        write(a.rout, [&](int k) { return r[k / NT][k % NT]; });
+    }
     if (a.uout && (!ONE || a.m == 0)) {
         // the iterate of this residual: u^ = L^{-1}(f^ - r^)
         read(a.fh, [&](int e, double v) { r[e / NT][e % NT] = v - r[e / NT][e % NT]; });
@@ -566,14 +617,21 @@ static hipError_t cycles_launch(const CycArgs& a, int LA, long* blocks, hipStrea
     return hipErrorInvalidValue;
 }
 
+bool cycles_lines(int Nt, int L, long S) {
+    const int LA = cycles_lane_slabs(Nt, L, S);
+    return LA && L > 1 && S % LA == 0;
+}
+
 hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega, long S, int m,
                          const double* rin, const double* fh, double* rout, double* uout, double* partial,
-                         long max_partial, double* out_host, int* seq, int seq_val, hipStream_t st, int vt) {
+                         long max_partial, double* out_host, int* seq, int seq_val, hipStream_t st, int vt, bool rin_lines,
+                         bool rout_lines) {
     const int LA = cycles_lane_slabs(Nt, L, S);
     if (!LA || m < 0 || m > kMaxBatch || (L == 1 && m > 1)) return hipErrorInvalidValue;
     if (partial && 3L * (m + 1) * cycles_blocks(8, Nx) > max_partial) return hipErrorInvalidValue;
     if ((rout && rout == rin) || (uout && (uout == rin || uout == rout || uout == fh))) return hipErrorInvalidValue;
-    const CycArgs a{L, m, S, Nx, omega, tab, rin, fh, rout, uout, partial};
+    if ((rin_lines || rout_lines) && !cycles_lines(Nt, L, S)) return hipErrorInvalidValue;
+    const CycArgs a{L, m, rin_lines, rout_lines, S, Nx, omega, tab, rin, fh, rout, uout, partial};
     hipError_t e = hipErrorInvalidValue;
     long blocks = 0;
 #define STH_CYC_NT(NTV)                                                                            \

@@ -243,16 +243,20 @@ hipError_t launch_eig_coarse_tail3(int dim, int Nt, const TimeMix* tma_dev, cons
 //  entries, cycles_partials() suffice): sums 3 c .. 3 c + 2 of out_host
 //  (mapped pinned host memory) are ||r||^2 and its lower and upper
 //  mode-weighted forms after c = 0 .. m cycles; seq (may be null): after sum
-//  j, seq[j] = seq_val.  Vectors differ, except fh == rin.
+//  j, seq[j] = seq_val.  Vectors differ, except fh == rin.  rin_lines,
+//  rout_lines: that vector is by time lines, an order for the batches'
+//  residuals between them (where cycles_lines allows it, of the same length).
 constexpr int kMaxBatch = 8;
 bool cycles_supported(int Nt, int L, long S);
+bool cycles_lines(int Nt, int L, long S);
 long cycles_partials(long Nx);
 size_t cycles_table_len(int Nt, int L, long Nx);
 hipError_t launch_cycles_table(int dim, int Nt, int L, const TimeMix* tm, const double* ktmt, const double* mu1, int n,
                                long Nx, const Transfer& tr, const double* vw, double* tab, hipStream_t st);
 hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega, long S, int m,
                          const double* rin, const double* fh, double* rout, double* uout, double* partial,
-                         long max_partial, double* out_host, int* seq, int seq_val, hipStream_t st, int vt = 0);
+                         long max_partial, double* out_host, int* seq, int seq_val, hipStream_t st, int vt = 0,
+                         bool rin_lines = false, bool rout_lines = false);
 //  rh = fh - L uh
 hipError_t launch_eig_residual(int dim, int Nt, const double* ktmt, const double* mu1, int n, const double* fh,
                                const double* uh, double* rh, long S, hipStream_t st);

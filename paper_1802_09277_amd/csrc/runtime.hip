@@ -92,6 +92,7 @@ struct sth_handle {
     // whole cycles on chip (launch_cycles): the eigenbasis solve runs batches
     // of cycles on the residual
     bool cyc = false;
+    bool pad_dirty = false;             // a vector by time lines has run over the zeros of padded modes
     bool batches = false;               // ... and so do solves of the coefficient iteration
     double* cyc_tab = nullptr;          // per mode: its matrices on every level (launch_cycles_table)
     double* hcyc = nullptr;             // mapped, coherent: the sums of a batch
@@ -244,6 +245,7 @@ struct sth_handle {
         int start = -1, end = 0, uout = -2, m = 0;
         int known = 0;                  // cycles of the batch whose sums have been tested already
         bool first = true;
+        bool start_lines = false;       // the first residual is by time lines (cyc_lines)
         bool nonzero = false;           // the initial guess has a nonzero entry
         bool inner = false;
         bool inner_store = false;       // the inner result is stored into u (u was zero), not added
@@ -2080,6 +2082,11 @@ static int solve_begin_impl(sth_handle* h, const double* f, double* u, double rt
         const long rows = h->lev_S[0] * h->Nt;
         h->ecur[0] = 0;
         h->unformed = sth_handle::Unformed{};
+        if (h->pad_dirty) {
+            for (double* v : {h->e1, h->e2, h->e3})
+                if (v) HIPCHK(launch_fill(v, h->lev_S[0] * eslab_len(h), 0.0, st, nullptr, h->f32));
+            h->pad_dirty = false;
+        }
         // (FP32 eigenbasis vectors: only in inner solves, whose f is the
         // outer residual in buf1 or the caller's f; a 3-D forward transform
         // into float data uses buf1 as its second work vector after its
@@ -2442,18 +2449,27 @@ static int cyc_free(const sth_handle* h, int a, int b, bool residual) {
     return -2;
 }
 
+// Residuals from one batch to the next by time lines: read and written in
+// order, where the transposition to rows of modes moves pieces of 64 bytes
+// (a batch of 8 cycles on 65536 modes x 1024 slabs x 3: 1.77 -> 1.31 ms, one
+// of 2: 1.74 -> 1.27 ms).  Not in the coefficient iteration, where the exact
+// norm at the end of every solve reads them by rows.
+static bool cyc_lines(const sth_handle* h) { return h->basis == 1 && cycles_lines(h->Nt, h->L, h->lev_S[0]); }
+
 // m cycles from buffer `from`; end / uout < -1: not stored; sums: the norms of
 // every cycle to the host
-static int cyc_launch(sth_handle* h, int from, int end, int uout, int m, bool sums) {
+static int cyc_launch(sth_handle* h, int from, bool from_lines, int end, bool end_lines, int uout, int m, bool sums) {
     auto& v = h->sv;
     h->tlev = 0;
     const double dof = (double)h->lev_S[0] * slab_len(h), eb = h->f32 ? 4.0 : 8.0;
     if (sums && h->want_poll) ++h->seq_counter;
+    if (end_lines) h->pad_dirty = h->Nxe != h->Nx;
     Timed tm(h, STH_K_EIG_CYCLE_CLOSE, dof * (m * (9.4 * h->Nt + 19.0) + (uout >= 0 ? 4.0 * h->Nt : 0.0)),
              dof * eb * (1.0 + (end >= 0 ? 1.0 : 0.0) + (uout >= 0 ? (from < 0 ? 1.0 : 2.0) : 0.0)), v.st);
     HIPCHK(launch_cycles(h->Nt, h->L, h->cyc_tab, h->Nxe, h->omega, h->lev_S[0], m, cyc_buf(h, from), h->e0,
                          end >= 0 ? cyc_buf(h, end) : nullptr, uout >= 0 ? cyc_buf(h, uout) : nullptr,
-                         sums ? h->cpartial : nullptr, h->n_cpartial, h->hcyc_dev, sums && h->want_poll ? h->hcseq_dev : nullptr, h->seq_counter, v.st, h->f32));
+                         sums ? h->cpartial : nullptr, h->n_cpartial, h->hcyc_dev, sums && h->want_poll ? h->hcseq_dev : nullptr, h->seq_counter, v.st, h->f32,
+                         from_lines, end_lines));
     h->wait_ev = nullptr;
     h->wait_slot = -1;
     h->wait_cyc = sums && h->want_poll ? 3 * (m + 1) : 0;
@@ -2465,18 +2481,19 @@ static int cyc_launch(sth_handle* h, int from, int end, int uout, int m, bool su
 // stopping test has seen (a batch taken again because its residual was not
 // stored).  last: the stopping cycle is expected in it, so the iterate is
 // formed with it, and with at most two cycles to go its residual is not stored.
-static int cyc_batch(sth_handle* h, int from, int want, int known, bool last) {
+static int cyc_batch(sth_handle* h, int from, bool from_lines, int want, int known, bool last) {
     auto& v = h->sv;
     v.m = std::max(0, std::min({want, h->L == 1 ? 1 : kMaxBatch, v.maxit - v.it + known}));
     if (!h->speculate) v.m = std::min(v.m, known + 1);
     v.start = from;
+    v.start_lines = from_lines;
     v.known = known;
     v.end = cyc_free(h, from, -2, true);
     // (one level: the cycle's own result is the iterate after the first cycle only)
     v.uout = (last && v.m > 0 && (h->L > 1 || from < 0)) ? cyc_free(h, from, v.end, false) : -2;
     if (v.uout >= 0 && h->L > 1 && v.m - known <= 2 && v.m <= kMaxBatch - 2) v.end = -2;
     v.phase = 10;
-    return cyc_launch(h, v.start, v.end, v.uout, v.m, true);
+    return cyc_launch(h, from, from_lines, v.end, cyc_lines(h), v.uout, v.m, true);
 }
 
 // the result after j cycles of the current batch
@@ -2492,10 +2509,12 @@ static int cyc_finish(sth_handle* h, int j, bool* more) {
     }
     int u = v.uout;
     if (u < 0 || j != v.m) {
-        const int from = j == v.m && j > 0 && v.end >= 0 ? v.end : v.start;
+        const bool stored = j == v.m && j > 0 && v.end >= 0;
+        const int from = stored ? v.end : v.start;
         u = cyc_free(h, from, -2, false);
         int rc;
-        if ((rc = cyc_launch(h, from, -2, u, from == v.start ? j : 0, false))) return rc;
+        if ((rc = cyc_launch(h, from, stored ? cyc_lines(h) : v.start_lines, -2, false, u, stored ? 0 : j, false)))
+            return rc;
     }
     h->wait_cyc = 0;                    // (a launch above sets it)
     const bool add = v.inner ? !v.inner_store : v.nonzero;
@@ -2507,16 +2526,18 @@ static int cyc_finish(sth_handle* h, int j, bool* more) {
 // which becomes the (empty) current batch
 static int cyc_exact(sth_handle* h, int j) {
     auto& v = h->sv;
-    int at = v.start, rc;
-    if (j > 0) {
-        const bool stored = j == v.m && v.end >= 0;
-        if (!(v.uout >= 0 && j == v.m)) v.uout = -2;
-        at = v.end >= 0 ? v.end : cyc_free(h, v.start, v.uout, true);
-        if (!stored && (rc = cyc_launch(h, v.start, at, -2, j, false))) return rc;
-    } else {
-        v.uout = -2;
+    // its residual, by rows of modes
+    const bool stored = j == v.m && j > 0 && v.end >= 0;
+    int at = stored ? v.end : v.start, rc;
+    bool lines = stored ? cyc_lines(h) : v.start_lines;
+    if (!(v.uout >= 0 && j == v.m && j > 0)) v.uout = -2;
+    if (lines || (j > 0 && !stored)) {
+        const int to = cyc_free(h, at, v.uout, true);
+        if ((rc = cyc_launch(h, at, lines, to, false, -2, stored ? 0 : j, false))) return rc;
+        at = to;
     }
     v.start = v.end = at;
+    v.start_lines = false;
     v.m = 0;
     v.phase = 11;
     h->wait_cyc = 0;
@@ -2562,7 +2583,7 @@ static int cyc_begin(sth_handle* h, const double* inner_fn) {
         if ((rc = spatial_apply(h, FWD_U, h->buf1, h->e0, rows, h->buf0, v.st, nz))) return rc;
     }
     v.first = true;
-    return cyc_batch(h, -1, first_batch(v.rtol), 0, h->L == 1);
+    return cyc_batch(h, -1, false, first_batch(v.rtol), 0, h->L == 1);
 }
 
 static int cyc_continue(sth_handle* h, bool* more) {
@@ -2576,7 +2597,7 @@ static int cyc_continue(sth_handle* h, bool* more) {
         if (!(v.rn > target()) || !std::isfinite(v.rn) || v.it >= v.maxit || v.growth >= 3) {
             return cyc_finish(h, 0, more);            // (the current batch is empty)
         }
-        return cyc_batch(h, v.start, 1, 0, true);
+        return cyc_batch(h, v.start, false, 1, 0, true);
     }
     const double* q = h->hcyc;
     int j = 0;
@@ -2630,8 +2651,8 @@ static int cyc_continue(sth_handle* h, bool* more) {
     const bool large = (double)h->lev_S[0] * slab_len(h) > 4e6;
     const bool last = want <= (large ? 2 : kMaxBatch);
     if (!last && large) want = std::max(1, want - 2);
-    if (v.end >= 0) return cyc_batch(h, v.end, want, 0, last);
-    return cyc_batch(h, v.start, v.m + want, v.m, last);
+    if (v.end >= 0) return cyc_batch(h, v.end, cyc_lines(h), want, 0, last);
+    return cyc_batch(h, v.start, v.start_lines, v.m + want, v.m, last);
 }
 
 // Once the work enqueued by the previous call has completed: read the
