@@ -1,10 +1,9 @@
 // gfx950 kernels of the space-time slab solver: the spatial eigenbasis
 // transforms of 2-D images with the whole image in LDS (eq.
 // equ:ST:generalDecompA with fast diagonalisation of K_x + lambda M_x), in
-// FP64, FP32 and BF16x3 MFMA, and the exact B-spline residual norm of an
+// FP32 and BF16x3 MFMA, and the exact B-spline residual norm of an
 // eigenbasis vector through the Gram matrix G = C^T C.
 #include <atomic>
-#include <type_traits>
 
 #include "kernels_common.hpp"
 
@@ -16,10 +15,12 @@ namespace sth {
 // out = U^T R U.  DIR 1 (inverse): Z = U Y U^T, then the epilogue EPI
 // (0 store, 1 out += alpha Z, 2 out = alpha Z).  Eight waves share the
 // NT16 x NT16 output tiles of each GEMM; the intermediate product goes back
-// into the image buffer.  CT is the compute type: double (MFMA f64 16x16x4)
-// or float (MFMA f32 16x16x4, FP32 accumulation); global data stay FP64.
+// into the image buffer.  MFMA f32 16x16x4, FP32 accumulation; FP64 or FP32
+// global data.
 // ---------------------------------------------------------------------------
-template <typename CT, int DIR, int NT16, int EPI, bool CORE, typename TI, typename TO>
+typedef float CT;                               // compute type
+
+template <int DIR, int NT16, int EPI, bool CORE, typename TI, typename TO>
 __global__ __launch_bounds__(512) void k_xform2d(const TI* __restrict__ in, TO* __restrict__ out,
                                                  const double* __restrict__ Upad, int n, long nimg,
                                                  double alpha, const int* guard, long ldi, long ldo) {
@@ -177,26 +178,26 @@ __global__ __launch_bounds__(512) void k_xform2d(const TI* __restrict__ in, TO* 
         if (edge && epart == 0) put(ei, ej, e);
     }
 }
-template <typename CT, int DIR, int NT16, int EPI, bool CORE, typename TI, typename TO>
+template <int DIR, int NT16, int EPI, bool CORE, typename TI, typename TO>
 static hipError_t xform2d_go(const TI* in, TO* out, const double* Upad, int n, long nimg, double alpha,
                              hipStream_t st, long* nblocks, const int* guard, long ldi, long ldo) {
     size_t shm = sizeof(CT) * 2 * (size_t)TileLds<CT, NT16>::SIZE;
     static std::atomic<bool> attr_set{false};       // set once; the attribute call is idempotent
     if (!attr_set.load(std::memory_order_acquire)) {
         // exactly the dynamic size: the block-wide vote holds a little static LDS
-        hipError_t e = hipFuncSetAttribute((const void*)k_xform2d<CT, DIR, NT16, EPI, CORE, TI, TO>,
+        hipError_t e = hipFuncSetAttribute((const void*)k_xform2d<DIR, NT16, EPI, CORE, TI, TO>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
         if (e != hipSuccess) return e;
         attr_set.store(true, std::memory_order_release);
     }
     long blocks = persistent_blocks(shm, nimg);
     if (nblocks) *nblocks = blocks;
-    hipLaunchKernelGGL((k_xform2d<CT, DIR, NT16, EPI, CORE, TI, TO>), dim3((unsigned)blocks), dim3(512), shm, st, in, out,
+    hipLaunchKernelGGL((k_xform2d<DIR, NT16, EPI, CORE, TI, TO>), dim3((unsigned)blocks), dim3(512), shm, st, in, out,
                        Upad, n, nimg, alpha, guard, ldi, ldo);
     return hipGetLastError();
 }
 
-template <typename CT, int DIR, int NT16, int EPI, typename TI, typename TO>
+template <int DIR, int NT16, int EPI, typename TI, typename TO>
 static hipError_t xform2d_launch(const TI* in, TO* out, const double* Upad, int n, long nimg, double alpha,
                                  hipStream_t st, long* nblocks = nullptr, const int* guard = nullptr,
                                  long ldi = 0, long ldo = 0) {
@@ -206,49 +207,47 @@ static hipError_t xform2d_launch(const TI* in, TO* out, const double* Upad, int 
     if (ldi < (long)n * n || ldo < (long)n * n) return hipErrorInvalidValue;
     if constexpr (kXform2dEdge<NT16>) {
         if (xform2d_core_tiles<NT16>(n) < NT16)
-            return xform2d_go<CT, DIR, NT16, EPI, true, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
+            return xform2d_go<DIR, NT16, EPI, true, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
     }
-    return xform2d_go<CT, DIR, NT16, EPI, false, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
+    return xform2d_go<DIR, NT16, EPI, false, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
 }
 
-template <typename CT, int DIR, int EPI, typename TI = double, typename TO = double>
+template <int DIR, int EPI, typename TI = double, typename TO = double>
 static hipError_t xform2d_np(const TI* in, TO* out, const double* Upad, int n, int np, long nimg,
                              double alpha, hipStream_t st, long* nblocks = nullptr, const int* guard = nullptr,
                              long ldi = 0, long ldo = 0) {
     switch (np / 16) {
-        case 1: return xform2d_launch<CT, DIR, 1, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
-        case 2: return xform2d_launch<CT, DIR, 2, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
-        case 3: return xform2d_launch<CT, DIR, 3, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
-        case 4: return xform2d_launch<CT, DIR, 4, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
-        case 5: return xform2d_launch<CT, DIR, 5, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
-        case 6: return xform2d_launch<CT, DIR, 6, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
+        case 1: return xform2d_launch<DIR, 1, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
+        case 2: return xform2d_launch<DIR, 2, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
+        case 3: return xform2d_launch<DIR, 3, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
+        case 4: return xform2d_launch<DIR, 4, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
+        case 5: return xform2d_launch<DIR, 5, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
+        case 6: return xform2d_launch<DIR, 6, EPI, TI, TO>(in, out, Upad, n, nimg, alpha, st, nblocks, guard, ldi, ldo);
         default: return hipErrorInvalidValue;
     }
 }
 
-template <typename CT>
-static hipError_t xform2d_prec(int dir, int epi, const double* in, double* out, const double* Upad, int n, int np,
+static hipError_t xform2d_f32(int dir, int epi, const double* in, double* out, const double* Upad, int n, int np,
                                long nimg, double alpha, hipStream_t st, const int* guard, long ldi, long ldo,
                                int io_f32) {
     if (io_f32) {
-        // FP32 eigenbasis vectors (FP32 transforms only): the forward
+        // FP32 eigenbasis vectors: the forward
         // transform writes them, the inverse reads them
-        if (!std::is_same<CT, float>::value) return hipErrorInvalidValue;
         if (dir == 0 && io_f32 == 2)
-            return xform2d_np<CT, 0, 0, double, float>(in, (float*)out, Upad, n, np, nimg, 1.0, st, nullptr, guard,
+            return xform2d_np<0, 0, double, float>(in, (float*)out, Upad, n, np, nimg, 1.0, st, nullptr, guard,
                                                        ldi, ldo);
         if (dir == 1 && io_f32 == 1 && epi == 0)
-            return xform2d_np<CT, 1, 0, float, double>((const float*)in, out, Upad, n, np, nimg, alpha, st, nullptr,
+            return xform2d_np<1, 0, float, double>((const float*)in, out, Upad, n, np, nimg, alpha, st, nullptr,
                                                        guard, ldi, ldo);
         if (dir == 1 && io_f32 == 1 && epi == 1)
-            return xform2d_np<CT, 1, 1, float, double>((const float*)in, out, Upad, n, np, nimg, alpha, st, nullptr,
+            return xform2d_np<1, 1, float, double>((const float*)in, out, Upad, n, np, nimg, alpha, st, nullptr,
                                                        guard, ldi, ldo);
         return hipErrorInvalidValue;
     }
-    if (dir == 0) return xform2d_np<CT, 0, 0>(in, out, Upad, n, np, nimg, 1.0, st, nullptr, guard, ldi, ldo);
-    if (epi == 0) return xform2d_np<CT, 1, 0>(in, out, Upad, n, np, nimg, alpha, st, nullptr, guard, ldi, ldo);
-    if (epi == 1) return xform2d_np<CT, 1, 1>(in, out, Upad, n, np, nimg, alpha, st, nullptr, guard, ldi, ldo);
-    if (epi == 2) return xform2d_np<CT, 1, 2>(in, out, Upad, n, np, nimg, alpha, st, nullptr, guard, ldi, ldo);
+    if (dir == 0) return xform2d_np<0, 0>(in, out, Upad, n, np, nimg, 1.0, st, nullptr, guard, ldi, ldo);
+    if (epi == 0) return xform2d_np<1, 0>(in, out, Upad, n, np, nimg, alpha, st, nullptr, guard, ldi, ldo);
+    if (epi == 1) return xform2d_np<1, 1>(in, out, Upad, n, np, nimg, alpha, st, nullptr, guard, ldi, ldo);
+    if (epi == 2) return xform2d_np<1, 2>(in, out, Upad, n, np, nimg, alpha, st, nullptr, guard, ldi, ldo);
     return hipErrorInvalidValue;
 }
 template <int NT16, int EPI, typename TI, typename TO>
@@ -582,10 +581,8 @@ hipError_t launch_xform2d(int prec, int dir, int epi, const double* in, double* 
                           int io_f32) {
     if (nimg <= 0) return hipSuccess;
     if (!xform2d_supported(np)) return hipErrorInvalidValue;
-    if (prec == 0)
-        return xform2d_prec<double>(dir, epi, in, out, Upad, n, np, nimg, alpha, st, guard, ldi, ldo, io_f32);
     if (prec == 1)
-        return xform2d_prec<float>(dir, epi, in, out, Upad, n, np, nimg, alpha, st, guard, ldi, ldo, io_f32);
+        return xform2d_f32(dir, epi, in, out, Upad, n, np, nimg, alpha, st, guard, ldi, ldo, io_f32);
     return hipErrorInvalidValue;
 }
 

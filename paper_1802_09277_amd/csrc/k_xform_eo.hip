@@ -401,6 +401,8 @@ static hipError_t eo_launch(EoArgs a, hipStream_t st) {
 #undef STH_EO_CASE
 }
 
+int xform_eo_rows(int n) { return eo_rows(n); }
+
 size_t xform_eo_pack_len(int n) {
     bool rem;
     return xform_eo_supported(n) ? (size_t)eo_rows(n) * (32 * eo_tiles(n, &rem) + 2) : 0;

@@ -104,6 +104,13 @@ constexpr int kEoMaxN = 1024;
 bool xform_eo_supported(int n);
 bool xform_eo_s_supported(int n, long inner);   // also the lane offsets fit 32 bits
 size_t xform_eo_pack_len(int n);
+int xform_eo_rows(int n);               // rows of a packed column tile
+//  Both axes of nimg n x n images (n <= 96) at strides ldi, ldo (0: n^2):
+//  out = T^T in T of the packed forward panels, or its inverse with the
+//  epilogue epi; in and out differ.
+bool xform2d_eo_supported(int n);
+hipError_t launch_xform2d_eo(bool inv, int epi, const double* in, double* out, const double* T, int n, long nimg,
+                             double alpha, hipStream_t st, const int* guard = nullptr, long ldi = 0, long ldo = 0);
 void xform_eo_pack(bool inv, const double* A, int n, int lda, double* out);
 hipError_t launch_xform_eo_x(bool inv, int epi, const double* in, double* out, const double* T, int n, long lines,
                              double alpha, hipStream_t st, const int* guard = nullptr);
@@ -118,8 +125,8 @@ bool xform_panel_f32_io(int np);
 // Both spatial axes of 2-D images (n x n each, nimg images, image i at
 // in + i ldi and out + i ldo; 0: n^2) in one kernel:
 // dir 0: out = U^T R U; dir 1: Z = U Y U^T with epilogue epi (0 store,
-// 1 out += alpha Z, 2 out = alpha Z).  Upad is U padded to np x np; prec 0
-// computes in FP64 (MFMA f64), 1 in FP32 (MFMA f32, FP32 accumulation).
+// 1 out += alpha Z, 2 out = alpha Z).  Upad is U padded to np x np; prec 1
+// (MFMA f32, FP32 accumulation); FP64: launch_xform2d_eo.
 constexpr int kXform2dMaxNp = 96;
 bool xform2d_supported(int np);
 // Spatial modes per time row of an eigenbasis vector: n^d, padded to a

@@ -400,6 +400,16 @@ static int xform_s(sth_handle* h, int prec, const double* in, double* out, const
     return STH_OK;
 }
 
+// both axes of 2-D images in one kernel, with the padded forward matrix A
+static hipError_t xform2d(sth_handle* h, int prec, bool fwd, int epi, const double* in, double* out, const double* A,
+                          long rows, double alpha, hipStream_t st, const int* guard = nullptr, long ldi = 0,
+                          long ldo = 0, int io_f32 = 0) {
+    if (prec == STH_FP64 && !io_f32)
+        return launch_xform2d_eo(!fwd, epi, in, out, h->eo[(A == h->Tf ? 0 : 2) + (fwd ? 0 : 1)], h->n, rows, alpha,
+                                 st, guard, ldi, ldo);
+    return launch_xform2d(prec, fwd ? 0 : 1, epi, in, out, A, h->n, h->np, rows, alpha, st, guard, ldi, ldo, io_f32);
+}
+
 // u (mode 1: +=, 2: =) omega * D^{-1} in, on slabs [s0, s0+ns) of level lvl.
 // `in` may alias buf1 but not buf0.
 static int slab_inverse(sth_handle* h, int lvl, const double* in, double* u, int epi, double alpha, long s0,
@@ -420,7 +430,7 @@ static int slab_inverse(sth_handle* h, int lvl, const double* in, double* u, int
             if (h->prec == STH_BF16X3)
                 HIPCHK(launch_xform2d_bf16x3(0, in, b0, h->Ti, h->n, h->np, rows, 1.0, st));
             else
-                HIPCHK(launch_xform2d(h->prec, 0, 0, in, b0, h->Tf, h->n, h->np, rows, 1.0, st));
+                HIPCHK(xform2d(h, h->prec, true, 0, in, b0, h->Tf, rows, 1.0, st));
         }
         {
             Timed tm(h, STH_K_TIMEMIX, dof * (4.0 * h->Nt + 4.0), 16.0 * dof, st);
@@ -431,7 +441,7 @@ static int slab_inverse(sth_handle* h, int lvl, const double* in, double* u, int
             if (h->prec == STH_BF16X3)
                 HIPCHK(launch_xform2d_bf16x3(epi, b1, u, h->Tf, h->n, h->np, rows, alpha, st));
             else
-                HIPCHK(launch_xform2d(h->prec, 1, epi, b1, u, h->Tf, h->n, h->np, rows, alpha, st));
+                HIPCHK(xform2d(h, h->prec, false, epi, b1, u, h->Tf, rows, alpha, st));
         }
     } else if (h->dim == 2) {
         const int pr = h->prec;
@@ -482,14 +492,14 @@ static int pinv_apply(sth_handle* h, int lvl, const double* in, double* out, lon
             if (h->prec == STH_BF16X3)
                 HIPCHK(launch_xform2d_bf16x3(0, in, b0, h->Ti, h->n, h->np, rows, 1.0, st));
             else
-                HIPCHK(launch_xform2d(h->prec, 0, 0, in, b0, h->Tf, h->n, h->np, rows, 1.0, st));
+                HIPCHK(xform2d(h, h->prec, true, 0, in, b0, h->Tf, rows, 1.0, st));
         }
         if ((rc = scale(b0))) return rc;
         Timed tm(h, STH_K_XFORM_2D, 4.0 * h->n * dof, 16.0 * dof, st);
         if (h->prec == STH_BF16X3)
             HIPCHK(launch_xform2d_bf16x3(0, b0, out, h->Tf, h->n, h->np, rows, 1.0, st));
         else
-            HIPCHK(launch_xform2d(h->prec, 1, 0, b0, out, h->Tf, h->n, h->np, rows, 1.0, st));
+            HIPCHK(xform2d(h, h->prec, false, 0, b0, out, h->Tf, rows, 1.0, st));
     } else if (h->dim == 2) {
         const int pr = h->prec;
         if ((rc = xform_x(h, pr, 0, in, b0, h->Tf, rows * n, 1.0, st))) return rc;
@@ -775,8 +785,7 @@ static int spatial_apply(sth_handle* h, SpatialKind kind, const double* in, doub
             HIPCHK(launch_xform2d_bf16x3(epi, in, out, fwd ? At : A, h->n, h->np, rows, 1.0, st, guard,
                                          fwd ? 0 : ld, fwd ? ld : 0, io_f32));
         else
-            HIPCHK(launch_xform2d(prec, fwd ? 0 : 1, epi, in, out, A, h->n, h->np, rows, 1.0, st, guard,
-                                  fwd ? 0 : ld, fwd ? ld : 0, io_f32));
+            HIPCHK(xform2d(h, prec, fwd, epi, in, out, A, rows, 1.0, st, guard, fwd ? 0 : ld, fwd ? ld : 0, io_f32));
         return STH_OK;
     }
     // axis by axis, ping-ponging between the buffers; with accumulation (or

@@ -45,6 +45,23 @@ def _slab_inverse(prob, r):
     (2, 256, 2, 20, 1), (2, 257, 3, 20, 1), (2, 258, 4, 1, 2), (2, 300, 2, 1, 1),
 ])
 def test_slab_inverse_and_update(dim, n, degree, n_slabs, n_elem_t):
+    _check(dim, n, degree, n_slabs, n_elem_t)
+
+
+# both axes of an image at once: halves below, at and above the tiles of 16
+# rows and columns, odd and even n, one image to more than the card holds, odd
+# counts of images
+@pytest.mark.parametrize("n,degree,n_slabs,n_elem_t", [
+    (1, 1, 1, 1), (2, 2, 1, 1), (3, 1, 2, 1), (4, 2, 3, 2), (15, 2, 2, 1), (16, 2, 16, 2), (17, 3, 1, 2), (20, 2, 700, 1),
+    (29, 1, 3, 2), (31, 2, 1, 1), (32, 2, 9, 1), (33, 3, 5, 1), (34, 4, 1, 2), (35, 2, 3, 1), (36, 1, 2, 2), (40, 2, 24, 2),
+    (47, 1, 3, 1), (61, 3, 7, 2), (62, 4, 2, 1), (63, 2, 3, 1), (64, 2, 300, 1), (65, 3, 260, 2), (66, 4, 3, 1), (67, 2, 1, 1),
+    (79, 1, 3, 2), (80, 2, 2, 1), (81, 3, 1, 1), (94, 2, 2, 1), (95, 1, 2, 1), (96, 2, 130, 1),
+])
+def test_slab_inverse_and_update_images(n, degree, n_slabs, n_elem_t):
+    _check(2, n, degree, n_slabs, n_elem_t)
+
+
+def _check(dim, n, degree, n_slabs, n_elem_t):
     import paper_1802_09277_amd as sth
     prob = Problem(dim, n + 2 - degree, degree, n_slabs, n_elem_t)
     assert prob.n == n
