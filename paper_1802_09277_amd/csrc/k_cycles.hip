@@ -47,6 +47,7 @@ namespace sth {
 
 struct CycArgs {
     int L, m;
+    int steps;                  // damped block-Jacobi steps instead of cycles (ONE, m = 0)
     int rin_lines, rout_lines;  // residual by time lines: [mode][row of a lane][lane]
     long S, Nx;
     double omega;
@@ -122,16 +123,6 @@ __global__ __launch_bounds__(256) void k_mode_table(int dim, int n, int L, long 
 
 // wave-uniform tables: scalar loads
 typedef const __attribute__((address_space(4))) double* uptr;
-
-// A double from another lane of the wave by data-parallel primitives (no trip
-// through LDS): lanes without a source, or in rows outside the mask, get 0.
-constexpr int kDppRowShr = 0x110, kDppWaveShr1 = 0x138, kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
-template <int CTRL, int ROWS> __device__ __forceinline__ double dpp(double v) {
-    const long b = __builtin_bit_cast(long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
-    return __builtin_bit_cast(double, (long)(unsigned)lo | (long)hi << 32);
-}
 
 // ONE: a single level.  A cycle is the exact solve e = L^{-1} r, whose result
 // goes to uout, and r becomes its residual r - L e (m = 1).
@@ -233,7 +224,7 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_
     }
 
     // value of the previous lane (0 for the first)
-    auto prev = [&](double v) { return dpp<kDppWaveShr1, 0xf>(v); };
+    auto prev = [&](double v) { return wave_dpp<kDppWaveShr1, 0xf>(v); };
     // exact solve of a level over NS slabs per lane, in place: u_s = a_s +
     // x_{s-1} A^{-1} e_1 with a_s = A^{-1} f_s, the scalars x over the lanes by
     // a prefix sum with the constant factor gamma^NS
@@ -259,21 +250,21 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_
         // within rows of 16 lanes, then row 0 into 1 and 2 into 3, then the
         // first half into the second, with the power of the factor between
         double w = G;
-        y += G * dpp<kDppRowShr + 1, 0xf>(y);
+        y += G * wave_dpp<kDppRowShr + 1, 0xf>(y);
         w *= lane & 1 ? G : 1.0;
         G *= G;
-        y += G * dpp<kDppRowShr + 2, 0xf>(y);
+        y += G * wave_dpp<kDppRowShr + 2, 0xf>(y);
         w *= lane & 2 ? G : 1.0;
         G *= G;
-        y += G * dpp<kDppRowShr + 4, 0xf>(y);
+        y += G * wave_dpp<kDppRowShr + 4, 0xf>(y);
         w *= lane & 4 ? G : 1.0;
         G *= G;
-        y += G * dpp<kDppRowShr + 8, 0xf>(y);
+        y += G * wave_dpp<kDppRowShr + 8, 0xf>(y);
         w *= lane & 8 ? G : 1.0;
         G *= G;
-        y += w * dpp<kDppRowBcast15, 0xa>(y);
+        y += w * wave_dpp<kDppRowBcast15, 0xa>(y);
         w *= lane & 16 ? G : 1.0;
-        y += w * dpp<kDppRowBcast31, 0xc>(y);
+        y += w * wave_dpp<kDppRowBcast31, 0xc>(y);
         double x = prev(y);
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
@@ -392,12 +383,12 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_
             for (int t = 0; t < NT; ++t) q += r[i][t] * r[i][t];
             s2 += i < nv ? q : 0.0;
         }
-        s2 += dpp<kDppRowShr + 1, 0xf>(s2);
-        s2 += dpp<kDppRowShr + 2, 0xf>(s2);
-        s2 += dpp<kDppRowShr + 4, 0xf>(s2);
-        s2 += dpp<kDppRowShr + 8, 0xf>(s2);
-        s2 += dpp<kDppRowBcast15, 0xa>(s2);
-        s2 += dpp<kDppRowBcast31, 0xc>(s2);          // the total in the last lane
+        s2 += wave_dpp<kDppRowShr + 1, 0xf>(s2);
+        s2 += wave_dpp<kDppRowShr + 2, 0xf>(s2);
+        s2 += wave_dpp<kDppRowShr + 4, 0xf>(s2);
+        s2 += wave_dpp<kDppRowShr + 8, 0xf>(s2);
+        s2 += wave_dpp<kDppRowBcast15, 0xa>(s2);
+        s2 += wave_dpp<kDppRowBcast31, 0xc>(s2);          // the total in the last lane
         if (m0 + wave >= a.Nx) s2 = 0.0;
         if (lane == 63) {
             red[wave][c][0] = s2;
@@ -409,6 +400,8 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_
 
     sums(0);
     if constexpr (ONE) {
+#pragma unroll 1
+        for (int i = 0; i < a.steps; ++i) smooth();
         if (a.m > 0) {
             double e[LA][NT];
 #pragma unroll
@@ -592,7 +585,7 @@ static hipError_t cycles_go(const CycArgs& a, long* blocks, hipStream_t st) {
     *blocks = cycles_blocks(MB, a.Nx);
     const dim3 grid((unsigned)*blocks), block(64 * MB);
     if constexpr (LA > 1)
-        if (a.L > 1) {
+        if (a.L > 1 && !a.steps) {
             hipLaunchKernelGGL((k_cycles<NT, LA, MB, VT, false>), grid, block, 0, st, a, len);
             return hipGetLastError();
         }
@@ -617,6 +610,22 @@ static hipError_t cycles_launch(const CycArgs& a, int LA, long* blocks, hipStrea
     return hipErrorInvalidValue;
 }
 
+hipError_t launch_smoothing(int Nt, int L, const double* tab, long Nx, double omega, long S, int steps,
+                            const double* r, double* uout, hipStream_t st) {
+    const int LA = cycles_lane_slabs(Nt, L, S);
+    if (!LA || steps < 1 || r == uout) return hipErrorInvalidValue;
+    const CycArgs a{L, 0, steps, 0, 0, S, Nx, omega, tab, r, r, nullptr, uout, nullptr};
+    long blocks = 0;
+    switch (Nt) {
+        case 2: return cycles_launch<2, double>(a, LA, &blocks, st);
+        case 3: return cycles_launch<3, double>(a, LA, &blocks, st);
+        case 4: return cycles_launch<4, double>(a, LA, &blocks, st);
+        case 5: return cycles_launch<5, double>(a, LA, &blocks, st);
+        case 6: return cycles_launch<6, double>(a, LA, &blocks, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 bool cycles_lines(int Nt, int L, long S) {
     const int LA = cycles_lane_slabs(Nt, L, S);
     return LA && L > 1 && S % LA == 0;
@@ -631,7 +640,7 @@ hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega
     if (partial && 3L * (m + 1) * cycles_blocks(8, Nx) > max_partial) return hipErrorInvalidValue;
     if ((rout && rout == rin) || (uout && (uout == rin || uout == rout || uout == fh))) return hipErrorInvalidValue;
     if ((rin_lines || rout_lines) && !cycles_lines(Nt, L, S)) return hipErrorInvalidValue;
-    const CycArgs a{L, m, rin_lines, rout_lines, S, Nx, omega, tab, rin, fh, rout, uout, partial};
+    const CycArgs a{L, m, 0, rin_lines, rout_lines, S, Nx, omega, tab, rin, fh, rout, uout, partial};
     hipError_t e = hipErrorInvalidValue;
     long blocks = 0;
 #define STH_CYC_NT(NTV)                                                                            \

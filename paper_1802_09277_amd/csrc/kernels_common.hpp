@@ -39,6 +39,16 @@ template <> struct Mfma16<float> {
     }
 };
 
+// A double from another lane of the wave by data-parallel primitives (no trip
+// through LDS): lanes without a source, or in rows outside the mask, get 0.
+constexpr int kDppRowShr = 0x110, kDppWaveShl1 = 0x130, kDppWaveShr1 = 0x138, kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
+template <int CTRL, int ROWS> __device__ __forceinline__ double wave_dpp(double v) {
+    const long b = __builtin_bit_cast(long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, (long)(unsigned)lo | (long)hi << 32);
+}
+
 // Grid of a persistent image loop: as many 512-thread blocks as fit on the
 // 256 compute units at once (LDS-limited), at most one per image.
 static long persistent_blocks(size_t shm, long nimg) {

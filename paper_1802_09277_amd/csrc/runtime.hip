@@ -687,7 +687,8 @@ static int child_cycle(sth_handle* c, const double* f, double* u, hipStream_t st
     return vcycle_lvl(c, 0, f, u, true, st);
 }
 
-static int mode_cycle(sth_handle* h, const double* f, double* u, bool zero_guess, bool have_r, hipStream_t st);
+static int mode_cycle(sth_handle* h, const double* f, double* u, bool zero_guess, bool have_r, hipStream_t st,
+                      int steps = 0);
 
 static int vcycle_lvl(sth_handle* h, int lvl, const double* f, double* u, bool zero_guess, hipStream_t st) {
     if (lvl == 0 && h->basis == 0 && h->cyc) return mode_cycle(h, f, u, zero_guess, false, st);
@@ -828,7 +829,10 @@ static int spatial_apply(sth_handle* h, SpatialKind kind, const double* in, doub
 // two transforms and a residual for each smoothing step of each level (at 101
 // x 101 x 300 x 3 unknowns 1236 us, now 384).  From a zero guess r = f;
 // have_r: buf1 holds f - L u already.  buf0 and buf1 are the work vectors.
-static int mode_cycle(sth_handle* h, const double* f, double* u, bool zero_guess, bool have_r, hipStream_t st) {
+// steps > 0: that many smoothing steps instead of a cycle (two at 22^3 x 50 x
+// 4 unknowns 246 -> 127 us: the second residual and its transforms go).
+static int mode_cycle(sth_handle* h, const double* f, double* u, bool zero_guess, bool have_r, hipStream_t st,
+                      int steps) {
     const long S = h->lev_S[0], rows = S * h->Nt;
     int rc;
     if (!zero_guess && !have_r && (rc = residual(h, 0, f, u, h->buf1, 0, S, 1.0, st))) return rc;
@@ -837,7 +841,11 @@ static int mode_cycle(sth_handle* h, const double* f, double* u, bool zero_guess
     double* a = axes2 ? h->buf1 : h->buf0;
     double* b = axes2 ? h->buf0 : h->buf1;
     if ((rc = spatial_apply(h, FWD_U, zero_guess ? f : h->buf1, a, rows, b, st))) return rc;
-    {
+    if (steps > 0) {
+        const double dof = (double)S * slab_len(h);
+        Timed tm(h, STH_K_EIG_SMOOTH, dof * (4.0 * steps + 2.0 * h->Nt + 4.0), dof * 24.0, st);
+        HIPCHK(launch_smoothing(h->Nt, h->L, h->cyc_tab, h->Nxe, h->omega, S, steps, a, b, st));
+    } else {
         const double dof = (double)S * slab_len(h);
         Timed tm(h, STH_K_EIG_CYCLE_CLOSE, dof * (13.4 * h->Nt + 19.0), dof * 24.0, st);
         HIPCHK(launch_cycles(h->Nt, h->L, h->cyc_tab, h->Nxe, h->omega, S, 1, a, a, nullptr, b, nullptr, 0, nullptr,
@@ -1884,6 +1892,8 @@ int sth_block_solve(sth_handle* h, const double* r, double* z, void* stream) {
 
 int sth_smooth(sth_handle* h, const double* f, double* u, int steps, void* stream) {
     if (!h || !f || !u || steps < 0) return fail(STH_EINVAL, "bad argument");
+    // (one step: the slab inverse of the residual, the same transforms)
+    if (steps > 1 && h->basis == 0 && h->cyc) return mode_cycle(h, f, u, false, false, (hipStream_t)stream, steps);
     for (int i = 0; i < steps; ++i) {
         int rc = smooth_step(h, 0, f, u, false, (hipStream_t)stream);
         if (rc) return rc;

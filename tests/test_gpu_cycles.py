@@ -114,3 +114,17 @@ def test_coefficient_solve(shape):
     w = s.new_vector()
     s.solve_fgmres(f, w, rtol=1e-8, maxit=80)
     assert _relres(s, f, w) <= 1e-8 * (1.0 + 1e-4)
+
+
+@pytest.mark.parametrize("shape", SHAPES + [(2, 99, 2, 40, 1, 5)])
+def test_smoothing_steps(shape):
+    """Several steps at once against one at a time, to the repository's bound
+    of smoothing steps, 1e-11 of the largest entry."""
+    print(f"[gpu-cycles] smoothing {shape}", flush=True)
+    s = _solver(shape, "nodal")
+    f, g = _vector(s, 7), _vector(s, 8)
+    w = g.clone()
+    for steps in range(1, 6):
+        s.smooth(f, w, steps=1)
+        u = s.smooth(f, g.clone(), steps=steps)
+        assert float((u - w).abs().max()) <= 1e-11 * float(w.abs().max())
