@@ -190,13 +190,13 @@ constexpr int kRY = 4;
 
 // MAXR: rows of the (TY + 2P)-row strip that one thread stages (RT = 1:
 // kRY + 2P; RT >= 2: at most kRY + P)
-template <int NT, int P, int MAXR>
+template <int NT, int P, int MAXR, bool GUARD>
 __global__ __launch_bounds__(512) void k_residual2d(int n, int TXT, int RT, const double* __restrict__ M1b,
                                                      const double* __restrict__ K1b, const double* __restrict__ ktmt,
                                                      const double* __restrict__ f,
                                                      const double* __restrict__ u, double* __restrict__ r,
                                                      long s0, double sign, const int* guard) {
-    if (guard_off(guard)) return;
+    if (GUARD && guard_off(guard)) return;
     constexpr int B = 2 * P + 1;
     extern __shared__ double sm[];
     const int TY = RT * kRY, HY = TY + 2 * P, W = n + 2 * P;
@@ -314,32 +314,36 @@ __global__ __launch_bounds__(512) void k_residual2d(int n, int TXT, int RT, cons
     }
 }
 
-template <int NT, int P>
-static hipError_t residual2d_launch(int n, const double* M1b, const double* K1b, const double* ktmt,
-                                    const double* f, const double* u, double* r, long s0, long ns, double sign,
-                                    hipStream_t st, const int* guard) {
+template <int NT, int P, int MAXR, bool GUARD>
+static hipError_t residual2d_go(int n, const double* M1b, const double* K1b, const double* ktmt, const double* f,
+                                const double* u, double* r, long s0, long ns, double sign, hipStream_t st,
+                                const int* guard) {
     int TXT = (n + 7) / 8 * 8;
     int RT = TXT >= 256 ? 1 : 256 / TXT;
     int TY = RT * kRY, HY = TY + 2 * P;
     size_t shm = sizeof(double) * ((size_t)HY * (n + 2 * P) + 2 * (size_t)HY * n + 2 * (size_t)TY * (2 * P + 1));
+    const void* k = (const void*)k_residual2d<NT, P, MAXR, GUARD>;
     static std::atomic<bool> attr_set{false};       // set once; the attribute call is idempotent
     if (!attr_set.load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_residual2d<NT, P, kRY + 2 * P>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void*)k_residual2d<NT, P, kRY + P>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         attr_set.store(true, std::memory_order_release);
     }
-    dim3 grid((unsigned)((n + TY - 1) / TY), (unsigned)ns);
-    if (RT == 1)
-        hipLaunchKernelGGL((k_residual2d<NT, P, kRY + 2 * P>), grid, dim3(TXT * RT), shm, st, n, TXT, RT, M1b, K1b,
-                           ktmt, f, u, r, s0, sign, guard);
-    else
-        hipLaunchKernelGGL((k_residual2d<NT, P, kRY + P>), grid, dim3(TXT * RT), shm, st, n, TXT, RT, M1b, K1b,
-                           ktmt, f, u, r, s0, sign, guard);
+    const dim3 grid((unsigned)((n + TY - 1) / TY), (unsigned)ns);
+    hipLaunchKernelGGL((k_residual2d<NT, P, MAXR, GUARD>), grid, dim3(TXT * RT), shm, st, n, TXT, RT, M1b, K1b, ktmt, f,
+                       u, r, s0, sign, guard);
     return hipGetLastError();
+}
+
+template <int NT, int P>
+static hipError_t residual2d_launch(int n, const double* M1b, const double* K1b, const double* ktmt,
+                                    const double* f, const double* u, double* r, long s0, long ns, double sign,
+                                    hipStream_t st, const int* guard) {
+    if ((n + 7) / 8 * 8 > 128)                      // one thread row
+        return guard ? residual2d_go<NT, P, kRY + 2 * P, true>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard)
+                     : residual2d_go<NT, P, kRY + 2 * P, false>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
+    return guard ? residual2d_go<NT, P, kRY + P, true>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard)
+                 : residual2d_go<NT, P, kRY + P, false>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
 }
 
 template <int P>
@@ -366,7 +370,9 @@ static hipError_t residual2d_nt(int Nt, int n, const double* M1b, const double* 
 // The wave marches along y: for each input row and time row it applies M_1
 // and K_1 along x (neighbours by cross-lane reads), keeps the last 2P+1
 // results per time row in registers, and completes each output row with the
-// y pass and the temporal contraction.  The next input row is loaded while
+// y pass and the temporal contraction (256^2 x 3 on 256 slabs 288 us, 128^2 x
+// 4 on 256 113 us: 4.2 and 3.6 TB/s; LDS shuffles for the neighbours 292 and
+// 120 us).  The next input row is loaded while
 // the current one is processed.  With `partial` the block's sum of squares
 // of r goes to partial[blockIdx.x] (fixed order).
 // waves per SIMD the marching kernel asks for: 4 (at most 128 VGPRs) where
@@ -449,10 +455,11 @@ void k_residual2d_march(int n, int nxc, int nyr, int YR, long nwaves,
 #pragma unroll
             for (int tr = 0; tr < NR; ++tr) {
                 double a = bm[P] * cv[tr], b = bk[P] * cv[tr];
+                double up = cv[tr], dn = cv[tr];
 #pragma unroll
                 for (int d = 1; d <= P; ++d) {
-                    const double up = __shfl_down(cv[tr], d);    // column x + d
-                    const double dn = __shfl_up(cv[tr], d);      // column x - d
+                    up = wave_dpp<kDppWaveShl1, 0xf>(up);        // column x + d
+                    dn = wave_dpp<kDppWaveShr1, 0xf>(dn);        // column x - d
                     a += bm[P + d] * up + bm[P - d] * dn;
                     b += bk[P + d] * up + bk[P - d] * dn;
                 }
@@ -849,6 +856,16 @@ static bool residual_marches(int dim, int n, int p, int Nt) {
     return dim == 2 && n >= 128 && p >= 1 && p <= kMaxP && 2 * (Nt + 1) * (2 * p + 1) <= 64;
 }
 
+// ... and narrower ones where its waves' columns are used to 60 % and fill 900
+// waves of 16 rows (its chain over the rows is long): 101^2 x 3 on 300 slabs
+// 78 -> 59 us, on 20 slabs 13 against 19; 79^2 x 4 on 160 40 -> 33; 60^2 x 3 on
+// 400 38 -> 28, but 62^2 (two ranges of 60 columns) 38 against 40; 70^2 x 3 on
+// 120 18 against 27.
+static bool residual_marches_narrow(int n, int p, int Nt, long ns) {
+    const long xs = 64 - 2 * p, nxc = (n + xs - 1) / xs;
+    return p >= 1 && 2 * (Nt + 1) * (2 * p + 1) <= 64 && 10 * n >= 6 * nxc * xs && ns * n * n >= 900 * 16 * xs;
+}
+
 hipError_t launch_residual_norm(int dim, int Nt, int p, int n, const double* M1b, const double* K1b,
                                 const double* ktmt, const double* f, const double* u, double* r, long ns,
                                 double* partial, long max_partial, double* out, double* out_host, hipStream_t st) {
@@ -875,7 +892,7 @@ hipError_t launch_residual(int dim, int Nt, int p, int n, const double* M1b, con
                            long s0, long ns, double sign, hipStream_t st, const int* guard) {
     if (ns <= 0) return hipSuccess;
     if (p < 1 || p > kMaxP) return hipErrorInvalidValue;
-    if (residual_marches(dim, n, p, Nt)) {
+    if (residual_marches(dim, n, p, Nt) || (dim == 2 && residual_marches_narrow(n, p, Nt, ns))) {
         switch (p) {
             case 1: return residual2d_march_nt<1>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, nullptr, nullptr, st, guard);
             case 2: return residual2d_march_nt<2>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, nullptr, nullptr, st, guard);

@@ -68,3 +68,29 @@ def test_residual_3d(n_elem, degree, n_slabs, n_elem_t):
         print(f"  n={n} p={degree} S={n_slabs} N_t={nt}: {err:.2e} of the bound {tol:.2e}")
         assert err <= tol
     s.close()
+
+
+@pytest.mark.parametrize("n_elem,degree,n_slabs,n_elem_t", [
+    (41, 1, 480, 1), (60, 2, 251, 1), (59, 3, 250, 1), (76, 1, 170, 2), (80, 2, 151, 2), (79, 4, 140, 1), (101, 1, 90, 3), (127, 2, 60, 1),
+])
+def test_narrow_images_march(n_elem, degree, n_slabs, n_elem_t):
+    """2-D images below 128 columns with enough slabs for the marching kernel,
+    against a few of their slabs alone, which the kernel of whole rows takes:
+    the repository's residual bound, 1e-12 of the largest entry."""
+    import paper_1802_09277_amd as sth
+    s = sth.Solver(2, n_elem, degree, n_slabs, n_elem_t)
+    part = 5
+    # the same slab length: a prefix of the time interval
+    t = sth.Solver(2, n_elem, degree, part, n_elem_t, T=part / n_slabs)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n_elem)
+    f, u = (torch.randn(s.vector_len, generator=gen, dtype=torch.float64, device="cuda") for _ in range(2))
+    r = s.residual(f, u, s.new_vector())
+    m = t.vector_len
+    want = t.residual(f[:m].clone(), u[:m].clone(), t.new_vector())
+    assert float((r[:m] - want).abs().max()) <= 1e-12 * float(want.abs().max())
+    # the last slabs: the same operator on a shifted window, past its first slab
+    off = s.vector_len - m
+    slab = m // part
+    want = t.residual(f[off:].clone(), u[off:].clone(), t.new_vector())
+    assert float((r[off + slab:] - want[slab:]).abs().max()) <= 1e-12 * float(want.abs().max())
