@@ -553,9 +553,17 @@ hipError_t launch_cycles_table(int dim, int Nt, int L, const TimeMix* tm, const 
 // sum j of the batch by block j (fixed order) to out[j] and the host, then a
 // completion mark of its own
 __global__ __launch_bounds__(256) void k_cycle_sums(const double* __restrict__ partial, long count,
-                                                    double* out_host, int* seq, int seq_val) {
+                                                    double* out_host, int* seq, int seq_val, SolveStart start,
+                                                    int nsums) {
     __shared__ double red[4];
-    const double* p = partial + (long)blockIdx.x * count;
+    const bool fin = (int)blockIdx.x == nsums;              // the solve's prologue
+    const double* p = fin ? start.partial : partial + (long)blockIdx.x * count;
+    int nz = 0;
+    if (fin) {
+        count = kNormBlocks;
+        for (int i = threadIdx.x; i < kNormBlocks; i += 256) nz |= p[kNormBlocks + i] != 0.0;
+        nz = __syncthreads_or(nz);
+    }
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     long i = threadIdx.x;
     for (; i + 768 < count; i += 1024) {
@@ -571,7 +579,14 @@ __global__ __launch_bounds__(256) void k_cycle_sums(const double* __restrict__ p
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) {
-        out_host[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+        v = (red[0] + red[1]) + (red[2] + red[3]);
+        if (fin) {
+            *start.out = *start.out_host = v;
+            start.flags[0] = *start.flag_host = nz ? 1 : 0;
+            start.flags[1] = nz ? 0 : 1;
+        } else {
+            out_host[blockIdx.x] = v;
+        }
         if (seq) {
             __threadfence_system();
             seq[blockIdx.x] = seq_val;
@@ -634,7 +649,7 @@ bool cycles_lines(int Nt, int L, long S) {
 hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega, long S, int m,
                          const double* rin, const double* fh, double* rout, double* uout, double* partial,
                          long max_partial, double* out_host, int* seq, int seq_val, hipStream_t st, int vt, bool rin_lines,
-                         bool rout_lines) {
+                         bool rout_lines, const SolveStart* start) {
     const int LA = cycles_lane_slabs(Nt, L, S);
     if (!LA || m < 0 || m > kMaxBatch || (L == 1 && m > 1)) return hipErrorInvalidValue;
     if (partial && 3L * (m + 1) * cycles_blocks(8, Nx) > max_partial) return hipErrorInvalidValue;
@@ -654,8 +669,8 @@ hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega
     }
 #undef STH_CYC_NT
     if (e != hipSuccess || !partial) return e;
-    hipLaunchKernelGGL(k_cycle_sums, dim3(3 * (m + 1)), dim3(256), 0, st, partial, blocks, out_host, seq,
-                       seq_val);
+    hipLaunchKernelGGL(k_cycle_sums, dim3(3 * (m + 1) + (start ? 1 : 0)), dim3(256), 0, st, partial, blocks, out_host,
+                       seq, seq_val, start ? *start : SolveStart{}, 3 * (m + 1));
     return hipGetLastError();
 }
 

@@ -353,31 +353,9 @@ __global__ __launch_bounds__(256) void k_prologue(const double* __restrict__ f, 
     }
 }
 
-__global__ __launch_bounds__(256) void k_prologue_final(const double* __restrict__ partial, double* out,
-                                                        double* out_host, int* flags, int* flag_host) {
-    __shared__ double sh[256];
-    double s = 0.0;
-    int nz = 0;
-    for (int i = threadIdx.x; i < kNormBlocks; i += 256) {
-        s += partial[i];
-        nz |= partial[kNormBlocks + i] != 0.0;
-    }
-    nz = __syncthreads_or(nz);
-    const double tot = block_sum_256(s, sh);
-    if (threadIdx.x == 0) {
-        out[0] = tot;
-        *out_host = tot;
-        flags[0] = nz ? 1 : 0;
-        flags[1] = nz ? 0 : 1;
-        *flag_host = nz ? 1 : 0;
-    }
-}
-
-hipError_t launch_solve_prologue(const double* f, const double* u, long len, double* partial, double* out,
-                                 double* out_host, int* flags, int* flag_host, hipStream_t st) {
+hipError_t launch_solve_prologue(const double* f, const double* u, long len, double* partial, hipStream_t st) {
     const long chunk = std::max<long>(1, (len + kNormBlocks - 1) / kNormBlocks);
     hipLaunchKernelGGL(k_prologue, dim3(kNormBlocks), dim3(256), 0, st, f, u, len, chunk, partial);
-    hipLaunchKernelGGL(k_prologue_final, dim3(1), dim3(256), 0, st, partial, out, out_host, flags, flag_host);
     return hipGetLastError();
 }
 

@@ -25,9 +25,7 @@ __global__ __launch_bounds__(256) void k_residual(int p, int n, const double* __
                                                   const double* __restrict__ K1b, TimeOp op,
                                                   const double* __restrict__ f,
                                                   const double* __restrict__ u, double* __restrict__ r,
-                                                  long s0, double sign, int tiles_x, int tiles_y,
-                                                  const int* guard) {
-    if (guard_off(guard)) return;
+                                                  long s0, double sign, int tiles_x, int tiles_y) {
     using Tl = ResTile<DIM>;
     constexpr int TX = Tl::TX, TY = Tl::TY, TZ = Tl::TZ;
     constexpr int HXM = TX + 2 * kMaxP, HYM = TY + 2 * kMaxP, HZM = (DIM == 3) ? TZ + 2 * kMaxP : 1;
@@ -159,7 +157,7 @@ __global__ __launch_bounds__(256) void k_residual(int p, int n, const double* __
 template <int DIM>
 static hipError_t residual_dim(int Nt, int p, int n, const double* M1b, const double* K1b,
                                const TimeOp& op, const double* f, const double* u, double* r,
-                               long s0, long ns, double sign, hipStream_t st, const int* guard) {
+                               long s0, long ns, double sign, hipStream_t st) {
     using Tl = ResTile<DIM>;
     int tiles_x = (n + Tl::TX - 1) / Tl::TX, tiles_y = (n + Tl::TY - 1) / Tl::TY;
     int tiles_z = (DIM == 3) ? (n + Tl::TZ - 1) / Tl::TZ : 1;
@@ -168,7 +166,7 @@ static hipError_t residual_dim(int Nt, int p, int n, const double* M1b, const do
     case NTV:                                                                                      \
         if constexpr (DIM == 2 || NTV == 8) {                                                      \
             hipLaunchKernelGGL((k_residual<DIM, NTV>), grid, dim3(256), 0, st, p, n, M1b, K1b, op, \
-                               f, u, r, s0, sign, tiles_x, tiles_y, guard);                               \
+                               f, u, r, s0, sign, tiles_x, tiles_y);                               \
             break;                                                                                 \
         }                                                                                          \
         return hipErrorInvalidValue;
@@ -190,13 +188,12 @@ constexpr int kRY = 4;
 
 // MAXR: rows of the (TY + 2P)-row strip that one thread stages (RT = 1:
 // kRY + 2P; RT >= 2: at most kRY + P)
-template <int NT, int P, int MAXR, bool GUARD>
+template <int NT, int P, int MAXR>
 __global__ __launch_bounds__(512) void k_residual2d(int n, int TXT, int RT, const double* __restrict__ M1b,
                                                      const double* __restrict__ K1b, const double* __restrict__ ktmt,
                                                      const double* __restrict__ f,
                                                      const double* __restrict__ u, double* __restrict__ r,
-                                                     long s0, double sign, const int* guard) {
-    if (GUARD && guard_off(guard)) return;
+                                                     long s0, double sign) {
     constexpr int B = 2 * P + 1;
     extern __shared__ double sm[];
     const int TY = RT * kRY, HY = TY + 2 * P, W = n + 2 * P;
@@ -314,15 +311,14 @@ __global__ __launch_bounds__(512) void k_residual2d(int n, int TXT, int RT, cons
     }
 }
 
-template <int NT, int P, int MAXR, bool GUARD>
+template <int NT, int P, int MAXR>
 static hipError_t residual2d_go(int n, const double* M1b, const double* K1b, const double* ktmt, const double* f,
-                                const double* u, double* r, long s0, long ns, double sign, hipStream_t st,
-                                const int* guard) {
+                                const double* u, double* r, long s0, long ns, double sign, hipStream_t st) {
     int TXT = (n + 7) / 8 * 8;
     int RT = TXT >= 256 ? 1 : 256 / TXT;
     int TY = RT * kRY, HY = TY + 2 * P;
     size_t shm = sizeof(double) * ((size_t)HY * (n + 2 * P) + 2 * (size_t)HY * n + 2 * (size_t)TY * (2 * P + 1));
-    const void* k = (const void*)k_residual2d<NT, P, MAXR, GUARD>;
+    const void* k = (const void*)k_residual2d<NT, P, MAXR>;
     static std::atomic<bool> attr_set{false};       // set once; the attribute call is idempotent
     if (!attr_set.load(std::memory_order_acquire)) {
         const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -330,34 +326,32 @@ static hipError_t residual2d_go(int n, const double* M1b, const double* K1b, con
         attr_set.store(true, std::memory_order_release);
     }
     const dim3 grid((unsigned)((n + TY - 1) / TY), (unsigned)ns);
-    hipLaunchKernelGGL((k_residual2d<NT, P, MAXR, GUARD>), grid, dim3(TXT * RT), shm, st, n, TXT, RT, M1b, K1b, ktmt, f,
-                       u, r, s0, sign, guard);
+    hipLaunchKernelGGL((k_residual2d<NT, P, MAXR>), grid, dim3(TXT * RT), shm, st, n, TXT, RT, M1b, K1b, ktmt, f,
+                       u, r, s0, sign);
     return hipGetLastError();
 }
 
 template <int NT, int P>
 static hipError_t residual2d_launch(int n, const double* M1b, const double* K1b, const double* ktmt,
                                     const double* f, const double* u, double* r, long s0, long ns, double sign,
-                                    hipStream_t st, const int* guard) {
+                                    hipStream_t st) {
     if ((n + 7) / 8 * 8 > 128)                      // one thread row
-        return guard ? residual2d_go<NT, P, kRY + 2 * P, true>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard)
-                     : residual2d_go<NT, P, kRY + 2 * P, false>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
-    return guard ? residual2d_go<NT, P, kRY + P, true>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard)
-                 : residual2d_go<NT, P, kRY + P, false>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
+        return residual2d_go<NT, P, kRY + 2 * P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
+    return residual2d_go<NT, P, kRY + P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
 }
 
 template <int P>
 static hipError_t residual2d_nt(int Nt, int n, const double* M1b, const double* K1b, const double* ktmt,
                                 const double* f, const double* u, double* r, long s0, long ns, double sign,
-                                hipStream_t st, const int* guard) {
+                                hipStream_t st) {
     switch (Nt) {
-        case 2: if (P + 1 <= 2) return residual2d_launch<2, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard); break;
-        case 3: if (P + 1 <= 3) return residual2d_launch<3, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard); break;
-        case 4: if (P + 1 <= 4) return residual2d_launch<4, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard); break;
-        case 5: return residual2d_launch<5, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
-        case 6: return residual2d_launch<6, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
-        case 7: return residual2d_launch<7, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
-        case 8: return residual2d_launch<8, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
+        case 2: if (P + 1 <= 2) return residual2d_launch<2, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st); break;
+        case 3: if (P + 1 <= 3) return residual2d_launch<3, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st); break;
+        case 4: if (P + 1 <= 4) return residual2d_launch<4, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st); break;
+        case 5: return residual2d_launch<5, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
+        case 6: return residual2d_launch<6, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
+        case 7: return residual2d_launch<7, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
+        case 8: return residual2d_launch<8, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
         default: break;
     }
     return hipErrorInvalidValue;
@@ -389,9 +383,7 @@ void k_residual2d_march(int n, int nxc, int nyr, int YR, long nwaves,
                                                           const double* __restrict__ ktmt,
                                                           const double* __restrict__ f,
                                                           const double* __restrict__ u, double* __restrict__ r,
-                                                          long s0, double sign, double* __restrict__ partial,
-                                                          const int* guard) {
-    if (guard_off(guard)) return;
+                                                          long s0, double sign, double* __restrict__ partial) {
     constexpr int B = 2 * P + 1, NR = NT + 1;   // band width; time rows with the coupling row
     constexpr int XS = 64 - 2 * P;              // output columns per wave
     const int lane = threadIdx.x & 63;
@@ -564,8 +556,7 @@ void k_residual3d(int n, int hx_n, int hy_n, int hpx, int hpy, int tiles_x,
                                                              const double* __restrict__ ktmt,
                                                              const double* __restrict__ f,
                                                              const double* __restrict__ u, double* __restrict__ r,
-                                                             long s0, double sign, const int* guard) {
-    if (guard_off(guard)) return;
+                                                             long s0, double sign) {
     constexpr int B = 2 * P + 1, NR = NT + 1;
     extern __shared__ double sm[];
     const int lx_n = hx_n + 2 * P, ly_n = hy_n + 2 * P;
@@ -776,7 +767,7 @@ static int residual3d_planes(int n, int p, long tiles) {
 
 template <int NT, int P>
 static hipError_t residual3d_launch(int n, const double* M1b, const double* K1b, const double* ktmt, const double* f,
-                                    const double* u, double* r, long s0, long ns, double sign, hipStream_t st, const int* guard) {
+                                    const double* u, double* r, long s0, long ns, double sign, hipStream_t st) {
     Res3Tile t{};
     if (!residual3d_tile(NT, P, n, &t)) return hipErrorInvalidValue;
     static std::atomic<bool> attr_set{false};       // set once; the attribute call is idempotent
@@ -792,18 +783,18 @@ static hipError_t residual3d_launch(int n, const double* M1b, const double* K1b,
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_residual3d<NT, P>), dim3((unsigned)blocks), dim3((t.hx * t.hy + 63) / 64 * 64), t.shm, st, n,
                        t.hx, t.hy, t.hpx, t.hpy, t.tiles_x, t.tiles_y, zc, nzc, blocks, M1b, K1b, ktmt, f, u, r, s0,
-                       sign, guard);
+                       sign);
     return hipGetLastError();
 }
 
 template <int P>
 static hipError_t residual3d_nt(int Nt, int n, const double* M1b, const double* K1b, const double* ktmt,
                                 const double* f, const double* u, double* r, long s0, long ns, double sign,
-                                hipStream_t st, const int* guard) {
+                                hipStream_t st) {
 #define STH_R3_CASE(NTV)                                                                                      \
     case NTV:                                                                                                  \
         if constexpr (NTV > P && !(P == 4 && NTV == 8))                                                        \
-            return residual3d_launch<NTV, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);                    \
+            return residual3d_launch<NTV, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);                    \
         return hipErrorInvalidValue;
     switch (Nt) {
         STH_R3_CASE(2) STH_R3_CASE(3) STH_R3_CASE(4) STH_R3_CASE(5) STH_R3_CASE(6) STH_R3_CASE(7) STH_R3_CASE(8)
@@ -824,24 +815,24 @@ static int march_rows(int n, int p, long ns) {
 template <int NT, int P>
 static hipError_t residual2d_march_launch(int n, const double* M1b, const double* K1b, const double* ktmt,
                                           const double* f, const double* u, double* r, long s0, long ns, double sign,
-                                          double* partial, long* nblocks, hipStream_t st, const int* guard) {
+                                          double* partial, long* nblocks, hipStream_t st) {
     const int nxc = (n + 63 - 2 * P) / (64 - 2 * P), YR = march_rows(n, P, ns), nyr = (n + YR - 1) / YR;
     const long nwaves = ns * nxc * nyr, blocks = (nwaves + 3) / 4;
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
     if (nblocks) *nblocks = blocks;
     hipLaunchKernelGGL((k_residual2d_march<NT, P>), dim3((unsigned)blocks), dim3(256), 0, st, n, nxc, nyr, YR, nwaves,
-                       M1b, K1b, ktmt, f, u, r, s0, sign, partial, guard);
+                       M1b, K1b, ktmt, f, u, r, s0, sign, partial);
     return hipGetLastError();
 }
 
 template <int P>
 static hipError_t residual2d_march_nt(int Nt, int n, const double* M1b, const double* K1b, const double* ktmt,
                                       const double* f, const double* u, double* r, long s0, long ns, double sign,
-                                      double* partial, long* nblocks, hipStream_t st, const int* guard) {
+                                      double* partial, long* nblocks, hipStream_t st) {
 #define STH_RM_CASE(NTV)                                                                                    \
     case NTV:                                                                                                \
         if constexpr (2 * (NTV + 1) * (2 * P + 1) <= 64)                                                     \
-            return residual2d_march_launch<NTV, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, partial, nblocks, st, guard); \
+            return residual2d_march_launch<NTV, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, partial, nblocks, st); \
         return hipErrorInvalidValue;
     switch (Nt) {
         STH_RM_CASE(2) STH_RM_CASE(3) STH_RM_CASE(4) STH_RM_CASE(5) STH_RM_CASE(6) STH_RM_CASE(7) STH_RM_CASE(8)
@@ -876,10 +867,10 @@ hipError_t launch_residual_norm(int dim, int Nt, int p, int n, const double* M1b
     long blocks = 0;
     hipError_t e;
     switch (p) {
-        case 1: e = residual2d_march_nt<1>(Nt, n, M1b, K1b, ktmt, f, u, r, 0, ns, 1.0, partial, &blocks, st, nullptr); break;
-        case 2: e = residual2d_march_nt<2>(Nt, n, M1b, K1b, ktmt, f, u, r, 0, ns, 1.0, partial, &blocks, st, nullptr); break;
-        case 3: e = residual2d_march_nt<3>(Nt, n, M1b, K1b, ktmt, f, u, r, 0, ns, 1.0, partial, &blocks, st, nullptr); break;
-        default: e = residual2d_march_nt<4>(Nt, n, M1b, K1b, ktmt, f, u, r, 0, ns, 1.0, partial, &blocks, st, nullptr); break;
+        case 1: e = residual2d_march_nt<1>(Nt, n, M1b, K1b, ktmt, f, u, r, 0, ns, 1.0, partial, &blocks, st); break;
+        case 2: e = residual2d_march_nt<2>(Nt, n, M1b, K1b, ktmt, f, u, r, 0, ns, 1.0, partial, &blocks, st); break;
+        case 3: e = residual2d_march_nt<3>(Nt, n, M1b, K1b, ktmt, f, u, r, 0, ns, 1.0, partial, &blocks, st); break;
+        default: e = residual2d_march_nt<4>(Nt, n, M1b, K1b, ktmt, f, u, r, 0, ns, 1.0, partial, &blocks, st); break;
     }
     if (e != hipSuccess) return e;
     return launch_sum_partials(partial, (int)blocks, out, out_host, 1, nullptr, CycleFlag{}, st);
@@ -889,39 +880,39 @@ bool residual_norm_fused(int dim, int n, int p, int Nt) { return residual_marche
 
 hipError_t launch_residual(int dim, int Nt, int p, int n, const double* M1b, const double* K1b,
                            const TimeOp& op, const double* ktmt, const double* f, const double* u, double* r,
-                           long s0, long ns, double sign, hipStream_t st, const int* guard) {
+                           long s0, long ns, double sign, hipStream_t st) {
     if (ns <= 0) return hipSuccess;
     if (p < 1 || p > kMaxP) return hipErrorInvalidValue;
     if (residual_marches(dim, n, p, Nt) || (dim == 2 && residual_marches_narrow(n, p, Nt, ns))) {
         switch (p) {
-            case 1: return residual2d_march_nt<1>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, nullptr, nullptr, st, guard);
-            case 2: return residual2d_march_nt<2>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, nullptr, nullptr, st, guard);
-            case 3: return residual2d_march_nt<3>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, nullptr, nullptr, st, guard);
-            case 4: return residual2d_march_nt<4>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, nullptr, nullptr, st, guard);
+            case 1: return residual2d_march_nt<1>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, nullptr, nullptr, st);
+            case 2: return residual2d_march_nt<2>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, nullptr, nullptr, st);
+            case 3: return residual2d_march_nt<3>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, nullptr, nullptr, st);
+            case 4: return residual2d_march_nt<4>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, nullptr, nullptr, st);
         }
     }
     if (dim == 2) {
         int TXT = (n + 7) / 8 * 8, RT = TXT >= 256 ? 1 : 256 / TXT;
         int TY = RT * kRY, HY = TY + 2 * p;
         size_t shm = sizeof(double) * ((size_t)HY * (n + 2 * p) + 2 * (size_t)HY * n + 2 * (size_t)TY * (2 * p + 1));
-        if (shm > 150 * 1024 || TXT * RT > 512) return residual_dim<2>(Nt, p, n, M1b, K1b, op, f, u, r, s0, ns, sign, st, guard);
+        if (shm > 150 * 1024 || TXT * RT > 512) return residual_dim<2>(Nt, p, n, M1b, K1b, op, f, u, r, s0, ns, sign, st);
         switch (p) {
-            case 1: return residual2d_nt<1>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
-            case 2: return residual2d_nt<2>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
-            case 3: return residual2d_nt<3>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
-            case 4: return residual2d_nt<4>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
+            case 1: return residual2d_nt<1>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
+            case 2: return residual2d_nt<2>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
+            case 3: return residual2d_nt<3>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
+            case 4: return residual2d_nt<4>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
         }
     }
     if (dim == 3) {
         // degree 4 with 8 time rows: the window of the marching kernel spills
         // (1090 us against 933 us of the per-tile kernel on 40 slabs of 32^3 x 8;
         // with 7 rows it is ahead, 763 against 828 us)
-        if (p == 4 && Nt == 8) return residual_dim<3>(Nt, p, n, M1b, K1b, op, f, u, r, s0, ns, sign, st, guard);
+        if (p == 4 && Nt == 8) return residual_dim<3>(Nt, p, n, M1b, K1b, op, f, u, r, s0, ns, sign, st);
         switch (p) {
-            case 1: return residual3d_nt<1>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
-            case 2: return residual3d_nt<2>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
-            case 3: return residual3d_nt<3>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
-            case 4: return residual3d_nt<4>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st, guard);
+            case 1: return residual3d_nt<1>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
+            case 2: return residual3d_nt<2>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
+            case 3: return residual3d_nt<3>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
+            case 4: return residual3d_nt<4>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
         }
     }
     return hipErrorInvalidValue;

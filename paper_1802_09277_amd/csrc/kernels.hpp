@@ -60,7 +60,7 @@ struct CycleFlag {
 // ktmt: device copy of op (K_t then M_t, kNt x kNt each).
 hipError_t launch_residual(int dim, int Nt, int p, int n, const double* M1b, const double* K1b,
                            const TimeOp& op, const double* ktmt, const double* f, const double* u, double* r,
-                           long s0, long ns, double sign, hipStream_t st, const int* guard = nullptr);
+                           long s0, long ns, double sign, hipStream_t st);
 
 // The residual with its squared norm (2-D images of 128 or more columns and
 // small degrees: residual_norm_fused): r = f - L u over all ns slabs, and
@@ -253,7 +253,16 @@ hipError_t launch_eig_coarse_tail3(int dim, int Nt, const TimeMix* tma_dev, cons
 //  j, seq[j] = seq_val.  Vectors differ, except fh == rin.  rin_lines,
 //  rout_lines: that vector is by time lines, an order for the batches'
 //  residuals between them (where cycles_lines allows it, of the same length).
+//  start (may be null; with sums): the last sum also finishes a solve's
+//  prologue, mark included: out[0] = ||f||^2 (also to out_host), flags[0] = 1 if
+//  some entry of u is not zero (NaN included; also to flag_host), flags[1] = 1 -
+//  flags[0].
 constexpr int kMaxBatch = 8;
+struct SolveStart {
+    const double* partial;
+    double *out, *out_host;
+    int *flags, *flag_host;
+};
 bool cycles_supported(int Nt, int L, long S);
 bool cycles_lines(int Nt, int L, long S);
 long cycles_partials(long Nx);
@@ -263,7 +272,7 @@ hipError_t launch_cycles_table(int dim, int Nt, int L, const TimeMix* tm, const 
 hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega, long S, int m,
                          const double* rin, const double* fh, double* rout, double* uout, double* partial,
                          long max_partial, double* out_host, int* seq, int seq_val, hipStream_t st, int vt = 0,
-                         bool rin_lines = false, bool rout_lines = false);
+                         bool rin_lines = false, bool rout_lines = false, const SolveStart* start = nullptr);
 //  uout = L^{-1}(r - r_m), what m = steps damped block-Jacobi steps on the
 //  finest level add to the iterate of the residual r
 hipError_t launch_smoothing(int Nt, int L, const double* tab, long Nx, double omega, long S, int steps,
@@ -354,12 +363,10 @@ hipError_t launch_normalize(double* w, long len, const double* n2, hipStream_t s
 hipError_t launch_multiaxpy(const double* V, long ld, int k, const double* c, double alpha, double* w, long len,
                             hipStream_t st);
 
-// Start of a solve in one read of f and u: out[0] = ||f||^2 (also to out_host),
-// flags[0] = 1 if some entry of u is not zero (NaN included), flags[1] = 1 -
-// flags[0] (flags[0] also to flag_host); the host pointers are mapped pinned
-// memory; partial needs 2 kNormBlocks entries.
-hipError_t launch_solve_prologue(const double* f, const double* u, long len, double* partial, double* out,
-                                 double* out_host, int* flags, int* flag_host, hipStream_t st);
+// Start of a solve in one read of f and u: partial sums of ||f||^2 and block
+// flags, for the batch's sums to finish (SolveStart); partial needs 2
+// kNormBlocks entries.
+hipError_t launch_solve_prologue(const double* f, const double* u, long len, double* partial, hipStream_t st);
 
 // Two-stage deterministic sum of squares: partial sums over a fixed number
 // of blocks, then one block; result in out[0].

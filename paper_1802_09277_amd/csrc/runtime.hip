@@ -39,7 +39,7 @@ static thread_local std::string g_err;
 constexpr int kNormSlots = 14;
 constexpr int slot_base(int slot) { return 2 + 3 * slot; }
 constexpr int kMixR = 11, kMixF = 12;
-constexpr int kCycSums = 3 * (kMaxBatch + 1);      // sums of a batch of cycles
+constexpr int kCycSums = 3 * (kMaxBatch + 1) + 1;  // sums of a batch of cycles, and the solve's prologue
 
 static int fail(int code, const std::string& msg) {
     g_err = msg;
@@ -245,8 +245,11 @@ struct sth_handle {
         int start = -1, end = 0, uout = -2, m = 0;
         int known = 0;                  // cycles of the batch whose sums have been tested already
         bool first = true;
+        bool mapped = false;            // uout is being mapped into u (from a zero guess), behind its batch
         bool start_lines = false;       // the first residual is by time lines (cyc_lines)
         bool nonzero = false;           // the initial guess has a nonzero entry
+        bool restarted = false;         // the first batch was taken again from f - L u
+        bool prologue = false;          // the batch's sums finish the prologue
         bool inner = false;
         bool inner_store = false;       // the inner result is stored into u (u was zero), not added
         int tprec = STH_FP64;
@@ -343,7 +346,7 @@ struct Timed {
 // building blocks
 // ---------------------------------------------------------------------------
 static int residual(sth_handle* h, int lvl, const double* f, const double* u, double* r, long s0, long ns,
-                    double sign, hipStream_t st, const int* guard = nullptr) {
+                    double sign, hipStream_t st) {
     h->tlev = lvl;
     double dof = (double)ns * slab_len(h);
     int B = 2 * h->p + 1;
@@ -351,7 +354,7 @@ static int residual(sth_handle* h, int lvl, const double* f, const double* u, do
     double bytes = dof * (f ? 24.0 : 16.0);
     Timed tm(h, STH_K_RESIDUAL, flops, bytes, st);
     HIPCHK(launch_residual(h->dim, h->Nt, h->p, h->n, h->M1b, h->K1b, h->ops[lvl],
-                           h->dktmt + (size_t)lvl * 2 * kNt * kNt, f, u, r, s0, ns, sign, st, guard));
+                           h->dktmt + (size_t)lvl * 2 * kNt * kNt, f, u, r, s0, ns, sign, st));
     return STH_OK;
 }
 
@@ -2485,13 +2488,16 @@ static int cyc_launch(sth_handle* h, int from, bool from_lines, int end, bool en
     if (end_lines) h->pad_dirty = h->Nxe != h->Nx;
     Timed tm(h, STH_K_EIG_CYCLE_CLOSE, dof * (m * (9.4 * h->Nt + 19.0) + (uout >= 0 ? 4.0 * h->Nt : 0.0)),
              dof * eb * (1.0 + (end >= 0 ? 1.0 : 0.0) + (uout >= 0 ? (from < 0 ? 1.0 : 2.0) : 0.0)), v.st);
+    const SolveStart start{h->partial, h->dnorm + 1, h->hnorm_dev + 1, h->dgo + 6, h->hflag_dev + 4};
+    const bool fin = sums && v.prologue;
     HIPCHK(launch_cycles(h->Nt, h->L, h->cyc_tab, h->Nxe, h->omega, h->lev_S[0], m, cyc_buf(h, from), h->e0,
                          end >= 0 ? cyc_buf(h, end) : nullptr, uout >= 0 ? cyc_buf(h, uout) : nullptr,
                          sums ? h->cpartial : nullptr, h->n_cpartial, h->hcyc_dev, sums && h->want_poll ? h->hcseq_dev : nullptr, h->seq_counter, v.st, h->f32,
-                         from_lines, end_lines));
+                         from_lines, end_lines, fin ? &start : nullptr));
+    v.prologue = false;
     h->wait_ev = nullptr;
     h->wait_slot = -1;
-    h->wait_cyc = sums && h->want_poll ? 3 * (m + 1) : 0;
+    h->wait_cyc = sums && h->want_poll ? 3 * (m + 1) + (fin ? 1 : 0) : 0;
     h->wait_cyc_seq = h->seq_counter;
     return STH_OK;
 }
@@ -2504,6 +2510,7 @@ static int cyc_batch(sth_handle* h, int from, bool from_lines, int want, int kno
     auto& v = h->sv;
     v.m = std::max(0, std::min({want, h->L == 1 ? 1 : kMaxBatch, v.maxit - v.it + known}));
     if (!h->speculate) v.m = std::min(v.m, known + 1);
+    v.mapped = false;
     v.start = from;
     v.start_lines = from_lines;
     v.known = known;
@@ -2523,7 +2530,7 @@ static int cyc_finish(sth_handle* h, int j, bool* more) {
     h->wait_cyc = 0;
     if (j == 0 && v.start < 0 && !v.inner) {
         // no cycle: u stays as it is (zero again where it was a work vector)
-        if (h->basis == 0) HIPCHK(launch_fill(v.u, h->lev_S[0] * slab_len(h), 0.0, v.st));
+        if (h->basis == 0 || (v.mapped && !v.nonzero)) HIPCHK(launch_fill(v.u, h->lev_S[0] * slab_len(h), 0.0, v.st));
         return STH_OK;
     }
     int u = v.uout;
@@ -2536,6 +2543,7 @@ static int cyc_finish(sth_handle* h, int j, bool* more) {
             return rc;
     }
     h->wait_cyc = 0;                    // (a launch above sets it)
+    if (v.mapped && u == v.uout && j == v.m && !v.nonzero) return STH_OK;
     const bool add = v.inner ? !v.inner_store : v.nonzero;
     return spatial_apply(h, INV_U, cyc_buf(h, u), v.u, h->lev_S[0] * h->Nt, h->basis == 0 ? h->e0 : h->buf0, v.st,
                          nullptr, v.tprec, add ? 1 : 0, h->buf1, h->f32 ? 1 : 0);
@@ -2582,26 +2590,43 @@ static int cyc_begin(sth_handle* h, const double* inner_fn) {
     h->tlev = 0;
     const long rows = h->lev_S[0] * h->Nt, len = h->lev_S[0] * slab_len(h);
     int rc;
-    // the initial residual in the eigenbasis: f^ from a zero guess (the usual
-    // start, found on the device: the transforms of the other case return at
-    // once), else that of f - L u
+    // the initial residual in the eigenbasis: f^, for a zero guess (the usual
+    // start); whether u is zero comes with the first batch's sums, and that
+    // batch is taken again from f - L u if it is not (cyc_restart).  Launches
+    // guarded by a device flag for either case cost three more a solve, about
+    // 5 us each.
     if (v.inner) {
         h->hnorm[1] = (*inner_fn) * (*inner_fn);     // read by the host only
-        if ((rc = spatial_apply(h, FWD_U, v.f, h->e0, rows, h->buf0, v.st, nullptr, v.tprec, 0,
-                                h->f32 ? h->buf1 : nullptr, h->f32 ? 2 : 0)))
-            return rc;
     } else {
-        int* nz = h->dgo + 6;                        // and its negation behind it
-        {
-            Timed tm(h, STH_K_NORM, 2.0 * len, 16.0 * len, v.st);
-            HIPCHK(launch_solve_prologue(v.f, v.u, len, h->partial, h->dnorm + 1, h->hnorm_dev + 1, nz,
-                                         h->hflag_dev + 4, v.st));
-        }
-        if ((rc = spatial_apply(h, FWD_U, v.f, h->e0, rows, h->buf0, v.st, nz + 1))) return rc;
-        if ((rc = residual(h, 0, v.f, v.u, h->buf1, 0, h->lev_S[0], 1.0, v.st, nz))) return rc;
-        if ((rc = spatial_apply(h, FWD_U, h->buf1, h->e0, rows, h->buf0, v.st, nz))) return rc;
+        Timed tm(h, STH_K_NORM, 2.0 * len, 16.0 * len, v.st);
+        HIPCHK(launch_solve_prologue(v.f, v.u, len, h->partial, v.st));
+        v.prologue = true;
     }
+    if ((rc = spatial_apply(h, FWD_U, v.f, h->e0, rows, h->buf0, v.st, nullptr, v.tprec, 0, h->f32 ? h->buf1 : nullptr,
+                            h->f32 ? 2 : 0)))
+        return rc;
     v.first = true;
+    if ((rc = cyc_batch(h, -1, false, first_batch(v.rtol), 0, h->L == 1))) return rc;
+    // One level: the first cycle is the exact solve, which nearly always ends
+    // the iteration, so its result goes into u without waiting for the norms
+    // (from a zero guess, which this only replaces; 1024 modes x 16 slabs x 4
+    // 72 -> 38 us with the launches that go besides).
+    if (!v.inner && v.uout >= 0 && h->L == 1) {
+        v.mapped = true;
+        return spatial_apply(h, INV_U, cyc_buf(h, v.uout), v.u, rows, h->buf0, v.st, h->dgo + 7, v.tprec, 0, h->buf1);
+    }
+    return STH_OK;
+}
+
+// The first batch again, from the residual of a guess that is not zero.
+static int cyc_restart(sth_handle* h) {
+    auto& v = h->sv;
+    if (h->basis == 0) return coefficient_begin(h);      // (u holds the guess: no third buffer)
+    const long rows = h->lev_S[0] * h->Nt;
+    int rc;
+    if ((rc = residual(h, 0, v.f, v.u, h->buf1, 0, h->lev_S[0], 1.0, v.st))) return rc;
+    if ((rc = spatial_apply(h, FWD_U, h->buf1, h->e0, rows, h->buf0, v.st))) return rc;
+    v.first = v.restarted = true;
     return cyc_batch(h, -1, false, first_batch(v.rtol), 0, h->L == 1);
 }
 
@@ -2625,8 +2650,8 @@ static int cyc_continue(sth_handle* h, bool* more) {
         v.fn = std::sqrt(h->hnorm[1]);
         if (v.fn == 0.0) v.fn = 1.0;
         v.nonzero = !v.inner && h->hflag[4] != 0;
+        if (v.nonzero && !v.restarted) return cyc_restart(h);
         v.prev = std::sqrt(q[0]);
-        if (coef && v.nonzero) return coefficient_begin(h);      // (u holds the guess: no third buffer)
     } else {
         j = v.known + 1;                             // (sum `known` is the last one tested)
     }
