@@ -34,11 +34,12 @@
 // traffic, against 40 B per unknown of passes over the vectors level by
 // level; a batch moves 16 B per unknown, 24 with the iterate.  On 65536 modes
 // x 1024 slabs x 3 (1.6 GB vectors) a cycle takes 0.13 ms; a batch of 8 takes
-// 1.32 ms, one of 2 1.15 ms and 2.07 ms with the iterate: there the transfers
-// bound it (2.3 to 2.8 TB/s by rows of modes, 3.6 by time lines; one block per
+// 1.23 ms, one of 2 1.13 ms and 2.04 ms with the iterate: there the transfers
+// bound it (2.4 to 2.9 TB/s by rows of modes, 3.7 by time lines; one block per
 // compute unit at 250 registers, so little of them overlaps the cycles).
-// Solves, from passes level by level: the 12 cycles there 23.6 -> 9.3 ms,
-// 4489 modes x 256 slabs x 5 1078 -> 320 us, 1024 x 16 x 4 114 -> 73 us.
+// Solves, from passes level by level: the 12 cycles there 24.2 -> 8.6 ms,
+// 4489 modes x 256 slabs x 5 1082 -> 262 us, 1024 x 16 x 4 114 -> 36 us (with
+// the transforms and launches that changed besides).
 #include <algorithm>
 
 #include "kernels_common.hpp"
@@ -142,10 +143,15 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_
     __shared__ double red[MB][kMaxBatch + 1][3];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // the blocks that share the 128-byte lines of 16 modes sit on one XCD
-    constexpr int SH = 16 / MB;
-    const long bq = blockIdx.x / 8;
-    const long m0 = (((bq / SH) * 8 + blockIdx.x % 8) * SH + bq % SH) * MB;
+    // Blocks whose pieces are whole lines go round over the XCDs (32768 modes x
+    // 128 slabs x 4: 126 against 134 us for 8 cycles).  Else the blocks of one
+    // XCD take a contiguous range of modes, so that the lines that neighbours
+    // share stay in its L2 (against eight modes' neighbours only: 66564 modes x
+    // 64 slabs x 6, whose rows do not start on a line, 270 -> 236 us, 65536 x
+    // 1024 x 3 1.32 -> 1.21 ms).
+    const bool whole = MB * sizeof(VT) == 128 && a.Nx % MB == 0;
+    const long m0 = (whole ? (long)blockIdx.x
+                           : (long)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8) * MB;
     const long mode = m0 + wave < a.Nx ? m0 + wave : a.Nx - 1;
     const double* tab0 = a.tab + mode * len;
     const double* ptab0 = a.tab + a.Nx * len;
@@ -527,8 +533,7 @@ bool cycles_supported(int Nt, int L, long S) { return cycles_lane_slabs(Nt, L, S
 // else 8.
 template <int NT, int LA> constexpr bool cycles_wide() { return LA <= 2 || (LA == 4 && NT <= 5) || (LA == 8 && NT == 2); }
 static long cycles_blocks(int MB, long Nx) {
-    const long unit = 8 * (16 / MB);
-    return ((Nx + MB - 1) / MB + unit - 1) / unit * unit;
+    return ((Nx + MB - 1) / MB + 7) / 8 * 8;
 }
 
 long cycles_partials(long Nx) { return 3L * (kMaxBatch + 1) * cycles_blocks(8, Nx); }
