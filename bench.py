@@ -149,11 +149,11 @@ def finish_cpu_baseline(cfg, sample_slabs, started, limit_s):
 KERNEL_FILES = ("kernels.hpp", "kernels_common.hpp", "k_residual.hip", "k_xform2d.hip", "k_xform_axis.hip",
                 "k_xform_panel.hip", "k_eigen.hip", "k_misc.hip", "k_minres.hip")
 CLASS_SOURCES = {
-    "eig_cycle_close": ("kernels_common.hpp", "k_eigen.hip"),
+    "eig_cycle_close": ("kernels_common.hpp", "k_eigen.hip", "k_cycles.hip"),
     "eig_cycle_end": ("kernels_common.hpp", "k_eigen.hip"),
-    "eig_smooth": ("kernels_common.hpp", "k_eigen.hip"),
-    "xform_axis": ("kernels_common.hpp", "k_xform_axis.hip", "k_xform_panel.hip"),
-    "xform_2d": ("kernels_common.hpp", "k_xform2d.hip"),
+    "eig_smooth": ("kernels_common.hpp", "k_eigen.hip", "k_cycles.hip"),
+    "xform_axis": ("kernels_common.hpp", "k_xform_axis.hip", "k_xform_panel.hip", "k_xform_eo.hip"),
+    "xform_2d": ("kernels_common.hpp", "k_xform2d.hip", "k_xform2d_eo.hip"),
     "residual": ("kernels_common.hpp", "k_residual.hip"),
 }
 
