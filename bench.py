@@ -147,7 +147,8 @@ def finish_cpu_baseline(cfg, sample_slabs, started, limit_s):
 # the sources a kernel class compiles from (the committed HBM counters of a
 # class stay valid while these are unchanged); other classes: every kernel file
 KERNEL_FILES = ("kernels.hpp", "kernels_common.hpp", "k_residual.hip", "k_xform2d.hip", "k_xform_axis.hip",
-                "k_xform_panel.hip", "k_eigen.hip", "k_misc.hip", "k_minres.hip")
+                "k_xform_panel.hip", "k_xform_eo.hip", "k_xform2d_eo.hip", "k_cycles.hip", "k_eigen.hip", "k_misc.hip",
+                "k_minres.hip")
 CLASS_SOURCES = {
     "eig_cycle_close": ("kernels_common.hpp", "k_eigen.hip", "k_cycles.hip"),
     "eig_cycle_end": ("kernels_common.hpp", "k_eigen.hip"),

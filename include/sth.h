@@ -229,7 +229,8 @@ int sth_vcycle(sth_handle* h, const double* f, double* u, void* stream);
  * receives the result).  Blocks the host until the result is in u.  iters
  * and relres (may be NULL) receive the cycle count and the final relative
  * residual (in the eigenbasis iteration an upper bound of it when the
- * two-sided bound decides the test, else the exact value).  With
+ * two-sided bound decides the test, else the exact value).  From a guess of
+ * zeros u may hold intermediate vectors until the call returns.  With
  * iterate_basis 1 and transform_prec FP32 or BF16x3 the solve is an FP64
  * defect correction: each outer step forms the FP64 residual and its exact
  * norm, and an eigenbasis solve with reduced-precision transforms reduces
@@ -258,7 +259,10 @@ int sth_solve_fgmres(sth_handle* h, const double* f, double* u, double rtol, int
  * read) into a HIP graph for the given (f, u) and replays it (on any
  * stream; a new f or u, or a change of the timing mask, recaptures).
  * enable = 0 launches every kernel individually; so does kernel timing
- * (sth_timing), which needs events around the individual launches. */
+ * (sth_timing), which needs events around the individual launches.  Solves
+ * that run batches of cycles on chip (V(1,1) with FP64 or mixed eigenbasis
+ * cycles, N_t <= 6, up to four levels, 512 slabs or 1024 for N_t <= 3,
+ * rtol >= 1e-12) have a few launches in all and are not replayed. */
 int sth_use_graphs(sth_handle* h, int enable);
 
 /* Speculative cycles (default on; eigenbasis iteration with V(1,1) cycles,
@@ -273,7 +277,8 @@ int sth_use_graphs(sth_handle* h, int enable);
  * pass the same way (its threshold (rtol ||f||)^2 formed on the device), and
  * on the 2-D path the mapping of the result into u goes behind the exact
  * norm, guarded by the device's copy of the final test.
- * enable = 0 waits for each norm first; so does kernel timing. */
+ * enable = 0 waits for each norm first; so does kernel timing.  In solves
+ * by batches of cycles (sth_use_graphs): several cycles to a batch, or one. */
 int sth_speculate(sth_handle* h, int enable);
 
 /* Level transfers (Section 3.1, time coarsening by combining two slabs):
