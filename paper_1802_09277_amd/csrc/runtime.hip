@@ -802,7 +802,9 @@ static int spatial_apply(sth_handle* h, SpatialKind kind, const double* in, doub
         // float eigenbasis data with reduced-precision transforms: the
         // intermediate between the two axes is float as well
         const bool fmid = io_f32 != 0 && prec != STH_FP64;
-        if (fwd) {
+        // (a storing inverse of reduced precision takes the contiguous axis
+        // first as well: the order shows in its noise)
+        if (fwd || (prec != STH_FP64 && epi == 0 && io_f32 == 0)) {
             if ((rc = xform_x(h, prec, 0, in, tmp, T, rows * n, 1.0, st, g, fmid ? 2 : 0))) return rc;
             if ((rc = xform_s(h, prec, tmp, out, T, rows, n, st, g, fmid ? 3 : io_f32))) return rc;
         } else {
