@@ -70,7 +70,9 @@ struct sth_handle {
     // device data
     double* Tf = nullptr;               // np x np, U padded  (forward: r^ = U^T r)
     double* Ti = nullptr;               // np x np, U^T padded (inverse: z = U z^)
-    double* eo[4] = {};                 // packed FP64 panels of U forward, inverse, C forward, inverse
+    // packed FP64 panels of U forward, inverse, C forward, inverse (FP64
+    // transforms: the others never take one, and their odd n has no split)
+    double* eo[4] = {};
     double* mu1 = nullptr;
     double* M1b = nullptr;
     double* K1b = nullptr;
@@ -378,7 +380,7 @@ static int split_of(const sth_handle* h, const double* T) { return !h->split ? 0
 static int xform_x(sth_handle* h, int prec, int epi, const double* in, double* out, const double* T, long lines,
                    double alpha, hipStream_t st, const int* guard = nullptr, int io = 0) {
     const double dof = (double)lines * h->n;
-    const bool eo = prec == STH_FP64 && xform_eo_supported(h->n);
+    const bool eo = prec == STH_FP64 && h->eo[0] && xform_eo_supported(h->n);
     const int sym = split_of(h, T);
     Timed tm(h, STH_K_XFORM_X, (eo || sym ? 1.0 : 2.0) * h->n * dof,
              dof * ((epi == 1 ? 24.0 : 16.0) - (io ? 4.0 : 0.0)), st);
@@ -392,7 +394,7 @@ static int xform_x(sth_handle* h, int prec, int epi, const double* in, double* o
 static int xform_s(sth_handle* h, int prec, const double* in, double* out, const double* T, long nbatch,
                    long inner, hipStream_t st, const int* guard = nullptr, int io_f32 = 0) {
     const double dof = (double)nbatch * h->n * inner;
-    const bool eo = prec == STH_FP64 && xform_eo_s_supported(h->n, inner);
+    const bool eo = prec == STH_FP64 && h->eo[0] && xform_eo_s_supported(h->n, inner);
     const int sym = split_of(h, T);
     Timed tm(h, STH_K_XFORM_S, (eo || sym ? 1.0 : 2.0) * h->n * dof,
              (io_f32 == 3 ? 8.0 : (io_f32 ? 12.0 : 16.0)) * dof, st);
@@ -407,7 +409,7 @@ static int xform_s(sth_handle* h, int prec, const double* in, double* out, const
 static hipError_t xform2d(sth_handle* h, int prec, bool fwd, int epi, const double* in, double* out, const double* A,
                           long rows, double alpha, hipStream_t st, const int* guard = nullptr, long ldi = 0,
                           long ldo = 0, int io_f32 = 0) {
-    if (prec == STH_FP64 && !io_f32)
+    if (prec == STH_FP64 && !io_f32 && h->eo[0])
         return launch_xform2d_eo(!fwd, epi, in, out, h->eo[(A == h->Tf ? 0 : 2) + (fwd ? 0 : 1)], h->n, rows, alpha,
                                  st, guard, ldi, ldo);
     return launch_xform2d(prec, fwd ? 0 : 1, epi, in, out, A, h->n, h->np, rows, alpha, st, guard, ldi, ldo, io_f32);
@@ -1299,7 +1301,7 @@ static size_t workspace_of(Problem q) {
     size_t total = 0;
     total += 2 * sizeof(double) * np * np;                   // transforms
     const bool onchip = cycles_on_chip(q, level_count(q)), batches = coefficient_batches(q, level_count(q));
-    total += (q.basis == 1 || batches ? 4 : 2) * sizeof(double) * xform_eo_pack_len((int)n);
+    if (q.prec == STH_FP64) total += (q.basis == 1 || batches ? 4 : 2) * sizeof(double) * xform_eo_pack_len((int)n);
     total += sizeof(double) * n * (1 + 2 * (2 * q.degree + 1));
     const bool f32 = f32_storage(q, level_count(q));
     // f^, u^ (x2 or 3)
@@ -1454,7 +1456,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     h->dim = q.dim;
     h->n = h->S.n;
     h->np = (h->n + 15) / 16 * 16;
-    h->split = h->np == h->n && xform_split_supported(h->n);
+    h->split = h->S.half > 0 && h->np == h->n && xform_split_supported(h->n);
     h->Nt = h->S.Nt;
     h->p = q.degree;
     h->Nx = (long)h->n * h->n * (q.dim == 3 ? h->n : 1);
@@ -1651,7 +1653,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
         }
     }
     // packed panels of the FP64 per-axis transforms
-    const size_t eo_len = xform_eo_pack_len(n);
+    const size_t eo_len = q.prec == STH_FP64 ? xform_eo_pack_len(n) : 0;
     std::vector<double> eo_host[4];
     for (int i = 0; i < (h->basis == 1 || h->batches ? 4 : 2) && eo_len > 0; ++i) {
         eo_host[i].assign(eo_len, 0.0);

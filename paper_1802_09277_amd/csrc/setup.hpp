@@ -81,7 +81,8 @@ struct Setup {
     Mat M1, K1, U;         // 1-D spatial matrices (interior), eigenvectors
     std::vector<double> mu;
     // ceil(n / 2): columns [0, half) of U are even and [half, n) odd under the
-    // reflection i -> n - 1 - i (each block in ascending mu)
+    // reflection i -> n - 1 - i (each block in ascending mu); 0 where U has no
+    // such order (reduced-precision transforms with an odd n)
     int half = 0;
     double m1_min = 0, m1_max = 0;   // extreme eigenvalues of M1 (eigenbasis iteration only)
     std::vector<TemporalLevel> levels;

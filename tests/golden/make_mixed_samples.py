@@ -26,6 +26,12 @@ CONFIGS = [
     # one axis at a time, widths padded to 112, 144 and 208
     ("solve", 2, 110, 2, 16, 1, 4, "bf16x3"), ("solve", 2, 143, 3, 8, 1, 2, "bf16x3"),
     ("solve", 2, 208, 2, 4, 1, 2, "bf16x3"),
+    # odd numbers of functions per axis
+    ("solve", 2, 107, 2, 8, 2, 128, "fp32"), ("solve", 2, 128, 3, 24, 1, 6, "bf16x3"),
+    ("solve", 2, 125, 2, 16, 2, 128, "bf16x3"), ("solve", 2, 12, 3, 10, 2, 128, "bf16x3"),
+    ("solve", 2, 21, 2, 24, 1, 128, "bf16x3"), ("solve", 3, 16, 3, 8, 2, 128, "bf16x3"),
+    ("solve", 3, 18, 3, 16, 3, 4, "fp32"), ("block_solve", 2, 36, 1, 6, 2, 128, "bf16x3"),
+    ("block_solve", 3, 9, 2, 4, 1, 128, "fp32"),
 ]
 
 
