@@ -555,11 +555,9 @@ hipError_t launch_cycles_table(int dim, int Nt, int L, const TimeMix* tm, const 
 #undef STH_TAB_NT
 }
 
-// sum j of the batch by block j (fixed order) to out[j] and the host, then a
-// completion mark of its own
+// sum j of the batch by block j (fixed order) to the host
 __global__ __launch_bounds__(256) void k_cycle_sums(const double* __restrict__ partial, long count,
-                                                    double* out_host, int* seq, int seq_val, SolveStart start,
-                                                    int nsums) {
+                                                    double* out_host, SolveStart start, int nsums) {
     __shared__ double red[4];
     const bool fin = (int)blockIdx.x == nsums;              // the solve's prologue
     const double* p = fin ? start.partial : partial + (long)blockIdx.x * count;
@@ -591,10 +589,6 @@ __global__ __launch_bounds__(256) void k_cycle_sums(const double* __restrict__ p
             start.flags[1] = nz ? 0 : 1;
         } else {
             out_host[blockIdx.x] = v;
-        }
-        if (seq) {
-            __threadfence_system();
-            seq[blockIdx.x] = seq_val;
         }
     }
 }
@@ -653,8 +647,8 @@ bool cycles_lines(int Nt, int L, long S) {
 
 hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega, long S, int m,
                          const double* rin, const double* fh, double* rout, double* uout, double* partial,
-                         long max_partial, double* out_host, int* seq, int seq_val, hipStream_t st, int vt, bool rin_lines,
-                         bool rout_lines, const SolveStart* start) {
+                         long max_partial, double* out_host, hipStream_t st, int vt, bool rin_lines, bool rout_lines,
+                         const SolveStart* start) {
     const int LA = cycles_lane_slabs(Nt, L, S);
     if (!LA || m < 0 || m > kMaxBatch || (L == 1 && m > 1)) return hipErrorInvalidValue;
     if (partial && 3L * (m + 1) * cycles_blocks(8, Nx) > max_partial) return hipErrorInvalidValue;
@@ -675,7 +669,7 @@ hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega
 #undef STH_CYC_NT
     if (e != hipSuccess || !partial) return e;
     hipLaunchKernelGGL(k_cycle_sums, dim3(3 * (m + 1) + (start ? 1 : 0)), dim3(256), 0, st, partial, blocks, out_host,
-                       seq, seq_val, start ? *start : SolveStart{}, 3 * (m + 1));
+                       start ? *start : SolveStart{}, 3 * (m + 1));
     return hipGetLastError();
 }
 

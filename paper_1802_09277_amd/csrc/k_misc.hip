@@ -20,11 +20,7 @@ __global__ __launch_bounds__(kSumThreads) void k_sum_partials(const double* __re
         // a skipped cycle stops the cycles guarded by its own flag too
         if (flag.dev && threadIdx.x == 0) {
             *flag.dev = 0;
-            if (flag.host) *flag.host = 0;
-            if (flag.seq) {
-                __threadfence_system();
-                *flag.seq = flag.seq_val;
-            }
+            if (flag.host) *flag.host = kFlagSkipped;
         }
         return;
     }
@@ -73,10 +69,6 @@ __global__ __launch_bounds__(kSumThreads) void k_sum_partials(const double* __re
         }
         *flag.dev = go;
         if (flag.host) *flag.host = go;
-        if (flag.seq) {
-            __threadfence_system();
-            *flag.seq = flag.seq_val;
-        }
     }
 }
 

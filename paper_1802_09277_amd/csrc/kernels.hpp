@@ -37,7 +37,7 @@ struct Transfer {               // 2Nt x Nt prolongation
 // host copy) when the lower bound of its B-spline residual,
 // max(nb_lo ||r^||^2, (1 - 1e-8) sum_m v_m r^_m^2), exceeds *thr =
 // (rtol ||f||)^2, and 0 otherwise (possible convergence, or non-finite); a
-// skipped sum stores 0.
+// skipped sum stores 0 (kFlagSkipped in the host copy).
 // With exact = 1 (sum of an exact B-spline norm) the flag is instead 1 when
 // the host will end the solve on it: ||r|| = sqrt(sum) is not finite or not
 // above thr[1] = rtol ||f||.
@@ -47,12 +47,16 @@ struct CycleFlag {
     const double* thr = nullptr;   // device pair: (rtol ||f||)^2, rtol ||f||
     double nb_lo = 0.0;
     int exact = 0;
-    // completion mark: after the outputs above, a system-scope fence and
-    // *seq = seq_val (mapped host memory) for a host that polls instead of
-    // waiting for an event
-    int* seq = nullptr;
-    int seq_val = 0;
 };
+
+// A host that polls instead of waiting for an event clears every mapped value
+// it is going to read (kNotYet, kNoFlagYet) before the launches that store them
+// and waits for each: values and a mark behind a system-scope fence may become
+// visible to the host in another order (in about 1 of 2000 solves the mark was
+// there before the sums, all of which were the previous batch's), one aligned
+// store of 8 bytes is there whole or not at all.
+constexpr unsigned long long kNotYet = 0x7ff8a5c35a3ca5c3ull;   // a NaN that no sum gives
+constexpr int kNoFlagYet = -1, kFlagSkipped = 2;                // kFlagSkipped: the cycle did not run, no sums
 
 // r = f + sign * (-(A u)_n + (B u)_{n-1}) for slabs [s0, s0+ns) of a vector
 // with slab length Nt*n^dim; the coupling uses slab s-1 of the same vector
@@ -249,12 +253,11 @@ hipError_t launch_eig_coarse_tail3(int dim, int Nt, const TimeMix* tma_dev, cons
 //  vw may be null when no sums are taken).  partial (may be null; max_partial
 //  entries, cycles_partials() suffice): sums 3 c .. 3 c + 2 of out_host
 //  (mapped pinned host memory) are ||r||^2 and its lower and upper
-//  mode-weighted forms after c = 0 .. m cycles; seq (may be null): after sum
-//  j, seq[j] = seq_val.  Vectors differ, except fh == rin.  rin_lines,
+//  mode-weighted forms after c = 0 .. m cycles.  Vectors differ, except fh == rin.  rin_lines,
 //  rout_lines: that vector is by time lines, an order for the batches'
 //  residuals between them (where cycles_lines allows it, of the same length).
 //  start (may be null; with sums): the last sum also finishes a solve's
-//  prologue, mark included: out[0] = ||f||^2 (also to out_host), flags[0] = 1 if
+//  prologue: out[0] = ||f||^2 (also to out_host), flags[0] = 1 if
 //  some entry of u is not zero (NaN included; also to flag_host), flags[1] = 1 -
 //  flags[0].
 constexpr int kMaxBatch = 8;
@@ -271,7 +274,7 @@ hipError_t launch_cycles_table(int dim, int Nt, int L, const TimeMix* tm, const 
                                long Nx, const Transfer& tr, const double* vw, double* tab, hipStream_t st);
 hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega, long S, int m,
                          const double* rin, const double* fh, double* rout, double* uout, double* partial,
-                         long max_partial, double* out_host, int* seq, int seq_val, hipStream_t st, int vt = 0,
+                         long max_partial, double* out_host, hipStream_t st, int vt = 0,
                          bool rin_lines = false, bool rout_lines = false, const SolveStart* start = nullptr);
 //  uout = L^{-1}(r - r_m), what m = steps damped block-Jacobi steps on the
 //  finest level add to the iterate of the residual r

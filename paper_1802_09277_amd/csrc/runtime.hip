@@ -39,7 +39,7 @@ static thread_local std::string g_err;
 constexpr int kNormSlots = 14;
 constexpr int slot_base(int slot) { return 2 + 3 * slot; }
 constexpr int kMixR = 11, kMixF = 12;
-constexpr int kCycSums = 3 * (kMaxBatch + 1) + 1;  // sums of a batch of cycles, and the solve's prologue
+constexpr int kCycSums = 3 * (kMaxBatch + 1);      // sums of a batch of cycles
 
 static int fail(int code, const std::string& msg) {
     g_err = msg;
@@ -99,9 +99,8 @@ struct sth_handle {
     double* cyc_tab = nullptr;          // per mode: its matrices on every level (launch_cycles_table)
     double* hcyc = nullptr;             // mapped, coherent: the sums of a batch
     double* hcyc_dev = nullptr;
-    int* hcseq = nullptr;               // and their completion marks
-    int* hcseq_dev = nullptr;
-    int wait_cyc = 0, wait_cyc_seq = 0; // marks the blocking solve waits for (0: none)
+    int wait_cyc = 0;                   // sums the blocking solve waits for (0: none)
+    bool wait_start = false;            // ... and the solve's prologue
     bool defer_close = false;           // set by a solve iteration: level 0 leaves its post-smoothing
     const double* pending_ec = nullptr; // coarse correction waiting for the fused cycle close
     // The solve loop's fused cycle closes do not store the cycle's result
@@ -214,7 +213,6 @@ struct sth_handle {
         int ecur0 = 0, pre_idx = 1;
         bool presmoothed = false;
         int slot = 0;
-        int seqv = 0;                   // completion mark of the cycle's final sum
         Unformed unf;
     };
     struct SolveState {
@@ -285,14 +283,12 @@ struct sth_handle {
     hipEvent_t evring[4] = {nullptr, nullptr, nullptr, nullptr};
     int evnext = 0;
     hipEvent_t wait_ev = nullptr;       // event the caller waits for before solve_continue
-    // or (wait_slot >= 0) the completion mark wait_seq in hseq[wait_slot]:
-    // the blocking solve with eager launches polls mapped memory instead of
+    // or (wait_slot >= 0) the sums and the flag of that norm slot: the
+    // blocking solve with eager launches polls mapped memory instead of
     // recording an event per cycle (an event record leaves the GPU idle for
     // a few microseconds at every cycle boundary)
-    int* hseq = nullptr;                // mapped, coherent: per norm slot, last completion mark
-    int* hseq_dev = nullptr;
-    int seq_counter = 0, last_seq = 0;
-    int wait_slot = -1, wait_seq = 0;
+    int wait_slot = -1;
+    bool wait_first = false;            // ... and the initial pass of a speculative solve
     bool want_poll = false, poll_seq = false;
 };
 
@@ -856,7 +852,7 @@ static int mode_cycle(sth_handle* h, const double* f, double* u, bool zero_guess
         const double dof = (double)S * slab_len(h);
         Timed tm(h, STH_K_EIG_CYCLE_CLOSE, dof * (13.4 * h->Nt + 19.0), dof * 24.0, st);
         HIPCHK(launch_cycles(h->Nt, h->L, h->cyc_tab, h->Nxe, h->omega, S, 1, a, a, nullptr, b, nullptr, 0, nullptr,
-                             nullptr, 0, st, false));
+                             st));
     }
     return spatial_apply(h, INV_U, b, u, rows, a, st, nullptr, STH_FP64, zero_guess ? 0 : 1, b);
 }
@@ -994,6 +990,14 @@ static int eig_vcycle(sth_handle* h, int lvl, bool zero_guess, hipStream_t st) {
     return STH_OK;
 }
 
+// Clears a norm slot and its flag for a host that polls them (kNotYet); the
+// last pass that stored there has been waited for.
+static void clear_value(double* p) { std::memcpy(p, &kNotYet, sizeof(double)); }
+static void clear_slot(sth_handle* h, int slot, int flag) {
+    for (int i = 0; i < 3; ++i) clear_value(h->hnorm + slot_base(slot) + i);
+    h->hflag[flag] = kNoFlagYet;
+}
+
 // ||r^||^2 of the residual r^ = f^ - L u^ of the current eigenbasis iterate
 // to the pinned host scalars of a norm slot (not synchronised).  With one
 // pre-smoothing step in the cycle and a level below, a single pass (the
@@ -1020,10 +1024,7 @@ static int eig_residual_cheap(sth_handle* h, hipStream_t st) {
         const int slot = nxt == 2 ? 1 : 0;
         CycleFlag flag;
         if (h->guard) flag = CycleFlag{h->dgo + slot, h->hflag_dev + slot, h->dthr, h->nb_lo};
-        if (flag.dev && h->poll_seq) {
-            flag.seq = h->hseq_dev + slot;
-            flag.seq_val = h->last_seq = ++h->seq_counter;
-        }
+        if (flag.dev && h->poll_seq) clear_slot(h, slot, slot);
         const int chain = chain_length(h, S, 65536);
         // in the solve loop the result is formed only if it is read
         const bool lazy = h->lazy_close;
@@ -1669,17 +1670,11 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     const unsigned mapped = hipHostMallocMapped | hipHostMallocCoherent;
     if (hipHostMalloc((void**)&h->hnorm, kNormSlots * sizeof(double), mapped) != hipSuccess ||
         hipHostMalloc((void**)&h->hflag, 5 * sizeof(int), mapped) != hipSuccess ||
-        hipHostMalloc((void**)&h->hseq, 2 * sizeof(int), mapped) != hipSuccess ||
-        hipHostMalloc((void**)&h->hcyc, kCycSums * sizeof(double), mapped) != hipSuccess ||
-        hipHostMalloc((void**)&h->hcseq, kCycSums * sizeof(int), mapped) != hipSuccess)
+        hipHostMalloc((void**)&h->hcyc, kCycSums * sizeof(double), mapped) != hipSuccess)
         return cleanup(STH_ENOMEM, "pinned host allocation failed");
-    for (int i = 0; i < kCycSums; ++i) h->hcseq[i] = 0;
-    h->hseq[0] = h->hseq[1] = 0;
     if (hipHostGetDevicePointer((void**)&h->hnorm_dev, h->hnorm, 0) != hipSuccess ||
         hipHostGetDevicePointer((void**)&h->hcyc_dev, h->hcyc, 0) != hipSuccess ||
-        hipHostGetDevicePointer((void**)&h->hcseq_dev, h->hcseq, 0) != hipSuccess ||
-        hipHostGetDevicePointer((void**)&h->hflag_dev, h->hflag, 0) != hipSuccess ||
-        hipHostGetDevicePointer((void**)&h->hseq_dev, h->hseq, 0) != hipSuccess)
+        hipHostGetDevicePointer((void**)&h->hflag_dev, h->hflag, 0) != hipSuccess)
         return cleanup(STH_EHIP, "pinned host memory is not mapped");
     if (hipMalloc((void**)&h->dgo, 8 * sizeof(int)) != hipSuccess ||
         hipMalloc((void**)&h->dthr, 2 * sizeof(double)) != hipSuccess)
@@ -2080,12 +2075,13 @@ static int solve_begin_impl(sth_handle* h, const double* f, double* u, double rt
     v.inner = inner_fn != nullptr;
     v.tprec = tprec;
     h->wait_cyc = 0;
+    h->wait_first = false;
     if ((h->basis == 1 ? h->cyc : h->batches) && rtol >= kCycMinRtol) return cyc_begin(h, inner_fn);
     // cycles enqueued ahead of their predecessor's norm (eigenbasis with the
     // fused cycle close; not while kernels are timed one by one)
     v.spec = h->basis == 1 && h->fuse_close && h->speculate && !h->timing;
-    // completion marks instead of per-cycle events: the blocking solve with
-    // eager launches (a captured graph would replay fixed marks)
+    // polled sums instead of per-cycle events: the blocking solve with eager
+    // launches
     h->poll_seq = h->want_poll && v.spec && !h->use_graph;
     h->wait_ev = nullptr;
     h->wait_slot = -1;
@@ -2100,6 +2096,7 @@ static int solve_begin_impl(sth_handle* h, const double* f, double* u, double rt
             Timed tm(h, STH_K_NORM, 2.0 * len, 8.0 * len, st);
             HIPCHK(launch_norm2(f, len, h->partial, h->dnorm + 1, st));
         }
+        if (h->poll_seq) clear_value(h->hnorm + 1);
         HIPCHK(hipMemcpyAsync(h->hnorm + 1, h->dnorm + 1, sizeof(double), hipMemcpyDeviceToHost, st));
     }
     int rc;
@@ -2160,6 +2157,7 @@ static int solve_begin_impl(sth_handle* h, const double* f, double* u, double rt
             HIPCHK(launch_spec_threshold(h->dthr, h->dnorm + 1, rtol, st));
         }
         h->first_flag = true;
+        if (h->poll_seq) clear_slot(h, 2, 3);
         rc = eig_residual_cheap(h, st);
         h->first_flag = false;
         if (rc) return rc;
@@ -2167,6 +2165,7 @@ static int solve_begin_impl(sth_handle* h, const double* f, double* u, double rt
         h->first_guard = true;
         if ((rc = spec_enqueue(h))) return rc;
         v.phase = 4;                    // (enqueue_iteration sets phase 1)
+        h->wait_first = h->wait_slot >= 0;
         return STH_OK;
     }
     return coefficient_begin(h);
@@ -2193,11 +2192,11 @@ static hipEvent_t next_event(sth_handle* h) {
 }
 
 static sth_handle::Snap take_snap(const sth_handle* h) {
-    return sth_handle::Snap{h->ecur[0], h->pre_idx, h->presmoothed, h->last_slot, h->last_seq, h->unformed};
+    return sth_handle::Snap{h->ecur[0], h->pre_idx, h->presmoothed, h->last_slot, h->unformed};
 }
 
 // Completion of the cycle just enqueued: an event, or nothing to record when
-// its final sum leaves a completion mark (poll_seq)
+// its final sum is polled for (poll_seq)
 static int mark_cycle(sth_handle* h, hipEvent_t* ev) {
     *ev = nullptr;
     if (h->poll_seq) return STH_OK;
@@ -2206,11 +2205,11 @@ static int mark_cycle(sth_handle* h, hipEvent_t* ev) {
     return STH_OK;
 }
 
-// the caller's next wait: for cycle s (its event or its completion mark)
+// the caller's next wait: for cycle s (its event or its norm slot)
 static void wait_for(sth_handle* h, const sth_handle::Snap& s, hipEvent_t ev) {
     h->wait_ev = ev;
     h->wait_slot = h->poll_seq ? s.slot : -1;
-    h->wait_seq = s.seqv;
+    h->wait_first = false;
 }
 
 static void put_snap(sth_handle* h, const sth_handle::Snap& s) {
@@ -2399,7 +2398,7 @@ static int solve_continue_spec(sth_handle* h, bool* more) {
     }
     v.rn = eig_lower_bound(h, slot);
     if (v.drain) return solve_finish(h, more);
-    const bool go = h->hflag[slot] != 0;
+    const bool go = h->hflag[slot] == 1;
     if (go) {
         if (v.growth >= 3 && v.pend) {
             // cycle b runs: take it as the last one
@@ -2488,21 +2487,25 @@ static int cyc_launch(sth_handle* h, int from, bool from_lines, int end, bool en
     auto& v = h->sv;
     h->tlev = 0;
     const double dof = (double)h->lev_S[0] * slab_len(h), eb = h->f32 ? 4.0 : 8.0;
-    if (sums && h->want_poll) ++h->seq_counter;
     if (end_lines) h->pad_dirty = h->Nxe != h->Nx;
     Timed tm(h, STH_K_EIG_CYCLE_CLOSE, dof * (m * (9.4 * h->Nt + 19.0) + (uout >= 0 ? 4.0 * h->Nt : 0.0)),
              dof * eb * (1.0 + (end >= 0 ? 1.0 : 0.0) + (uout >= 0 ? (from < 0 ? 1.0 : 2.0) : 0.0)), v.st);
     const SolveStart start{h->partial, h->dnorm + 1, h->hnorm_dev + 1, h->dgo + 6, h->hflag_dev + 4};
-    const bool fin = sums && v.prologue;
+    const bool fin = sums && v.prologue, poll = sums && h->want_poll;
+    for (int i = 0; poll && i < 3 * (m + 1); ++i) clear_value(h->hcyc + i);
+    if (poll && fin) {
+        clear_value(h->hnorm + 1);
+        h->hflag[4] = kNoFlagYet;
+    }
     HIPCHK(launch_cycles(h->Nt, h->L, h->cyc_tab, h->Nxe, h->omega, h->lev_S[0], m, cyc_buf(h, from), h->e0,
                          end >= 0 ? cyc_buf(h, end) : nullptr, uout >= 0 ? cyc_buf(h, uout) : nullptr,
-                         sums ? h->cpartial : nullptr, h->n_cpartial, h->hcyc_dev, sums && h->want_poll ? h->hcseq_dev : nullptr, h->seq_counter, v.st, h->f32,
-                         from_lines, end_lines, fin ? &start : nullptr));
+                         sums ? h->cpartial : nullptr, h->n_cpartial, h->hcyc_dev, v.st, h->f32, from_lines, end_lines,
+                         fin ? &start : nullptr));
     v.prologue = false;
     h->wait_ev = nullptr;
     h->wait_slot = -1;
-    h->wait_cyc = sums && h->want_poll ? 3 * (m + 1) + (fin ? 1 : 0) : 0;
-    h->wait_cyc_seq = h->seq_counter;
+    h->wait_cyc = poll ? 3 * (m + 1) : 0;
+    h->wait_start = fin;
     return STH_OK;
 }
 
@@ -2968,70 +2971,74 @@ hipEvent_t solve_wait_event(sth_handle* h) { return h->wait_ev; }
 
 extern "C" {
 
-// Waits until the final sum of the awaited cycle has left its completion
-// mark in mapped memory (it stores the mark after its norms and flag, behind
-// a system-scope fence).  After each millisecond of waiting it checks the
-// stream, so that a failed launch or a missing mark ends the wait with an
-// error; the check is rare because a stream query can itself put work
-// between the kernels.
-static int wait_mark(sth_handle* h, hipStream_t st) {
-    volatile int* p = h->hseq + h->wait_slot;
-    const int want = h->wait_seq;
-    auto last = std::chrono::steady_clock::now();
-    for (long spin = 1; *p != want; ++spin) {
+// Polls mapped memory until arrived().  After each millisecond of waiting it
+// checks the stream, so that a failed launch or a missing value ends the wait
+// with an error (a value of a stream that has ended is given one more second);
+// the check is rare because a stream query can itself put work between the
+// kernels.
+extern "C++" template <typename Arrived>
+static int poll_mapped(hipStream_t st, Arrived arrived) {
+    using clock = std::chrono::steady_clock;
+    auto last = clock::now(), ended = clock::time_point::max();
+    for (long spin = 1; !arrived(); ++spin) {
         if ((spin & 1023) != 0) continue;
-        const auto now = std::chrono::steady_clock::now();
-        if (now - last >= std::chrono::milliseconds(1)) {
-            last = now;
-            const hipError_t q = hipStreamQuery(st);
-            if (q == hipSuccess) {
-                if (*p == want) break;
-                return fail(STH_EHIP, "cycle completion mark not set");
-            }
-            if (q != hipErrorNotReady) return fail(STH_EHIP, std::string("stream work failed: ") + hipGetErrorString(q));
+        const auto now = clock::now();
+        if (now - last < std::chrono::milliseconds(1)) continue;
+        last = now;
+        if (ended != clock::time_point::max()) {
+            if (now - ended >= std::chrono::seconds(1)) return fail(STH_EHIP, "sums of a cycle did not reach the host");
+            continue;
         }
+        const hipError_t q = hipStreamQuery(st);
+        if (q == hipSuccess) ended = now;
+        else if (q != hipErrorNotReady)
+            return fail(STH_EHIP, std::string("stream work failed: ") + hipGetErrorString(q));
     }
     std::atomic_thread_fence(std::memory_order_acquire);
     return STH_OK;
 }
 
-// The same for the marks of a batch's sums.
-static int wait_cycle_marks(sth_handle* h, hipStream_t st) {
-    volatile int* p = h->hcseq;
-    const int want = h->wait_cyc_seq;
-    auto last = std::chrono::steady_clock::now();
-    int i = 0;                                       // marks seen so far
-    for (long spin = 1; i < h->wait_cyc; ++spin) {
-        while (i < h->wait_cyc && p[i] == want) ++i;
-        if ((spin & 1023) != 0 || i == h->wait_cyc) continue;
-        const auto now = std::chrono::steady_clock::now();
-        if (now - last >= std::chrono::milliseconds(1)) {
-            last = now;
-            const hipError_t q = hipStreamQuery(st);
-            if (q == hipSuccess) {
-                while (i < h->wait_cyc && p[i] == want) ++i;
-                if (i == h->wait_cyc) break;
-                return fail(STH_EHIP, "completion marks of a batch of cycles not set");
-            }
-            if (q != hipErrorNotReady) return fail(STH_EHIP, std::string("stream work failed: ") + hipGetErrorString(q));
-        }
-    }
-    std::atomic_thread_fence(std::memory_order_acquire);
-    return STH_OK;
+static bool value_there(const double* p) {
+    return *reinterpret_cast<const volatile unsigned long long*>(p) != kNotYet;
+}
+static int flag_now(const sth_handle* h, int i) { return *const_cast<const volatile int*>(h->hflag + i); }
+static bool slot_there(const sth_handle* h, int slot, int flag) {
+    const int f = flag_now(h, flag);
+    if (f == kNoFlagYet) return false;
+    for (int i = 0; f != kFlagSkipped && i < 3; ++i)
+        if (!value_there(h->hnorm + slot_base(slot) + i)) return false;
+    return true;
+}
+
+// the cycle of norm slot wait_slot (and the initial pass before it)
+static int wait_slot_sums(sth_handle* h, hipStream_t st) {
+    return poll_mapped(st, [&] {
+        return slot_there(h, h->wait_slot, h->wait_slot) &&
+               (!h->wait_first || (slot_there(h, 2, 3) && value_there(h->hnorm + 1)));
+    });
+}
+
+// the sums of a batch of cycles
+static int wait_cycle_sums(sth_handle* h, hipStream_t st) {
+    int i = 0;                                       // sums seen so far
+    return poll_mapped(st, [&] {
+        while (i < h->wait_cyc && value_there(h->hcyc + i)) ++i;
+        return i == h->wait_cyc && (!h->wait_start || (flag_now(h, 4) != kNoFlagYet && value_there(h->hnorm + 1)));
+    });
 }
 
 int sth_solve(sth_handle* h, const double* f, double* u, double rtol, int maxit, int* iters, double* relres,
               void* stream) {
     if (!h || !f || !u || !(rtol >= 0) || maxit < 0) return fail(STH_EINVAL, "bad argument");
     hipStream_t st = (hipStream_t)stream;
-    // completion marks instead of per-cycle events (also for the inner
-    // solves of a mixed-precision solve, which start inside the loop)
+    // polled sums instead of per-cycle events (also for the inner solves of
+    // a mixed-precision solve, which start inside the loop)
     h->want_poll = true;
     int rc = solve_begin(h, f, u, rtol, maxit, st);
     bool more = true;
     while (rc == STH_OK && more) {
-        if (h->wait_cyc > 0) rc = wait_cycle_marks(h, st);
-        else if (h->wait_slot >= 0) rc = wait_mark(h, st);
+        if (h->wait_cyc > 0) rc = wait_cycle_sums(h, st);
+        else if (h->wait_slot >= 0) rc = wait_slot_sums(h, st);
         else if (h->wait_ev) HIPCHK(hipEventSynchronize(h->wait_ev));
         else HIPCHK(hipStreamSynchronize(st));
         if (rc == STH_OK) rc = solve_continue(h, &more);
@@ -3068,7 +3075,7 @@ static int precondition(sth_handle* h, const double* v, double* z, hipStream_t s
         h->tlev = 0;
         Timed tm(h, STH_K_EIG_CYCLE_CLOSE, dof * (13.4 * h->Nt + 19.0), dof * 2.0 * (h->f32 ? 4.0 : 8.0), st);
         HIPCHK(launch_cycles(h->Nt, h->L, h->cyc_tab, h->Nxe, h->omega, h->lev_S[0], 1, h->e0, h->e0, nullptr,
-                             eig_u(h, 0, 0), nullptr, 0, nullptr, nullptr, 0, st, h->f32));
+                             eig_u(h, 0, 0), nullptr, 0, nullptr, st, h->f32));
     } else if ((rc = eig_vcycle(h, 0, true, st))) {
         return rc;
     }
@@ -3240,9 +3247,7 @@ int sth_destroy(sth_handle* h) {
             if (q) (void)hipFree(q);
     if (h->hnorm) (void)hipHostFree(h->hnorm);
     if (h->hflag) (void)hipHostFree(h->hflag);
-    if (h->hseq) (void)hipHostFree(h->hseq);
     if (h->hcyc) (void)hipHostFree(h->hcyc);
-    if (h->hcseq) (void)hipHostFree(h->hcseq);
     if (h->dthr) (void)hipFree(h->dthr);
     if (h->dmix) (void)hipFree(h->dmix);
     if (h->dgo) (void)hipFree(h->dgo);
