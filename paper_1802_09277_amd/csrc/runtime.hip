@@ -1250,8 +1250,14 @@ static bool f32_storage(const Problem& q, size_t levels) {
 // Whole cycles on chip: V(1,1) cycles, levels and time line within what a
 // block holds; in the B-spline coefficient iteration, whose cycle is the same
 // map between the spatial transforms, with exact FP64 slab inverses and
-// coarsening in time only
+// coarsening in time only.  Float vectors (the mixed form) only with FP32
+// transforms and degrees up to 2: on chip they are rounded in other places
+// than level by level, and the noise that the transforms leave in a result
+// follows each such rounding.  Measured over the two routes: 1e-9 to 5e-9 of
+// the solution with BF16x3, up to 5e-10 with FP32 and cubic or quartic splines,
+// below 5e-11 here.
 static bool cycles_on_chip(const Problem& q, size_t levels) {
+    if (f32_storage(q, levels) && (q.prec != STH_FP32 || q.degree > 2)) return false;
     return (q.basis == 1 || (q.prec == STH_FP64 && q.minres_iters == 0 && space_transition(q) == 0)) &&
            q.nu_pre == 1 && q.nu_post == 1 && cycles_supported(q.Nt(), (int)levels, q.n_slabs);
 }

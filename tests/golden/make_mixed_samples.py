@@ -32,6 +32,13 @@ CONFIGS = [
     ("solve", 2, 21, 2, 24, 1, 128, "bf16x3"), ("solve", 3, 16, 3, 8, 2, 128, "bf16x3"),
     ("solve", 3, 18, 3, 16, 3, 4, "fp32"), ("block_solve", 2, 36, 1, 6, 2, 128, "bf16x3"),
     ("block_solve", 3, 9, 2, 4, 1, 128, "fp32"),
+    # float eigenbasis vectors
+    ("solve", 3, 16, 3, 8, 2, 4, "bf16x3"), ("solve", 2, 116, 4, 8, 1, 4, "bf16x3"),
+    ("solve", 2, 90, 4, 8, 1, 4, "bf16x3"), ("solve", 2, 25, 3, 8, 2, 4, "bf16x3"),
+    ("solve", 2, 92, 2, 160, 1, 40, "bf16x3"), ("solve", 3, 16, 2, 16, 2, 4, "bf16x3"),
+    ("solve", 2, 128, 2, 64, 1, 16, "bf16x3"), ("solve", 3, 16, 2, 16, 2, 4, "fp32"),
+    ("solve", 2, 64, 2, 64, 1, 16, "fp32"), ("solve", 2, 62, 4, 64, 1, 16, "fp32"),
+    ("solve", 3, 27, 3, 24, 2, 4, "fp32"), ("solve", 2, 31, 3, 64, 2, 16, "fp32"),
 ]
 
 
