@@ -361,14 +361,14 @@ static hipError_t panel_go(const TI* in, TO* out, const double* T, int n, int np
         if (e != hipSuccess) return e;
         attr_set.store(true, std::memory_order_release);
     }
+    // Persistent blocks, 1, 2 or 4 per compute unit (4 x 8 waves = 32 waves): a
+    // multiple of 8 npanel, whose streams are whole (npanel may be 3, 5 or 7:
+    // widths 96, 160, 192, 224), no more than the tiles need.
     const long fit = (long)((160 * 1024) / shm);
-    // 1, 2 or 4 blocks per compute unit (4 x 8 waves = 32 waves): a power of
-    // two, so that halving below keeps a multiple of 8 npanel blocks
     const long per_cu = fit >= 4 ? 4 : (fit >= 2 ? 2 : 1);
-    // persistent blocks: a multiple of 8 npanel, no more than the tiles need
-    long blocks = 256 * per_cu;
-    const long need = ((ntiles + kPanelWaves - 1) / kPanelWaves) * npanel;
-    while (blocks > 8 * npanel && blocks / 2 >= need) blocks /= 2;
+    const long unit = 8L * npanel;
+    const long need = ((ntiles + kPanelWaves - 1) / kPanelWaves * npanel + unit - 1) / unit * unit;
+    const long blocks = std::min(need, std::max(unit, 256 * per_cu / unit * unit));
     hipLaunchKernelGGL((k_xform_panel<C, PW, XAXIS, EPI, TI, TO, SYM>), dim3((unsigned)blocks), dim3(kPanelThreads),
                        shm, st, in, out, T, n, np, npanel, nrows, inner, ntiles, alpha, guard);
     return hipGetLastError();
