@@ -239,8 +239,8 @@ struct sth_handle {
         // lower bound decides), the result added into u
         // batches of whole cycles (phase 10: batch enqueued, 11: exact norm of
         // a batch's residual): level-0 buffers of the batch's first and last
-        // residual and of the iterate formed with it (-1: f^, i.e. the initial
-        // residual; -2: none), its cycles, and whether it starts the solve
+        // residual and of the iterate formed with it (-1: f^, the residual of
+        // a zero guess; -2: none), its cycles, and whether it starts the solve
         bool cyc = false;
         int start = -1, end = 0, uout = -2, m = 0;
         int known = 0;                  // cycles of the batch whose sums have been tested already
@@ -249,6 +249,7 @@ struct sth_handle {
         bool start_lines = false;       // the first residual is by time lines (cyc_lines)
         bool nonzero = false;           // the initial guess has a nonzero entry
         bool restarted = false;         // the first batch was taken again from f - L u
+        bool at_guess = true;           // the batch starts from the residual of the guess
         bool prologue = false;          // the batch's sums finish the prologue
         bool inner = false;
         bool inner_store = false;       // the inner result is stored into u (u was zero), not added
@@ -2458,8 +2459,10 @@ static int solve_continue_spec(sth_handle* h, bool* more) {
 // up to kMaxBatch cycles on chip and returns the residual norms of each, which
 // go through the stopping test one after the other exactly as in the plain
 // loop.  The iterate that belongs to the residual the loop stops at is
-// L^{-1}(r^_0 - r^) on top of the initial guess.  A batch that ends past the
-// stopping cycle is taken again up to that cycle, from the same residual.
+// L^{-1}(f^ - r^), whatever the guess: its rounding is that of the iterate,
+// and none is left of a guess whose residual is far larger than f.  A batch
+// that ends past the stopping cycle is taken again up to that cycle, from the
+// same residual.
 // ---------------------------------------------------------------------------
 // Eigenbasis vector of a batch: -1 the initial residual, else the iterate
 // buffers.  The coefficient iteration has buf0, buf1 and, from the second
@@ -2524,6 +2527,7 @@ static int cyc_batch(sth_handle* h, int from, bool from_lines, int want, int kno
     v.m = std::max(0, std::min({want, h->L == 1 ? 1 : kMaxBatch, v.maxit - v.it + known}));
     if (!h->speculate) v.m = std::min(v.m, known + 1);
     v.mapped = false;
+    v.at_guess = v.at_guess && from == v.start;
     v.start = from;
     v.start_lines = from_lines;
     v.known = known;
@@ -2541,7 +2545,7 @@ static int cyc_finish(sth_handle* h, int j, bool* more) {
     *more = false;
     v.phase = 2;
     h->wait_cyc = 0;
-    if (j == 0 && v.start < 0 && !v.inner) {
+    if (j == 0 && v.at_guess && !v.inner) {
         // no cycle: u stays as it is (zero again where it was a work vector)
         if (h->basis == 0 || (v.mapped && !v.nonzero)) HIPCHK(launch_fill(v.u, h->lev_S[0] * slab_len(h), 0.0, v.st));
         return STH_OK;
@@ -2557,7 +2561,7 @@ static int cyc_finish(sth_handle* h, int j, bool* more) {
     }
     h->wait_cyc = 0;                    // (a launch above sets it)
     if (v.mapped && u == v.uout && j == v.m && !v.nonzero) return STH_OK;
-    const bool add = v.inner ? !v.inner_store : v.nonzero;
+    const bool add = v.inner && !v.inner_store;
     return spatial_apply(h, INV_U, cyc_buf(h, u), v.u, h->lev_S[0] * h->Nt, h->basis == 0 ? h->e0 : h->buf0, v.st,
                          nullptr, v.tprec, add ? 1 : 0, h->buf1, h->f32 ? 1 : 0);
 }
@@ -2578,6 +2582,7 @@ static int cyc_exact(sth_handle* h, int j) {
     }
     v.start = v.end = at;
     v.start_lines = false;
+    v.at_guess = v.at_guess && j == 0;
     v.m = 0;
     v.phase = 11;
     h->wait_cyc = 0;
@@ -2631,17 +2636,25 @@ static int cyc_begin(sth_handle* h, const double* inner_fn) {
     return STH_OK;
 }
 
-// The first batch again, from the residual of a guess that is not zero.
+// The first batch again, from the residual of a guess that is not zero (a
+// vector of its own: f^ stays for the iterate).  On one level, whose cycle is
+// the exact solve whatever the guess, its norms only: the cycle itself starts
+// from f^ (cyc_one_level), whose rounding is not the guess's.
 static int cyc_restart(sth_handle* h) {
     auto& v = h->sv;
     if (h->basis == 0) return coefficient_begin(h);      // (u holds the guess: no third buffer)
     const long rows = h->lev_S[0] * h->Nt;
     int rc;
     if ((rc = residual(h, 0, v.f, v.u, h->buf1, 0, h->lev_S[0], 1.0, v.st))) return rc;
-    if ((rc = spatial_apply(h, FWD_U, h->buf1, h->e0, rows, h->buf0, v.st))) return rc;
-    v.first = v.restarted = true;
-    return cyc_batch(h, -1, false, first_batch(v.rtol), 0, h->L == 1);
+    // (the transform leaves padded modes alone)
+    if (h->pad_dirty) HIPCHK(launch_fill(cyc_buf(h, 0), h->lev_S[0] * eslab_len(h), 0.0, v.st));
+    if ((rc = spatial_apply(h, FWD_U, h->buf1, cyc_buf(h, 0), rows, h->buf0, v.st))) return rc;
+    v.first = v.restarted = v.at_guess = true;
+    v.start = 0;
+    return cyc_batch(h, 0, false, h->L == 1 ? 0 : first_batch(v.rtol), 0, false);
 }
+
+static bool cyc_one_level(const sth_handle* h) { return h->L == 1 && h->sv.restarted && h->sv.at_guess; }
 
 static int cyc_continue(sth_handle* h, bool* more) {
     auto& v = h->sv;
@@ -2654,7 +2667,7 @@ static int cyc_continue(sth_handle* h, bool* more) {
         if (!(v.rn > target()) || !std::isfinite(v.rn) || v.it >= v.maxit || v.growth >= 3) {
             return cyc_finish(h, 0, more);            // (the current batch is empty)
         }
-        return cyc_batch(h, v.start, false, 1, 0, true);
+        return cyc_batch(h, cyc_one_level(h) ? -1 : v.start, false, 1, 0, true);
     }
     const double* q = h->hcyc;
     int j = 0;
@@ -2697,6 +2710,7 @@ static int cyc_continue(sth_handle* h, bool* more) {
         }
         return cyc_exact(h, j);
     }
+    if (cyc_one_level(h)) return cyc_batch(h, -1, false, 1, 0, true);
     // Not converged: as many cycles as the last contraction asks for.  On
     // large vectors (a batch's transfers, 16 B per unknown, cost more than a
     // launch and a host round trip) all but two of them first: the contraction
