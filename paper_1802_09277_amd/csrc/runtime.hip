@@ -139,6 +139,7 @@ struct sth_handle {
     double* kc = nullptr;               // projection coefficients and squared norm (kKrylovScalars)
     double* kpart = nullptr;            // 1024 x kMaxKrylov partial sums
     double* khost = nullptr;            // pinned copy of kc
+    double kappa = 1.0;                 // ratio of the extreme eigenvalues of the spatial pencil
     double nb_lo = 0.0;                 // ||(I (x) C) r^||^2 >= nb_lo ||r^||^2
     double nb_hi = 0.0;                 // ||(I (x) C) r^||^2 <= nb_hi ||r^||^2
     double* vw = nullptr;               // per axis and 1-D mode: G_jj and sum_k |G_jk| (G = C^T C)
@@ -1479,6 +1480,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
         return fail(STH_EINVAL, "iterate_basis must be 0 or 1");
     }
     h->L = (int)h->S.levels.size();
+    h->kappa = *std::max_element(h->S.mu.begin(), h->S.mu.end()) / *std::min_element(h->S.mu.begin(), h->S.mu.end());
     h->nb_lo = std::pow(h->S.m1_min, h->dim);
     h->nb_hi = std::pow(h->S.m1_max, h->dim);
     h->fuse_close = fused_cycle_close(q, (size_t)h->L);
@@ -2043,6 +2045,18 @@ static int cyc_continue(sth_handle* h, bool* more);
 // ||f|| (64 x 64 elements, p = 3, 256 slabs; 5e-14 with p = 4 and 256 x 256, 2e-15
 // to 2e-14 elsewhere), at 1e-12 still a fraction of the tolerance.
 constexpr double kCycMinRtol = 1e-12;
+// The coefficient iteration stops on the residual of the coefficients
+// themselves.  Formed once, from a carried residual, they leave their own
+// rounding in it: up to 2 eps kappa ||f||, kappa the ratio of the extreme
+// spatial eigenvalues (loads of the lowest modes: 2.2e-11 with 256 elements and
+// p = 2, 3.4e-11 with 250 and p = 1; eps kappa 1.5e-11 and 1.7e-11).  Where that
+// may be more than a fiftieth of the tolerance (1.5e-9 there, 1.2e-10 with 60
+// elements and p = 3), single cycles between the transforms take its place.
+// The eigenbasis iteration stops on the residual of its own iterate u^, which
+// has no such part.
+static double cyc_min_rtol(const sth_handle* h) {
+    return h->basis == 1 ? kCycMinRtol : std::max(kCycMinRtol, 100.0 * 2.2e-16 * h->kappa);
+}
 // Cycles of a solve's first batch, before its contraction is known: about
 // three quarters of what a residual reduction of 0.17 per cycle takes to
 // rtol (V(1,1) cycles need 10 to 14 to 1e-8; the last batch then starts from a
@@ -2083,7 +2097,7 @@ static int solve_begin_impl(sth_handle* h, const double* f, double* u, double rt
     v.tprec = tprec;
     h->wait_cyc = 0;
     h->wait_first = false;
-    if ((h->basis == 1 ? h->cyc : h->batches) && rtol >= kCycMinRtol) return cyc_begin(h, inner_fn);
+    if ((h->basis == 1 ? h->cyc : h->batches) && rtol >= cyc_min_rtol(h)) return cyc_begin(h, inner_fn);
     // cycles enqueued ahead of their predecessor's norm (eigenbasis with the
     // fused cycle close; not while kernels are timed one by one)
     v.spec = h->basis == 1 && h->fuse_close && h->speculate && !h->timing;

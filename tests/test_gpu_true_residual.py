@@ -45,3 +45,19 @@ def test_from_a_large_guess(shape, basis):
     v = u.clone()
     it, _, _ = s.solve(f, v, rtol=1e-9, maxit=80)
     assert it == 0 and torch.equal(u, v)
+
+
+@pytest.mark.parametrize("basis,rtols", [("eigen", (1e-8, 1e-10)), ("nodal", (1e-8, 1e-10, 1e-12))])
+@pytest.mark.parametrize("shape", FINE)
+def test_smooth_load(shape, basis, rtols):
+    print(f"[gpu-true-residual] load {shape} {basis}", flush=True)
+    s = _solver(shape, basis)
+    f = s.load_rhs(W.manufactured_modes(s.dim), s.new_vector())
+    for rtol in rtols:
+        u = s.new_vector()
+        it, rr, code = s.solve(f, u, rtol=rtol, maxit=80, check=False)
+        true = _relres(s, f, u)
+        print(f"  rtol {rtol}: {it} cycles, reported {rr:.2e}, true {true:.2e}")
+        assert code == 0 and true <= rtol
+        if basis == "nodal":                # (exact norms are reported)
+            assert abs(rr - true) <= 1e-2 * true
