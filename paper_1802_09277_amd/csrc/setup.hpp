@@ -84,7 +84,7 @@ struct Setup {
     // reflection i -> n - 1 - i (each block in ascending mu); 0 where U has no
     // such order (reduced-precision transforms with an odd n)
     int half = 0;
-    double m1_min = 0, m1_max = 0;   // extreme eigenvalues of M1 (eigenbasis iteration only)
+    double m1_min = 0, m1_max = 0;   // extreme eigenvalues of M1 (coefficient iteration: bounds of them)
     std::vector<TemporalLevel> levels;
 };
 

@@ -61,3 +61,21 @@ def test_smooth_load(shape, basis, rtols):
         assert code == 0 and true <= rtol
         if basis == "nodal":                # (exact norms are reported)
             assert abs(rr - true) <= 1e-2 * true
+
+
+def test_rough_load_in_batches():
+    """Quartic splines and a rough right-hand side: the mode-weighted bound of
+    the residual norm is negative, the eigenvalues of M_1 bound it, and a solve
+    takes a few batches with an exact norm near the end instead of one batch and
+    one exact norm for every cycle."""
+    s = _solver((2, 20, 4, 64, 1, 16), "nodal")
+    f = torch.from_numpy(np.random.default_rng(2).standard_normal(s.vector_len)).cuda()
+    u = s.new_vector()
+    s.solve(f, u, rtol=1e-8)
+    s.timing(1 << 11 | 1 << 13)
+    it, _, _ = s.solve(f, u.zero_(), rtol=1e-8)
+    batches = s.timing_report("eig_cycle_close")["launches"]
+    norms = s.timing_report("resnorm")["launches"]
+    s.timing(0)
+    print(f"  {it} cycles, {batches} batches, {norms} exact norms")
+    assert it >= 9 and norms <= 5 and batches <= 8
