@@ -1115,7 +1115,10 @@ int build_setup(const Problem& p, Setup& s, std::string& err) {
     // 40 ms for the eigenvalues).
     if (p.basis == 0) eigenvalue_bounds(s.M1, p.degree, s.m1_min, s.m1_max);
     if (p.prec == 0) {
-        if (!reflection_symmetric(s.M1, 1e-9) || !reflection_symmetric(s.K1, 1e-9)) {
+        // (the rounding of the knots, i / n_elem each, in elements of 1 / n_elem:
+        // measured up to 3.8 n eps for 2 to 3000 elements and all degrees)
+        const double tol = 16.0 * s.n * 2.2e-16;
+        if (!reflection_symmetric(s.M1, tol) || !reflection_symmetric(s.K1, tol)) {
             err = "1-D matrices of the uniform mesh are not symmetric under reflection";
             return -5;
         }
