@@ -3068,6 +3068,11 @@ int sth_solve(sth_handle* h, const double* f, double* u, double rtol, int maxit,
     // polled sums instead of per-cycle events (also for the inner solves of
     // a mixed-precision solve, which start inside the loop)
     h->want_poll = true;
+    // nothing to wait for is left of a solve that ended with an error
+    h->wait_cyc = 0;
+    h->wait_first = h->wait_start = false;
+    h->wait_slot = -1;
+    h->wait_ev = nullptr;
     int rc = solve_begin(h, f, u, rtol, maxit, st);
     bool more = true;
     while (rc == STH_OK && more) {
@@ -3079,7 +3084,10 @@ int sth_solve(sth_handle* h, const double* f, double* u, double rtol, int maxit,
     }
     h->want_poll = false;
     h->poll_seq = false;
-    if (rc) return rc;
+    if (rc) {
+        (void)hipStreamSynchronize(st);     // nor work that stores sums a later solve polls for
+        return rc;
+    }
     HIPCHK(hipStreamSynchronize(st));
     return solve_result(h, iters, relres);
 }
