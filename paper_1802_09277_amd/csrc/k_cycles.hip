@@ -406,8 +406,34 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_
 
     sums(0);
     if constexpr (ONE) {
+        if (a.steps) {
+            // what the steps add to the iterate, omega A^{-1} (r_0 + .. of each
+            // step): local to a slab and those that its steps reach, so that
+            // infinities and NaN go no further than step by step
+            double z[LA][NT];
+#pragma unroll
+            for (int i = 0; i < LA; ++i)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) z[i][t] = r[i][t];
 #pragma unroll 1
-        for (int i = 0; i < a.steps; ++i) smooth();
+            for (int i = 1; i < a.steps; ++i) {
+                smooth();
+#pragma unroll
+                for (int j = 0; j < LA; ++j)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) z[j][t] += r[j][t];
+            }
+            const uptr inv0 = mat(0);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int k = 0; k < NT; ++k) {
+                    const double c = om * inv0[t * NT + k];
+#pragma unroll
+                    for (int i = 0; i < LA; ++i) r[i][t] = k ? r[i][t] + c * z[i][k] : c * z[i][0];
+                }
+            write(a.uout, [&](int k) { return r[k / NT][k % NT]; });
+        }
         if (a.m > 0) {
             double e[LA][NT];
 #pragma unroll
@@ -500,7 +526,7 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_
     } else if (a.rout) {
         write(a.rout, [&](int k) { return r[k / NT][k % NT]; });
     }
-    if (a.uout && (!ONE || a.m == 0)) {
+    if (a.uout && (!ONE || (a.m == 0 && !a.steps))) {
         // the iterate of this residual: u^ = L^{-1}(f^ - r^)
         read(a.fh, [&](int e, double v) { r[e / NT][e % NT] = v - r[e / NT][e % NT]; });
         exact(r, 0);
@@ -626,7 +652,7 @@ static hipError_t cycles_launch(const CycArgs& a, int LA, long* blocks, hipStrea
 
 hipError_t launch_smoothing(int Nt, int L, const double* tab, long Nx, double omega, long S, int steps,
                             const double* r, double* uout, hipStream_t st) {
-    const int LA = cycles_lane_slabs(Nt, L, S);
+    const int LA = cycles_lane_slabs(Nt, 1, S);      // (no levels: as many lanes as there are slabs)
     if (!LA || steps < 1 || r == uout) return hipErrorInvalidValue;
     const CycArgs a{L, 0, steps, 0, 0, S, Nx, omega, tab, r, r, nullptr, uout, nullptr};
     long blocks = 0;

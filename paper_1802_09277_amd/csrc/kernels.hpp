@@ -276,8 +276,8 @@ hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega
                          const double* rin, const double* fh, double* rout, double* uout, double* partial,
                          long max_partial, double* out_host, hipStream_t st, int vt = 0,
                          bool rin_lines = false, bool rout_lines = false, const SolveStart* start = nullptr);
-//  uout = L^{-1}(r - r_m), what m = steps damped block-Jacobi steps on the
-//  finest level add to the iterate of the residual r
+//  uout: what `steps` damped block-Jacobi steps on the finest level add to the
+//  iterate of the residual r
 hipError_t launch_smoothing(int Nt, int L, const double* tab, long Nx, double omega, long S, int steps,
                             const double* r, double* uout, hipStream_t st);
 //  rh = fh - L uh

@@ -835,7 +835,7 @@ static int spatial_apply(sth_handle* h, SpatialKind kind, const double* in, doub
 // x 101 x 300 x 3 unknowns 1236 us, now 384).  From a zero guess r = f;
 // have_r: buf1 holds f - L u already.  buf0 and buf1 are the work vectors.
 // steps > 0: that many smoothing steps instead of a cycle (two at 22^3 x 50 x
-// 4 unknowns 246 -> 127 us: the second residual and its transforms go).
+// 4 unknowns 246 -> 125 us: the second residual and its transforms go).
 static int mode_cycle(sth_handle* h, const double* f, double* u, bool zero_guess, bool have_r, hipStream_t st,
                       int steps) {
     const long S = h->lev_S[0], rows = S * h->Nt;
