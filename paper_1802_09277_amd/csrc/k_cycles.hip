@@ -544,7 +544,7 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_
 
 // Slabs per lane: the fewest that hold the line and divide into its levels;
 // 16 (N_t <= 3: 96 registers of residual and 84 of coarse levels) at most.
-static int cycles_lane_slabs(int Nt, int L, long S) {
+int cycles_lane_slabs(int Nt, int L, long S) {
     if (Nt < 2 || Nt > 6 || L < 1 || L > 4 || S < 1) return 0;
     int LA = 1;
     while (LA < (1 << (L - 1)) || 64L * LA < S) LA *= 2;

@@ -266,6 +266,7 @@ struct SolveStart {
     double *out, *out_host;
     int *flags, *flag_host;
 };
+int cycles_lane_slabs(int Nt, int L, long S);  // slabs of a line per lane of its wave; 0: not supported
 bool cycles_supported(int Nt, int L, long S);
 bool cycles_lines(int Nt, int L, long S);
 long cycles_partials(long Nx);

@@ -1249,6 +1249,29 @@ static bool f32_storage(const Problem& q, size_t levels) {
            ((q.dim == 2 && xform2d_supported(np)) || xform_panel_f32_io(np));
 }
 
+// Whether whole cycles on chip are faster than the passes level by level.  A
+// wave takes the time line of one mode in 64 lanes, LA slabs to a lane, however
+// few slabs there are: about 5 N_t + 10 multiply-adds for each of its LA N_t
+// values per lane, 3.4e-6 us each over the card.  The passes move 40 B per
+// unknown (20 in float) and cost about 9 us of launches per level.  Level by
+// level from 85 % of their time on: 262144 modes x 8 slabs x 4, four levels
+// (one lane) 2.3 ms a solve against 11.8 on chip, 66564 x 64 x 6 (8 lanes) 8.0
+// against 10.4, 16384 x 16 x 4 0.52 against 0.83; on chip 4225 x 8 x 4 (one
+// lane) 0.26 ms against 0.68, 16641 x 72 x 6 2.1 against 3.2.  One level, whose cycle is
+// the exact solve, pays for its table with few modes or 16 slabs: 262144 modes
+// x 1 x 4 203 us against 284 on chip, x 16 x 4 724 against 645, 65536 x 1 x 4
+// 140 against 116.  The coefficient iteration's passes transform on every
+// level, so that several levels are always faster on chip (262144 x 8 x 4 21 ms
+// against 17).
+static bool cycles_pay(const Problem& q, size_t levels, bool f32) {
+    const double modes = std::pow((double)q.n(), q.dim), Nt = q.Nt(), S = q.n_slabs;
+    if (levels == 1) return S >= 16 || modes <= 65536;
+    if (q.basis == 0) return true;
+    const double on = 3.4e-6 * modes * cycles_lane_slabs(q.Nt(), (int)levels, q.n_slabs) * Nt * (5.0 * Nt + 10.0);
+    const double off = (f32 ? 20.0 : 40.0) * S * Nt * modes / 4.5e6 + 9.0 * levels;
+    return on <= 0.85 * off;
+}
+
 // Whole cycles on chip: V(1,1) cycles, levels and time line within what a
 // block holds; in the B-spline coefficient iteration, whose cycle is the same
 // map between the spatial transforms, with exact FP64 slab inverses and
@@ -1260,8 +1283,10 @@ static bool f32_storage(const Problem& q, size_t levels) {
 // below 5e-11 here.
 static bool cycles_on_chip(const Problem& q, size_t levels) {
     if (f32_storage(q, levels) && (q.prec != STH_FP32 || q.degree > 2)) return false;
+    if (!q.on_chip) return false;
     return (q.basis == 1 || (q.prec == STH_FP64 && q.minres_iters == 0 && space_transition(q) == 0)) &&
-           q.nu_pre == 1 && q.nu_post == 1 && cycles_supported(q.Nt(), (int)levels, q.n_slabs);
+           q.nu_pre == 1 && q.nu_post == 1 && cycles_supported(q.Nt(), (int)levels, q.n_slabs) &&
+           cycles_pay(q, levels, f32_storage(q, levels));
 }
 
 // ... and whole solves of the coefficient iteration in batches of them: with
@@ -1287,16 +1312,19 @@ static size_t cycle_partials(const Problem& q, size_t levels, long modes) {
 
 static size_t workspace_of(Problem q);
 
-int sth_workspace_bytes(const sth_problem* p, size_t* bytes) {
+int sth_workspace_bytes(const sth_problem* p, size_t* bytes) { return workspace_for(p, true, bytes); }
+
+}  // extern "C"
+
+int sth::workspace_for(const sth_problem* p, bool on_chip, size_t* bytes) {
     if (!p || !bytes) return fail(STH_EINVAL, "null argument");
     Problem q = to_problem(p);
     std::string e = validate(q);
     if (!e.empty()) return fail(STH_EINVAL, e);
+    q.on_chip = on_chip;
     *bytes = workspace_of(q);
     return STH_OK;
 }
-
-}  // extern "C"
 
 // device bytes of the setup of q and of the problems below it on coarser
 // spatial meshes (the same allocations as setup_problem)
@@ -1368,7 +1396,11 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out);
 
 extern "C" {
 
-int sth_setup(const sth_problem* p, void* stream, sth_handle** out) {
+int sth_setup(const sth_problem* p, void* stream, sth_handle** out) { return setup_for(p, true, stream, out); }
+
+}  // extern "C"
+
+int sth::setup_for(const sth_problem* p, bool on_chip, void* stream, sth_handle** out) {
     if (!p || !out) return fail(STH_EINVAL, "null argument");
     *out = nullptr;
     Problem q = to_problem(p);
@@ -1382,10 +1414,17 @@ int sth_setup(const sth_problem* p, void* stream, sth_handle** out) {
         const int rc = scratch_address(&scr);
         if (rc != STH_OK) return rc;
     }
-    return setup_problem(q, (hipStream_t)stream, out);
+    q.on_chip = on_chip;
+    int rc = setup_problem(q, (hipStream_t)stream, out);
+    if (rc == STH_ENOMEM && q.on_chip) {
+        // without the tables of cycles on chip, which may be larger than the
+        // vectors of few slabs
+        (void)hipGetLastError();
+        q.on_chip = false;
+        rc = setup_problem(q, (hipStream_t)stream, out);
+    }
+    return rc;
 }
-
-}  // extern "C"
 
 // The problem on the halved spatial mesh below the last level of h (a
 // space-time coarsening step): n_elem / 2 elements per axis, half the slabs

@@ -73,6 +73,7 @@ struct Request {
     int maxit = 0;
     double* u_out = nullptr;
     size_t vec_len = 0, footprint = 0;
+    bool on_chip = true;            // the setup may hold tables of whole cycles on chip
     std::string key;
     std::atomic<St> state{St::Pending};
     Entry* entry = nullptr;
@@ -181,7 +182,7 @@ int prepare(sth_server* s, Request* r, std::string& msg) {
     Entry* e = r->entry;
     int rc;
     if (!e->h) {
-        if ((rc = sth_setup(&r->prob, (void*)s->setup_st, &e->h))) {
+        if ((rc = sth::setup_for(&r->prob, r->on_chip, (void*)s->setup_st, &e->h))) {
             msg = sth_last_error();
             return rc;
         }
@@ -444,6 +445,12 @@ int sth_server_submit(sth_server* s, const sth_problem* p, const sth_rhs_modes* 
     r->prob = *p;
     r->vec_len = sth_problem_vector_len(p);
     r->footprint = ws + 2 * r->vec_len * sizeof(double);
+    if (r->footprint > s->budget) {
+        // a budget for the passes level by level is enough
+        if ((rc = sth::workspace_for(p, false, &ws))) return rc;
+        r->on_chip = false;
+        r->footprint = ws + 2 * r->vec_len * sizeof(double);
+    }
     if (r->footprint > s->budget) return STH_ENOMEM;
     const int M = rhs->n_modes;
     r->amp.assign(rhs->amp, rhs->amp + M);

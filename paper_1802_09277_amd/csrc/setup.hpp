@@ -56,6 +56,7 @@ struct Problem {
     double space_ratio = 0.0;   // > 0: coarsen in space too where tau_l / h_l^2 >= space_ratio
     int level_cap = 0;     // > 0: at most this many levels of this spatial mesh
     int minres_iters = 0;  // > 0: smoother slab inverse by this many MinRes iterations per pair
+    bool on_chip = true;   // whole cycles on chip, whose tables take device memory, where they pay
     int n() const { return n_elem + degree - 2; }
     int Nt() const { return n_elem_t + degree; }
     double tau() const { return T / n_slabs; }

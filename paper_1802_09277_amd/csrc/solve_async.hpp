@@ -8,6 +8,12 @@
 
 namespace sth {
 
+// sth_setup and sth_workspace_bytes; on_chip false: without the tables of whole
+// cycles on chip, the passes level by level in their place (sth_setup itself
+// falls back to them where device memory is short).
+int setup_for(const sth_problem* p, bool on_chip, void* stream, sth_handle** out);
+int workspace_for(const sth_problem* p, bool on_chip, size_t* bytes);
+
 // ||f||^2 and the residual norm^2 of the initial guess u to pinned host
 // scalars; starts a solve of L_h u = f to rtol within maxit cycles.
 int solve_begin(sth_handle* h, const double* f, double* u, double rtol, int maxit, hipStream_t st);
