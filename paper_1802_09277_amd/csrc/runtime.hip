@@ -67,7 +67,8 @@ struct sth_handle {
     std::vector<TimeOp> ops;
     std::vector<TimeMix> mixes;
     Transfer tr{};
-    // device data
+    // device data, in three allocations
+    double *tables = nullptr, *work = nullptr, *zeros = nullptr;
     double* Tf = nullptr;               // np x np, U padded  (forward: r^ = U^T r)
     double* Ti = nullptr;               // np x np, U^T padded (inverse: z = U z^)
     // packed FP64 panels of U forward, inverse, C forward, inverse (FP64
@@ -1488,6 +1489,24 @@ static int attach_coarse_space(sth_handle* h, const Problem& q, hipStream_t s) {
     return STH_OK;
 }
 
+// Several arrays in one allocation, at multiples of 256 bytes.
+struct DeviceBlock {
+    std::vector<std::pair<void**, size_t>> arrays;
+    size_t count = 0;                   // doubles
+    template <typename T> size_t add(T** ptr, size_t doubles) {
+        const size_t at = (count + 31) / 32 * 32;
+        arrays.emplace_back((void**)ptr, at);
+        count = at + std::max<size_t>(doubles, 1);
+        return at;
+    }
+    bool allocate(double** base) {
+        if (arrays.empty()) return true;
+        if (hipMalloc((void**)base, count * sizeof(double)) != hipSuccess) return false;
+        for (auto& a : arrays) *a.first = *base + a.second;
+        return true;
+    }
+};
+
 static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     *out = nullptr;
     // levels on this spatial mesh (all of them unless the hierarchy
@@ -1607,46 +1626,53 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     auto dalloc = [&](double** ptr, size_t count) -> bool {
         return hipMalloc((void**)ptr, std::max<size_t>(count, 1) * sizeof(double)) == hipSuccess;
     };
+    // Three allocations for all of it, and one copy: each costs microseconds
+    // that a small problem's setup has no use for.
+    DeviceBlock tables, work, zeros;    // uploaded first, then scratch; not initialised; cleared
+    std::vector<double> upload;
+    auto table = [&](auto** ptr, const void* src, size_t bytes) {
+        const size_t at = tables.add(ptr, (bytes + 7) / 8);
+        upload.resize(tables.count, 0.0);
+        if (src) std::memcpy(&upload[at], src, bytes);
+    };
+    const auto table_of = [&](double** ptr, const std::vector<double>& v) { table(ptr, v.data(), v.size() * sizeof(double)); };
     // buffers both iterations use hold either layout
     const long slab = h->basis == 1 ? std::max(slab_len(h), eslab_len(h)) : slab_len(h);
     const long eslab = eslab_len(h);
-    if (!dalloc(&h->Tf, (size_t)np * np) || !dalloc(&h->Ti, (size_t)np * np) || !dalloc(&h->mu1, n) ||
-        !dalloc(&h->M1b, (size_t)n * B) || !dalloc(&h->K1b, (size_t)n * B) ||
-        !dalloc(&h->buf0, (size_t)q.n_slabs * slab) || !dalloc(&h->buf1, (size_t)q.n_slabs * slab) ||
-        !dalloc(&h->partial, 2 * kNormBlocks) || !dalloc(&h->dnorm, kNormSlots) ||
-        !dalloc(&h->dktmt, (size_t)h->L * 2 * kNt * kNt))
-        return cleanup(STH_ENOMEM, "device allocation failed");
     std::vector<double> ktmt((size_t)h->L * 2 * kNt * kNt);
     for (int l = 0; l < h->L; ++l) {
         std::memcpy(&ktmt[(size_t)l * 2 * kNt * kNt], h->ops[l].Kt, sizeof(double) * kNt * kNt);
         std::memcpy(&ktmt[(size_t)l * 2 * kNt * kNt + kNt * kNt], h->ops[l].Mt, sizeof(double) * kNt * kNt);
     }
+    table_of(&h->Tf, Tf);
+    table_of(&h->Ti, Ti);
+    table_of(&h->mu1, h->S.mu);
+    table_of(&h->M1b, M1b);
+    table_of(&h->K1b, K1b);
+    table_of(&h->dktmt, ktmt);
+    table(&h->dmix, h->mixes.data(), sizeof(TimeMix) * h->mixes.size());
+    table(&h->dgo, nullptr, 8 * sizeof(int));       // (dgo[5] stays 0: the flag of an inner solve's zero guess)
+    work.add(&h->buf0, (size_t)q.n_slabs * slab);
+    work.add(&h->buf1, (size_t)q.n_slabs * slab);
     h->lu.assign(h->L, nullptr);
     h->lf.assign(h->L, nullptr);
     h->lu2.assign(h->L, nullptr);
     h->ecur.assign(h->L, 0);
     // doubles that hold `count` eigenbasis values (floats with FP32 storage)
     auto ecount = [&](size_t count) { return h->f32 ? (count + 1) / 2 : count; };
-    const size_t ebytes = h->f32 ? sizeof(float) : sizeof(double);
     h->eu.assign(h->L, nullptr);
     h->ef.assign(h->L, nullptr);
     h->eu2.assign(h->L, nullptr);
+    // (the padded modes of the eigenbasis vectors start, and stay, zero)
     for (int l = 1; l < h->L && !(h->cyc && h->basis == 0); ++l) {
-        if (!dalloc(&h->lu[l], (size_t)h->lev_S[l] * slab) || !dalloc(&h->lf[l], (size_t)h->lev_S[l] * slab))
-            return cleanup(STH_ENOMEM, "device allocation failed");
-        if (h->basis == 1 && !h->f32 && !dalloc(&h->lu2[l], (size_t)h->lev_S[l] * slab))
-            return cleanup(STH_ENOMEM, "device allocation failed");
-        if (h->f32) {
-            const size_t c = ecount((size_t)h->lev_S[l] * slab);
-            if (!dalloc(&h->eu[l], c) || !dalloc(&h->ef[l], c) || !dalloc(&h->eu2[l], c))
-                return cleanup(STH_ENOMEM, "device allocation failed");
-        }
+        DeviceBlock& block = h->basis == 1 ? zeros : work;
+        const size_t c = (size_t)h->lev_S[l] * slab;
+        block.add(&h->lu[l], c);
+        block.add(&h->lf[l], c);
+        if (h->basis == 1 && !h->f32) block.add(&h->lu2[l], c);
+        if (h->f32)
+            for (auto* v : {&h->eu[l], &h->ef[l], &h->eu2[l]}) block.add(v, ecount(c));
     }
-    if (hipMalloc((void**)&h->dmix, sizeof(TimeMix) * h->mixes.size()) != hipSuccess)
-        return cleanup(STH_ENOMEM, "device allocation failed");
-    if (hipMemcpyAsync(h->dmix, h->mixes.data(), sizeof(TimeMix) * h->mixes.size(), hipMemcpyHostToDevice, s) !=
-        hipSuccess)
-        return cleanup(STH_EHIP, "upload of the setup failed");
     std::vector<double> Cf, Ci, Gf;
     if (h->basis == 1 || h->batches) {
         // C = M_1 U = U^{-T} (from U^T M_1 U = I)
@@ -1659,86 +1685,62 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
                 Cf[(size_t)i * np + j] = c;
                 Ci[(size_t)j * np + i] = c;
             }
-        h->n_cpartial = (long)cycle_partials(q, (size_t)h->L, h->Nxe);
-        if (!dalloc(&h->cpartial, (size_t)h->n_cpartial) ||
-            !dalloc(&h->Cf, (size_t)np * np) || !dalloc(&h->Ci, (size_t)np * np) ||
-            !dalloc(&h->e0, ecount((size_t)q.n_slabs * eslab)) ||
-            (h->basis == 1 && !dalloc(&h->e1, ecount((size_t)q.n_slabs * eslab))) ||
-            (h->basis == 1 && !dalloc(&h->e2, ecount((size_t)q.n_slabs * eslab))) ||
-            (third_buffer(q, (size_t)h->L) && !dalloc(&h->e3, ecount((size_t)q.n_slabs * eslab))))
-            return cleanup(STH_ENOMEM, "device allocation failed");
-        // the padded modes of the eigenbasis vectors start (and stay) zero
-        for (double* v : {h->e0, h->e1, h->e2, h->e3})
-            if (v && hipMemsetAsync(v, 0, ebytes * (size_t)q.n_slabs * eslab, s) != hipSuccess)
-                return cleanup(STH_EHIP, "clearing the eigenbasis vectors failed");
-        for (int l = 1; l < h->L; ++l) {
-            for (double* v : {h->lu[l], h->lf[l], h->lu2[l]})
-                if (v && hipMemsetAsync(v, 0, sizeof(double) * (size_t)h->lev_S[l] * slab, s) != hipSuccess)
-                    return cleanup(STH_EHIP, "clearing the eigenbasis vectors failed");
-            for (double* v : {h->eu[l], h->ef[l], h->eu2[l]})
-                if (v && hipMemsetAsync(v, 0, ebytes * (size_t)h->lev_S[l] * slab, s) != hipSuccess)
-                    return cleanup(STH_EHIP, "clearing the eigenbasis vectors failed");
-        }
+        table_of(&h->Cf, Cf);
+        table_of(&h->Ci, Ci);
         // mode weights of the lower bound of the B-spline residual norm
-        const std::vector<double> vwh = residual_mode_weights(h->S);
-        if (!dalloc(&h->vw, (size_t)2 * n))
-            return cleanup(STH_ENOMEM, "device allocation failed");
-        if (hipMemcpyAsync(h->Cf, Cf.data(), Cf.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(h->Ci, Ci.data(), Ci.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(h->vw, vwh.data(), vwh.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess)
-            return cleanup(STH_EHIP, "upload of the setup failed");
+        table_of(&h->vw, residual_mode_weights(h->S));
         if (h->dim == 2 && xform2d_supported(np)) {
             // G = C^T C for the exact residual norm
             Gf.assign((size_t)np * np, 0.0);
             for (int i = 0; i < n; ++i)
-                for (int j = 0; j < n; ++j) {
-                    double g = 0.0;
-                    for (int k = 0; k < n; ++k) g += Cf[(size_t)k * np + i] * Cf[(size_t)k * np + j];
-                    Gf[(size_t)i * np + j] = g;
+                for (int k = 0; k < n; ++k) {
+                    const double c = Cf[(size_t)k * np + i];
+                    for (int j = 0; j < n; ++j) Gf[(size_t)i * np + j] += c * Cf[(size_t)k * np + j];
                 }
-            if (!dalloc(&h->Gf, (size_t)np * np) ||
-                hipMemcpyAsync(h->Gf, Gf.data(), Gf.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess)
-                return cleanup(STH_EHIP, "upload of the setup failed");
+            table_of(&h->Gf, Gf);
         }
+        zeros.add(&h->e0, ecount((size_t)q.n_slabs * eslab));
+        if (h->basis == 1) zeros.add(&h->e1, ecount((size_t)q.n_slabs * eslab));
+        if (h->basis == 1) zeros.add(&h->e2, ecount((size_t)q.n_slabs * eslab));
+        if (third_buffer(q, (size_t)h->L)) zeros.add(&h->e3, ecount((size_t)q.n_slabs * eslab));
     }
-    // packed panels of the FP64 per-axis transforms
+    // packed panels of the FP64 transforms
     const size_t eo_len = q.prec == STH_FP64 ? xform_eo_pack_len(n) : 0;
-    std::vector<double> eo_host[4];
+    std::vector<double> panels(eo_len);
     for (int i = 0; i < (h->basis == 1 || h->batches ? 4 : 2) && eo_len > 0; ++i) {
-        eo_host[i].assign(eo_len, 0.0);
-        xform_eo_pack(i % 2 == 1, i < 2 ? Tf.data() : Cf.data(), n, np, eo_host[i].data());
-        if (!dalloc(&h->eo[i], eo_len)) return cleanup(STH_ENOMEM, "device allocation failed");
-        if (hipMemcpyAsync(h->eo[i], eo_host[i].data(), eo_len * 8, hipMemcpyHostToDevice, s) != hipSuccess)
-            return cleanup(STH_EHIP, "upload of the setup failed");
+        xform_eo_pack(i % 2 == 1, i < 2 ? Tf.data() : Cf.data(), n, np, panels.data());
+        table_of(&h->eo[i], panels);
     }
-    if (h->cyc) {
-        if (!dalloc(&h->cyc_tab, cycles_table_len(h->Nt, h->L, h->Nxe)))
-            return cleanup(STH_ENOMEM, "device allocation failed");
+    tables.add(&h->partial, 2 * kNormBlocks);
+    tables.add(&h->dnorm, kNormSlots);
+    tables.add(&h->dthr, 2);
+    if (h->basis == 1 || h->batches) {
+        h->n_cpartial = (long)cycle_partials(q, (size_t)h->L, h->Nxe);
+        tables.add(&h->cpartial, (size_t)h->n_cpartial);
     }
-    const unsigned mapped = hipHostMallocMapped | hipHostMallocCoherent;
-    if (hipHostMalloc((void**)&h->hnorm, kNormSlots * sizeof(double), mapped) != hipSuccess ||
-        hipHostMalloc((void**)&h->hflag, 5 * sizeof(int), mapped) != hipSuccess ||
-        hipHostMalloc((void**)&h->hcyc, kCycSums * sizeof(double), mapped) != hipSuccess)
-        return cleanup(STH_ENOMEM, "pinned host allocation failed");
-    if (hipHostGetDevicePointer((void**)&h->hnorm_dev, h->hnorm, 0) != hipSuccess ||
-        hipHostGetDevicePointer((void**)&h->hcyc_dev, h->hcyc, 0) != hipSuccess ||
-        hipHostGetDevicePointer((void**)&h->hflag_dev, h->hflag, 0) != hipSuccess)
-        return cleanup(STH_EHIP, "pinned host memory is not mapped");
-    if (hipMalloc((void**)&h->dgo, 8 * sizeof(int)) != hipSuccess ||
-        hipMalloc((void**)&h->dthr, 2 * sizeof(double)) != hipSuccess)
+    if (h->cyc) tables.add(&h->cyc_tab, cycles_table_len(h->Nt, h->L, h->Nxe));
+    if (!tables.allocate(&h->tables) || !work.allocate(&h->work) || !zeros.allocate(&h->zeros))
         return cleanup(STH_ENOMEM, "device allocation failed");
-    // dgo[5] stays 0: the flag of an inner solve's zero guess
-    if (hipMemsetAsync(h->dgo, 0, 8 * sizeof(int), s) != hipSuccess)
-        return cleanup(STH_EHIP, "clearing the device flags failed");
+    if (zeros.count && hipMemsetAsync(h->zeros, 0, zeros.count * sizeof(double), s) != hipSuccess)
+        return cleanup(STH_EHIP, "clearing the eigenbasis vectors failed");
+    // sums and flags for the host, one line each
+    constexpr size_t kHostCyc = 16, kHostFlag = 48;
+    static_assert(kNormSlots <= kHostCyc && kCycSums <= kHostFlag - kHostCyc, "sections of the host's block");
+    const unsigned mapped = hipHostMallocMapped | hipHostMallocCoherent;
+    double* hdev = nullptr;
+    if (hipHostMalloc((void**)&h->hnorm, (kHostFlag + 8) * sizeof(double), mapped) != hipSuccess)
+        return cleanup(STH_ENOMEM, "pinned host allocation failed");
+    if (hipHostGetDevicePointer((void**)&hdev, h->hnorm, 0) != hipSuccess)
+        return cleanup(STH_EHIP, "pinned host memory is not mapped");
+    h->hnorm_dev = hdev;
+    h->hcyc = h->hnorm + kHostCyc;
+    h->hcyc_dev = hdev + kHostCyc;
+    h->hflag = (int*)(h->hnorm + kHostFlag);
+    h->hflag_dev = (int*)(hdev + kHostFlag);
     for (auto& e : h->evring)
         if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
             return cleanup(STH_EHIP, "event creation failed");
-    if (hipMemcpyAsync(h->Tf, Tf.data(), Tf.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(h->Ti, Ti.data(), Ti.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(h->mu1, h->S.mu.data(), (size_t)n * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(h->M1b, M1b.data(), M1b.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(h->K1b, K1b.data(), K1b.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(h->dktmt, ktmt.data(), ktmt.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
+    if (hipMemcpyAsync(h->tables, upload.data(), upload.size() * sizeof(double), hipMemcpyHostToDevice, s) != hipSuccess ||
         (h->cyc && launch_cycles_table(h->dim, h->Nt, h->L, h->dmix, h->dktmt, h->mu1, h->n, h->Nxe, h->tr, h->vw,
                                        h->cyc_tab, s) != hipSuccess) ||
         hipStreamSynchronize(s) != hipSuccess)
@@ -3315,23 +3317,9 @@ int sth_destroy(sth_handle* h) {
         if (q) (void)hipFree(q);
     for (double* q : h->mr)
         if (q) (void)hipFree(q);
-    for (double* q : h->eo)
+    for (double* q : {h->tables, h->work, h->zeros, h->kv, h->kz, h->kc, h->kpart})
         if (q) (void)hipFree(q);
-    if (h->cyc_tab) (void)hipFree(h->cyc_tab);
-    double* ptrs[] = {h->Tf, h->Ti, h->mu1, h->M1b, h->K1b, h->buf0, h->buf1, h->partial, h->dnorm, h->dktmt,
-                      h->Cf, h->Ci, h->Gf, h->e0, h->e1, h->e2, h->e3, h->cpartial, h->kv, h->kz, h->kc,
-                      h->kpart, h->vw};
-    for (double* q : ptrs)
-        if (q) (void)hipFree(q);
-    for (auto* vec : {&h->lu, &h->lf, &h->lu2, &h->eu, &h->ef, &h->eu2})
-        for (double* q : *vec)
-            if (q) (void)hipFree(q);
     if (h->hnorm) (void)hipHostFree(h->hnorm);
-    if (h->hflag) (void)hipHostFree(h->hflag);
-    if (h->hcyc) (void)hipHostFree(h->hcyc);
-    if (h->dthr) (void)hipFree(h->dthr);
-    if (h->dmix) (void)hipFree(h->dmix);
-    if (h->dgo) (void)hipFree(h->dgo);
     for (auto e : h->evring)
         if (e) (void)hipEventDestroy(e);
     if (h->khost) (void)hipHostFree(h->khost);
