@@ -715,12 +715,9 @@ void k_residual3d(int n, int hx_n, int hy_n, int hpx, int hpy, int tiles_x,
 
 // Tile of the 3-D residual: the hx x hy columns (at most 512 threads, LDS for
 // two blocks per compute unit if some tile allows it, else for one) with the
-// fewest threads over the whole image, halo and overhang included.
-struct Res3Tile {
-    int hx, hy, hpx, hpy, tiles_x, tiles_y;
-    size_t shm;
-};
-static bool residual3d_tile(int Nt, int p, int n, Res3Tile* best) {
+// fewest threads over the whole image, halo and overhang included.  (The search
+// takes 2 to 5 us of host time: once, at set-up.)
+bool residual3d_tile(int Nt, int p, int n, Res3Tile* best) {
     const int B = 2 * p + 1;
     for (size_t cap : {size_t(80) * 1024, size_t(160) * 1024}) {
         long cost = -1;
@@ -753,8 +750,9 @@ static bool residual3d_tile(int Nt, int p, int n, Res3Tile* best) {
 static int residual3d_planes(int n, int p, long tiles) {
     int best = n;
     double cost = -1.0;
-    for (int c = 1; c <= n; ++c) {
+    for (int c = 1; c <= n;) {          // (each chunk length once, with its fewest chunks)
         const int zc = (n + c - 1) / c;
+        c = zc > 1 ? (n + zc - 2) / (zc - 1) : n + 1;
         const long blocks = tiles * ((n + zc - 1) / zc);
         const double t = (double)((blocks + 511) / 512) * (zc + 2 * p / 3.0);
         if (cost < 0 || t < cost) {
@@ -767,9 +765,9 @@ static int residual3d_planes(int n, int p, long tiles) {
 
 template <int NT, int P>
 static hipError_t residual3d_launch(int n, const double* M1b, const double* K1b, const double* ktmt, const double* f,
-                                    const double* u, double* r, long s0, long ns, double sign, hipStream_t st) {
-    Res3Tile t{};
-    if (!residual3d_tile(NT, P, n, &t)) return hipErrorInvalidValue;
+                                    const double* u, double* r, long s0, long ns, double sign, const Res3Tile& t,
+                                    hipStream_t st) {
+    if (!t.hx) return hipErrorInvalidValue;
     static std::atomic<bool> attr_set{false};       // set once; the attribute call is idempotent
     if (!attr_set.load(std::memory_order_acquire)) {
         const hipError_t e = hipFuncSetAttribute((const void*)k_residual3d<NT, P>,
@@ -790,11 +788,11 @@ static hipError_t residual3d_launch(int n, const double* M1b, const double* K1b,
 template <int P>
 static hipError_t residual3d_nt(int Nt, int n, const double* M1b, const double* K1b, const double* ktmt,
                                 const double* f, const double* u, double* r, long s0, long ns, double sign,
-                                hipStream_t st) {
+                                const Res3Tile& t, hipStream_t st) {
 #define STH_R3_CASE(NTV)                                                                                      \
     case NTV:                                                                                                  \
         if constexpr (NTV > P && !(P == 4 && NTV == 8))                                                        \
-            return residual3d_launch<NTV, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);                    \
+            return residual3d_launch<NTV, P>(n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, t, st);                 \
         return hipErrorInvalidValue;
     switch (Nt) {
         STH_R3_CASE(2) STH_R3_CASE(3) STH_R3_CASE(4) STH_R3_CASE(5) STH_R3_CASE(6) STH_R3_CASE(7) STH_R3_CASE(8)
@@ -880,7 +878,7 @@ bool residual_norm_fused(int dim, int n, int p, int Nt) { return residual_marche
 
 hipError_t launch_residual(int dim, int Nt, int p, int n, const double* M1b, const double* K1b,
                            const TimeOp& op, const double* ktmt, const double* f, const double* u, double* r,
-                           long s0, long ns, double sign, hipStream_t st) {
+                           long s0, long ns, double sign, const Res3Tile& tile, hipStream_t st) {
     if (ns <= 0) return hipSuccess;
     if (p < 1 || p > kMaxP) return hipErrorInvalidValue;
     if (residual_marches(dim, n, p, Nt) || (dim == 2 && residual_marches_narrow(n, p, Nt, ns))) {
@@ -909,10 +907,10 @@ hipError_t launch_residual(int dim, int Nt, int p, int n, const double* M1b, con
         // with 7 rows it is ahead, 763 against 828 us)
         if (p == 4 && Nt == 8) return residual_dim<3>(Nt, p, n, M1b, K1b, op, f, u, r, s0, ns, sign, st);
         switch (p) {
-            case 1: return residual3d_nt<1>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
-            case 2: return residual3d_nt<2>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
-            case 3: return residual3d_nt<3>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
-            case 4: return residual3d_nt<4>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, st);
+            case 1: return residual3d_nt<1>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, tile, st);
+            case 2: return residual3d_nt<2>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, tile, st);
+            case 3: return residual3d_nt<3>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, tile, st);
+            case 4: return residual3d_nt<4>(Nt, n, M1b, K1b, ktmt, f, u, r, s0, ns, sign, tile, st);
         }
     }
     return hipErrorInvalidValue;

@@ -61,10 +61,16 @@ constexpr int kNoFlagYet = -1, kFlagSkipped = 2;                // kFlagSkipped:
 // r = f + sign * (-(A u)_n + (B u)_{n-1}) for slabs [s0, s0+ns) of a vector
 // with slab length Nt*n^dim; the coupling uses slab s-1 of the same vector
 // when s > 0.  f may be null (treated as zero).  M1b/K1b: bands [n][2p+1];
-// ktmt: device copy of op (K_t then M_t, kNt x kNt each).
+// ktmt: device copy of op (K_t then M_t, kNt x kNt each); tile: of
+// residual3d_tile(Nt, p, n, ..) in three dimensions.
+struct Res3Tile {
+    int hx = 0, hy = 0, hpx = 0, hpy = 0, tiles_x = 0, tiles_y = 0;
+    size_t shm = 0;
+};
+bool residual3d_tile(int Nt, int p, int n, Res3Tile* best);
 hipError_t launch_residual(int dim, int Nt, int p, int n, const double* M1b, const double* K1b,
                            const TimeOp& op, const double* ktmt, const double* f, const double* u, double* r,
-                           long s0, long ns, double sign, hipStream_t st);
+                           long s0, long ns, double sign, const Res3Tile& tile, hipStream_t st);
 
 // The residual with its squared norm (2-D images of 128 or more columns and
 // small degrees: residual_norm_fused): r = f - L u over all ns slabs, and

@@ -75,6 +75,7 @@ struct sth_handle {
     // transforms: the others never take one, and their odd n has no split)
     double* eo[4] = {};
     double* mu1 = nullptr;
+    Res3Tile res3;                      // of the 3-D residual
     double* M1b = nullptr;
     double* K1b = nullptr;
     double* dktmt = nullptr;            // per level: K_t then M_t (kNt x kNt each)
@@ -355,7 +356,7 @@ static int residual(sth_handle* h, int lvl, const double* f, const double* u, do
     double bytes = dof * (f ? 24.0 : 16.0);
     Timed tm(h, STH_K_RESIDUAL, flops, bytes, st);
     HIPCHK(launch_residual(h->dim, h->Nt, h->p, h->n, h->M1b, h->K1b, h->ops[lvl],
-                           h->dktmt + (size_t)lvl * 2 * kNt * kNt, f, u, r, s0, ns, sign, st));
+                           h->dktmt + (size_t)lvl * 2 * kNt * kNt, f, u, r, s0, ns, sign, h->res3, st));
     return STH_OK;
 }
 
@@ -1533,6 +1534,7 @@ static int setup_problem(Problem q, hipStream_t s, sth_handle** out) {
     h->nu_post = q.nu_post;
     h->prec = q.prec;
     h->basis = q.basis;
+    if (h->dim == 3) (void)residual3d_tile(h->Nt, h->p, h->n, &h->res3);
     if (h->basis != 0 && h->basis != 1) {
         delete h;
         return fail(STH_EINVAL, "iterate_basis must be 0 or 1");
