@@ -26,9 +26,11 @@
 // 3.9 ms per batch against 2.2 ms on 65536 modes x 1024 slabs x 3).  Rows
 // between lanes and the recurrence x_s = a_s + gamma x_{s-1} of the exact
 // solve go by data-parallel primitives (through LDS shuffles 9 to 14 % slower);
-// no barrier inside a cycle.  A block
-// takes 8 or 16 modes, pieces of 64 or 128 bytes of each row, transposed
-// through LDS on the way in and out.
+// no barrier inside a cycle.  A block takes eight modes, pieces of 64 bytes of
+// each row (float: 32), transposed through LDS on the way in and out.  (Blocks
+// of 16, whole lines, are 4 to 15 % slower in whole solves of 8 thousand to 262
+// thousand modes, in float as well: one block per compute unit, whose transfers
+// nothing overlaps.)
 //
 // A cycle takes about 5 N_t + 10 multiply-adds per unknown and no memory
 // traffic, against 40 B per unknown of passes over the vectors level by
@@ -127,15 +129,15 @@ typedef const __attribute__((address_space(4))) double* uptr;
 
 // ONE: a single level.  A cycle is the exact solve e = L^{-1} r, whose result
 // goes to uout, and r becomes its residual r - L e (m = 1).
-// MB: modes (waves) per block.
 // Waves per SIMD to leave registers for: two blocks of 8 per compute unit up
 // to 24 values per lane, so that one block's transfers overlap the other's
 // cycles (a first batch of 8 on 65536 modes x 512 slabs x 3: 722 against 1094
 // us; 10404 modes x 150 slabs x 6: 128 against 170 us a batch; a handful of
 // spilled registers costs less), else one block.
-template <int NT, int LA, int MB> constexpr int cycles_waves() { return MB == 16 || LA * NT <= 24 ? 4 : 2; }
-template <int NT, int LA, int MB, typename VT, bool ONE>
-__global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_waves<NT, LA, MB>()))) void k_cycles(CycArgs a, int len) {
+constexpr int MB = 8;                           // modes (waves) per block
+template <int NT, int LA> constexpr int cycles_waves() { return LA * NT <= 24 ? 4 : 2; }
+template <int NT, int LA, typename VT, bool ONE>
+__global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_waves<NT, LA>()))) void k_cycles(CycArgs a, int len) {
     constexpr int NM = NT * NT, E = LA * NT;
     constexpr int KB = E < 12 ? E : 12;         // rows per transposition
     constexpr int PITCH = 72;                   // 64 lanes, padded against bank conflicts of the eight modes
@@ -143,15 +145,11 @@ __global__ __launch_bounds__(64 * MB) __attribute__((amdgpu_waves_per_eu(cycles_
     __shared__ double red[MB][kMaxBatch + 1][3];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Blocks whose pieces are whole lines go round over the XCDs (32768 modes x
-    // 128 slabs x 4: 126 against 134 us for 8 cycles).  Else the blocks of one
-    // XCD take a contiguous range of modes, so that the lines that neighbours
-    // share stay in its L2 (against eight modes' neighbours only: 66564 modes x
-    // 64 slabs x 6, whose rows do not start on a line, 270 -> 236 us, 65536 x
-    // 1024 x 3 1.32 -> 1.21 ms).
-    const bool whole = MB * sizeof(VT) == 128 && a.Nx % MB == 0;
-    const long m0 = (whole ? (long)blockIdx.x
-                           : (long)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8) * MB;
+    // The blocks of one XCD take a contiguous range of modes, so that the lines
+    // that neighbours share stay in its L2 (against eight modes' neighbours only:
+    // 66564 modes x 64 slabs x 6, whose rows do not start on a line, 270 -> 236
+    // us, 65536 x 1024 x 3 1.32 -> 1.21 ms).
+    const long m0 = ((long)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8) * MB;
     const long mode = m0 + wave < a.Nx ? m0 + wave : a.Nx - 1;
     const double* tab0 = a.tab + mode * len;
     const double* ptab0 = a.tab + a.Nx * len;
@@ -553,16 +551,9 @@ int cycles_lane_slabs(int Nt, int L, long S) {
 
 bool cycles_supported(int Nt, int L, long S) { return cycles_lane_slabs(Nt, L, S) > 0; }
 
-// Modes per block: 16, whole 128-byte lines of each row, where the registers
-// allow 16 waves per compute unit and the modes still give two blocks to each
-// (a plain copy in this pattern runs at 4.4 TB/s, in 64-byte pieces at 3.5);
-// else 8.
-template <int NT, int LA> constexpr bool cycles_wide() { return LA <= 2 || (LA == 4 && NT <= 5) || (LA == 8 && NT == 2); }
-static long cycles_blocks(int MB, long Nx) {
-    return ((Nx + MB - 1) / MB + 7) / 8 * 8;
-}
+static long cycles_blocks(long Nx) { return ((Nx + MB - 1) / MB + 7) / 8 * 8; }
 
-long cycles_partials(long Nx) { return 3L * (kMaxBatch + 1) * cycles_blocks(8, Nx); }
+long cycles_partials(long Nx) { return 3L * (kMaxBatch + 1) * cycles_blocks(Nx); }
 
 size_t cycles_table_len(int Nt, int L, long Nx) { return (size_t)Nx * tab_len(Nt, L) + 2 * Nt * Nt; }
 
@@ -619,18 +610,18 @@ __global__ __launch_bounds__(256) void k_cycle_sums(const double* __restrict__ p
     }
 }
 
-template <int NT, int LA, int MB, typename VT>
+template <int NT, int LA, typename VT>
 static hipError_t cycles_go(const CycArgs& a, long* blocks, hipStream_t st) {
     const int len = tab_len(NT, a.L);
-    *blocks = cycles_blocks(MB, a.Nx);
+    *blocks = cycles_blocks(a.Nx);
     const dim3 grid((unsigned)*blocks), block(64 * MB);
     if constexpr (LA > 1)
         if (a.L > 1 && !a.steps) {
-            hipLaunchKernelGGL((k_cycles<NT, LA, MB, VT, false>), grid, block, 0, st, a, len);
+            hipLaunchKernelGGL((k_cycles<NT, LA, VT, false>), grid, block, 0, st, a, len);
             return hipGetLastError();
         }
     if constexpr (sizeof(VT) == 8) {
-        hipLaunchKernelGGL((k_cycles<NT, LA, MB, VT, true>), grid, block, 0, st, a, len);
+        hipLaunchKernelGGL((k_cycles<NT, LA, VT, true>), grid, block, 0, st, a, len);
         return hipGetLastError();
     }
     return hipErrorInvalidValue;        // (float vectors: several levels only)
@@ -638,12 +629,8 @@ static hipError_t cycles_go(const CycArgs& a, long* blocks, hipStream_t st) {
 
 template <int NT, typename VT>
 static hipError_t cycles_launch(const CycArgs& a, int LA, long* blocks, hipStream_t st) {
-#define STH_CYC(LAV)                                                                                       \
-    if (LA == LAV) {                                                                                       \
-        if constexpr (cycles_wide<NT, LAV>())                                                              \
-            if (a.Nx >= 16 * 512) return cycles_go<NT, LAV, 16, VT>(a, blocks, st);                        \
-        return cycles_go<NT, LAV, 8, VT>(a, blocks, st);                                                   \
-    }
+#define STH_CYC(LAV) \
+    if (LA == LAV) return cycles_go<NT, LAV, VT>(a, blocks, st);
     STH_CYC(1) STH_CYC(2) STH_CYC(4) STH_CYC(8)
     if constexpr (NT <= 3) { STH_CYC(16) }
 #undef STH_CYC
@@ -677,7 +664,7 @@ hipError_t launch_cycles(int Nt, int L, const double* tab, long Nx, double omega
                          const SolveStart* start) {
     const int LA = cycles_lane_slabs(Nt, L, S);
     if (!LA || m < 0 || m > kMaxBatch || (L == 1 && m > 1)) return hipErrorInvalidValue;
-    if (partial && 3L * (m + 1) * cycles_blocks(8, Nx) > max_partial) return hipErrorInvalidValue;
+    if (partial && 3L * (m + 1) * cycles_blocks(Nx) > max_partial) return hipErrorInvalidValue;
     if ((rout && rout == rin) || (uout && (uout == rin || uout == rout || uout == fh))) return hipErrorInvalidValue;
     if ((rin_lines || rout_lines) && !cycles_lines(Nt, L, S)) return hipErrorInvalidValue;
     const CycArgs a{L, m, 0, rin_lines, rout_lines, S, Nx, omega, tab, rin, fh, rout, uout, partial};

@@ -45,7 +45,7 @@
 namespace sth {
 
 constexpr int kEoMaxJ = 5;                      // 16-column tiles of a panel, per half
-constexpr long kEoFill = 1024;                  // (line tile, panel) pairs that fill the card: one per SIMD
+constexpr long kEoFill = 2048;                  // (line tile, panel) pairs that fill the card: two per SIMD
 
 struct EoArgs {
     const double* in;
@@ -336,8 +336,9 @@ static size_t eo_lds(int n, int nj) { return sizeof(double) * (size_t)eo_rows(n)
 // Column tiles of a panel: as many as LDS and the register budget allow (each
 // panel reads the data again, from L2), fewer where the line tiles alone
 // leave waves idle: then narrower panels shorten both a block's staging and
-// a wave's chain of MFMAs (a slab inverse of 9 images of 300^2: 59 us, against
-// 91 us with the widest panels that fit).
+// a wave's chain of MFMAs (a slab inverse of 9 images of 300^2: 61 us, against
+// 84 us with the widest panels that fit; from 1024 to 2048 pairs 24 images of
+// 256^2 93 -> 81, 36 of 200^2 83 -> 70, at 4096 the same).
 static int eo_panel_tiles(int n, long ntiles) {
     bool rem;
     const int tiles = eo_tiles(n, &rem);

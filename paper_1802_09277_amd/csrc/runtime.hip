@@ -2772,7 +2772,11 @@ static int cyc_continue(sth_handle* h, bool* more) {
     // large vectors (a batch's transfers, 16 B per unknown, cost more than a
     // launch and a host round trip) all but two of them first: the contraction
     // settles on the way, and a batch that ends past the stopping cycle would
-    // be taken again.
+    // be taken again.  (Both ways over 30 shapes: all but two first is ahead
+    // with 16 slabs per lane and, at N_t = 3, with 512 slabs, 201 million
+    // unknowns 8.8 against 10.2 ms, 13 million of 64^2 x 1024 x 3 469 against 559
+    // us; where the first guess is right it costs 3 to 12 %, 25 million of 256^2
+    // x 128 x 3 1604 against 1410 us.)
     int want = 1;
     if (rate > 0.0 && rate < 1.0 && target() > 0.0)
         want = (int)std::min(64.0, std::max(1.0, std::ceil(std::log(target() / v.rn) / std::log(rate) - 0.05)));
