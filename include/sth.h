@@ -151,7 +151,9 @@ void sth_problem_default(sth_problem* p);
 
 /* Device bytes that sth_setup would allocate for this problem (factors,
  * coarse-level vectors and workspaces; not the caller's vectors).  Host
- * only, no allocation: used for admission by memory footprint. */
+ * only, no allocation: used for admission by memory footprint.  (Where the
+ * device has less, sth_setup leaves out the tables of cycles on chip and
+ * solves level by level.) */
 int sth_workspace_bytes(const sth_problem* p, size_t* bytes);
 
 /* Host FP64 setup and upload on `stream`: the 1-D spatial mass and stiffness
@@ -228,9 +230,15 @@ int sth_vcycle(sth_handle* h, const double* f, double* u, void* stream);
  * vectors of sth_vector_len(h) doubles (u holds the initial guess and
  * receives the result).  Blocks the host until the result is in u.  iters
  * and relres (may be NULL) receive the cycle count and the final relative
- * residual (in the eigenbasis iteration an upper bound of it when the
- * two-sided bound decides the test, else the exact value).  From a guess of
- * zeros u may hold intermediate vectors until the call returns.  With
+ * residual: in the eigenbasis iteration that of its iterate u^ with u =
+ * (I (x) U) u^ (an upper bound of it when the two-sided bound decides the
+ * test, else the exact value; from rtol 1e-12 up the residual is carried
+ * from cycle to cycle, within 2e-13 ||f|| of the one formed from u^), which
+ * leaves out the rounding of the coefficients, eps times the ratio of the
+ * extreme spatial eigenvalues (measured up to 3e-11 ||f|| at 256 elements per
+ * axis).  In the coefficient iteration it is the residual of u itself, to a
+ * fiftieth of rtol.  From a guess of zeros u may hold intermediate vectors
+ * until the call returns.  With
  * iterate_basis 1 and transform_prec FP32 or BF16x3 the solve is an FP64
  * defect correction: each outer step forms the FP64 residual and its exact
  * norm, and an eigenbasis solve with reduced-precision transforms reduces
@@ -260,9 +268,12 @@ int sth_solve_fgmres(sth_handle* h, const double* f, double* u, double rtol, int
  * stream; a new f or u, or a change of the timing mask, recaptures).
  * enable = 0 launches every kernel individually; so does kernel timing
  * (sth_timing), which needs events around the individual launches.  Solves
- * that run batches of cycles on chip (V(1,1) with FP64 or mixed eigenbasis
- * cycles, N_t <= 6, up to four levels, 512 slabs or 1024 for N_t <= 3,
- * rtol >= 1e-12) have a few launches in all and are not replayed. */
+ * that run batches of cycles on chip have a few launches in all and are not
+ * replayed: V(1,1), N_t <= 6, up to four levels, 512 slabs or 1024 for
+ * N_t <= 3, rtol >= 1e-12 (coefficient iteration: 100 eps times the ratio of
+ * the extreme spatial eigenvalues, if that is more), enough slabs for the
+ * modes that it pays, and of the mixed forms those with FP64 vectors or FP32
+ * transforms and degree <= 2. */
 int sth_use_graphs(sth_handle* h, int enable);
 
 /* Speculative cycles (default on; eigenbasis iteration with V(1,1) cycles,
