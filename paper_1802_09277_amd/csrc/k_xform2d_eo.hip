@@ -18,7 +18,7 @@
 // barriers; the inverse exchanges its four parts tile by tile through LDS.
 // The four waves of an image read it again, from L1 and L2 (forward).  Bound
 // by latency at two to four waves per SIMD (registers) and, for many images,
-// by the MFMAs (65^2: 90 a wave and image, 21 % busy).  Against the image and
+// by the MFMAs (65^2: 90 a wave and image, 24 to 30 % busy).  Against the image and
 // U in LDS, eight waves to an image, two barriers to a product: a slab inverse
 // (a transform each way and the temporal solve) of 256 x 5 images of 65^2 142
 // -> 86 us (forward 62 -> 41, inverse 67 -> 35), 192 x 5 of 61^2 83 -> 56,

@@ -11,8 +11,9 @@
 //            x_i = p_i + q_i, x_{n-1-i} = p_i - q_i, i < h1.
 // FP64 matrix and vector rate are the same on this card (77.6 and 70 TFLOP/s
 // measured in registers), so halving the multiply-adds is what counts.  Large
-// n is bound by the MFMAs (n = 256, 3072 images: 0.95 ms per axis, 54
-// TFLOP/s at 81 % MFMA busy, the clock near 1.95 GHz under this load),
+// n is bound by the MFMAs (n = 256, 3072 images: 0.92 to 1.01 ms per axis, 51 to
+// 56 TFLOP/s at 72 to 78 % MFMA busy, the clock 2.1 to 2.2 GHz under this load,
+// 2.4 without; 384 images 127 to 144 us at 59 to 66 %),
 // small n by HBM and latency.  A slab inverse (two transforms of each axis
 // and the temporal solve), against panels of the full matrix for padded
 // widths that are a multiple of 32 and tiles staged per block otherwise:
